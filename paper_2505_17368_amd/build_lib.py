@@ -15,12 +15,13 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libhenn.so")
-# (source, object, extra flags): henn_search.hip builds in four parts (host
-# functions and root kernels; the FP32 / BF16 / FP8 search kernels)
-SOURCES = [("henn_api.hip", "henn_api", []),
-           *[("henn_search.hip", f"henn_search_{p}", [f"-DHENN_PART={p}"]) for p in range(4)],
-           ("henn_build.hip", "henn_build", []), ("henn_knn.hip", "henn_knn", []),
-           ("henn_serve.hip", "henn_serve", [])]
+# (source, object, extra flags): henn_search.hip builds in ten parts (host
+# functions and root kernels; the FP32 / BF16 / FP8 search kernels for each
+# form of the beam's list), the slow ones first
+SOURCES = [*[("henn_search.hip", f"henn_search_{p}", [f"-DHENN_PART={p}"])
+             for p in (*range(1, 10), 0)],
+           ("henn_knn.hip", "henn_knn", []), ("henn_api.hip", "henn_api", []),
+           ("henn_build.hip", "henn_build", []), ("henn_serve.hip", "henn_serve", [])]
 ARCH = os.environ.get("HENN_OFFLOAD_ARCH", "gfx950")
 FLAGS = ["-O3", "-fPIC", "-std=c++17", f"--offload-arch={ARCH}", "-Xclang", "-target-feature",
          "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",

@@ -1194,7 +1194,10 @@ static henn_status search_impl(const henn_index* idx, const float* Q, int64_t nq
     if (a.vis_bytes == 1 && (sp->flags & HENN_SEARCH_VIS16)) a.vis_bytes = 2;
     int wpb = want_wpb > 0 ? want_wpb : 4;
     if (wpb != 1 && wpb != 2 && wpb != 4 && wpb != 8) return fail(HENN_E_INVAL, "waves_per_block");
-    while (wpb > 1 && search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes) * wpb > 65536) wpb /= 2;
+    const bool exact_vis = (sp->flags & HENN_SEARCH_EXACT_VISITED) != 0;
+    while (wpb > 1 &&
+           search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes, exact_vis) * wpb > 65536)
+      wpb /= 2;
     sh.waves_per_block = wpb;
     sh.persistent = want_pers;
     sh.blocks = 0;
@@ -1202,7 +1205,6 @@ static henn_status search_impl(const henn_index* idx, const float* Q, int64_t nq
     // scratch: the persistent work counter (256 B), the root-scan data, the
     // exact visited sets
     const int rmode = root_mode(idx, sp);
-    const bool exact_vis = (sp->flags & HENN_SEARCH_EXACT_VISITED) != 0;
     if (sh.persistent || rmode != 0 || exact_vis) {
       const int64_t need = search_workspace_bytes(idx, nq, sp);
       if (fixed) {

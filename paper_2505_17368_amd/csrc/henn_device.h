@@ -107,7 +107,7 @@ __device__ inline void wave_sync() {
 
 __device__ inline int lane_id() { return (int)(threadIdx.x & 63); }
 
-__device__ inline uint64_t ballot(bool p) { return __ballot(p); }
+__device__ inline uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
 __device__ inline int popc64(uint64_t m) { return __popcll(m); }
 
@@ -394,15 +394,34 @@ __device__ inline float group_distance(const float (&q)[CPL][8], const void* row
   return out[0];
 }
 
-// Loads this lane's query slice (FP32 source, chunked; zero beyond d).
+// Loads this lane's query slice (FP32 source, chunked; zero beyond d).  The
+// offsets are clamped into the row and the values dropped afterwards, so that
+// every load is in flight at once without branches; 16 bytes each where rows
+// start 16-byte aligned.
 template <int CPL>
 __device__ inline void load_query(const float* qrow, int d, int t, float (&q)[CPL][8]) {
+  if (((d & 3) | (int)(reinterpret_cast<uintptr_t>(qrow) & 15)) == 0) {
 #pragma unroll
-  for (int i = 0; i < CPL; ++i) {
+    for (int i = 0; i < CPL; ++i) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int e = (t * CPL + i) * 8 + j;
-      q[i][j] = e < d ? qrow[e] : 0.0f;
+      for (int j = 0; j < 8; j += 4) {
+        const int e = (t * CPL + i) * 8 + j;
+        const float4 v = *reinterpret_cast<const float4*>(qrow + (e < d ? e : 0));
+        q[i][j] = e < d ? v.x : 0.0f;
+        q[i][j + 1] = e < d ? v.y : 0.0f;
+        q[i][j + 2] = e < d ? v.z : 0.0f;
+        q[i][j + 3] = e < d ? v.w : 0.0f;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int e = (t * CPL + i) * 8 + j;
+        const float v = qrow[e < d ? e : 0];
+        q[i][j] = e < d ? v : 0.0f;
+      }
     }
   }
 }

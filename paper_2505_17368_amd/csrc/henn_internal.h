@@ -254,8 +254,15 @@ inline int default_vis_bits(int ef_need, int64_t n, bool narrow_ok) {
   return b;
 }
 
-// Shared-memory bytes one wave needs for a given list capacity.
-size_t search_lds_per_wave(int ef_cap, int vis_bits, int vis_bytes);
+// Where a beam of capacity ef_cap keeps its list: 64-position blocks in
+// registers, or 0 for LDS.  Two blocks a lane are four registers and four are
+// eight; past that the list's compares and lane moves would cost more than
+// the LDS form's searches.
+constexpr int list_blocks(int ef_cap) { return ef_cap <= 128 ? 2 : ef_cap <= 256 ? 4 : 0; }
+
+// Shared-memory bytes one wave needs for a given list capacity (exact: the
+// exact visited set, whose list is in LDS at every capacity).
+size_t search_lds_per_wave(int ef_cap, int vis_bits, int vis_bytes, bool exact = false);
 
 // Whether every layer's rows have 32-bit first-chunk indices
 // (size * chunks per row < 2^32), which the search kernel needs.
@@ -264,19 +271,15 @@ bool rows_addressable(const SearchArgs& a);
 // Enqueues the search kernel.  Returns false when no kernel instance
 // matches (storage, lanes_per_vec, chunks_per_lane) or !rows_addressable(a).
 bool launch_search(int storage, const SearchArgs& a, const LaunchShape& s, hipStream_t st);
-// The per-storage halves of launch_search and launch_serve_step.
-bool launch_search_f32(const SearchArgs& a, const LaunchShape& s, hipStream_t st);
-bool launch_search_bf16(const SearchArgs& a, const LaunchShape& s, hipStream_t st);
-bool launch_search_fp8(const SearchArgs& a, const LaunchShape& s, hipStream_t st);
+// Its part for one (rows, list_blocks) pair, and the serving step's.
+template <int KIND, int NB>
+bool search_dispatch(const SearchArgs& a, const LaunchShape& s, hipStream_t st);
+template <int KIND, int NB>
+bool serve_dispatch(const SearchArgs& a, const ServeArgs& sv, const LaunchShape& sh,
+                    hipStream_t st);
 
 bool launch_serve_step(int storage, const SearchArgs& a, const ServeArgs& sv,
                        const LaunchShape& sh, hipStream_t st);
-bool launch_serve_f32(const SearchArgs& a, const ServeArgs& sv, const LaunchShape& sh,
-                      hipStream_t st);
-bool launch_serve_bf16(const SearchArgs& a, const ServeArgs& sv, const LaunchShape& sh,
-                       hipStream_t st);
-bool launch_serve_fp8(const SearchArgs& a, const ServeArgs& sv, const LaunchShape& sh,
-                      hipStream_t st);
 // root_keys (nullable): the new requests' complete-root keys, copied to
 // slot_root[slot].
 void launch_serve_admit(const float* staged_q, const int32_t* meta, int n_new, int d,

@@ -5,8 +5,9 @@
 // upper layers and max(ef, k) on layer 0, handing the best node down the
 // inter-layer edge (Def. HENN: the same point one layer below).
 //
-// The beam keeps one ascending list W of (distance, id, expanded) keys in
-// LDS and repeatedly expands the smallest unexpanded entry; this is the
+// The beam keeps one ascending list W of (distance, id, expanded) keys, in
+// registers up to a width of 256 and in LDS beyond, and repeatedly expands
+// the smallest unexpanded entry; this is the
 // two-heap SEARCH-LAYER of HNSW (the candidate set the paper relies on for
 // k > 1) in an equivalent form: the expansion sequence and the final list
 // are identical under the strict (distance, id) order.  Visited nodes are
@@ -21,10 +22,11 @@
 // Precision forms traverse BF16 / FP8 rows and re-rank the first
 // min(|W|, rerank_factor*k) entries from the FP32 copy at the end.
 //
-// The library compiles this file four times: HENN_PART 0 holds the host
-// functions and root-scan kernels, parts 1 / 2 / 3 the search and serving
-// kernels of FP32 / BF16 / FP8 rows, so that the instantiations build in
-// parallel.  Without HENN_PART one translation unit holds everything.
+// The library compiles this file ten times: HENN_PART 0 holds the host
+// functions and root-scan kernels, parts 1 .. 9 the search and serving
+// kernels of FP32 / BF16 / FP8 rows with the list in LDS or in two or four
+// registers a lane, so that the instantiations build in parallel.  Without
+// HENN_PART one translation unit holds everything.
 #include <math.h>
 
 #include "henn_device.h"
@@ -34,66 +36,176 @@
 #define HENN_PART -1
 #endif
 #define HENN_COMMON_PART (HENN_PART <= 0)
-#define HENN_KIND_PART(kind) (HENN_PART < 0 || HENN_PART == (kind) + 1)
 
 namespace henn {
 
 #if HENN_COMMON_PART
-size_t search_lds_per_wave(int ef_cap, int vis_bits, int vis_bytes) {
-  return (size_t)ef_cap * 8 + 64 * 8 * 2 + 64 * 4 * 2 + ((size_t)1 << vis_bits) * vis_bytes;
+size_t search_lds_per_wave(int ef_cap, int vis_bits, int vis_bytes, bool exact) {
+  const size_t vis = ((size_t)1 << vis_bits) * vis_bytes, list = (size_t)ef_cap * 8;
+  if (exact || list_blocks(ef_cap) == 0) return list + 64 * 8 * 2 + 64 * 4 * 2 + vis;
+  // the list is in registers; its final copy takes the table's place
+  return 64 * 8 + 64 * 4 * 3 + (vis > list ? vis : list);
 }
 #endif
 
-// One list W, merged in place.  A merge ranks the kept keys in kstage, then
-// reuses it as the map of the list positions that take a kept key.
 // The fresh neighbours of an expansion, by compacted slot: crow (the row's
-// first chunk index, row * chunks per row) and cidk (id << 1, the low word of
-// its key).
+// first chunk index, row * chunks per row), cidk (id << 1, the low word of
+// its key) and csc (FP8: its scale); then their keys in ckey.
+//
+// NB = 0: the list W is in LDS and merged in place; a merge ranks the kept
+// keys in kstage (which holds the scales until then) and reuses it as the map
+// of the list positions that take a kept key.
+// NB > 0: the list is in registers (RegList); W is where its final copy goes,
+// over the visited table, which is dead by then.
 struct WaveLds {
   uint64_t* W;
-  uint64_t* ckey;     // candidate keys (by compacted slot)
-  uint64_t* kstage;   // kept keys in arrival order; FP8 scales during the
-                      // gather and the merge's slot map after the ranks
+  uint64_t* ckey;    // candidate keys (by compacted slot)
+  uint64_t* kstage;  // NB = 0 only
+  float* csc;
   uint32_t* crow;
   uint32_t* cidk;
   void* vis;  // 2^vis_bits entries: uint8 or uint16 tags, or int32 ids
+  int lane;   // this lane's number, opaque to the compiler (see fresh_lane)
 };
 
-__device__ inline WaveLds carve(char* base, int ef_cap, int vis_bits, int vis_bytes) {
+// The lane number as a value the compiler cannot see through.  Taken once per
+// query: what is derived from it (offsets, masks) is then computed where it
+// is used and not kept in registers across the queries of a persistent wave.
+__device__ inline int fresh_lane() {
+  int l = lane_id();
+  asm volatile("" : "+v"(l));
+  return l;
+}
+
+template <int NB>
+__device__ inline WaveLds carve(char* base, int ef_cap) {
   WaveLds s;
-  s.W = reinterpret_cast<uint64_t*>(base);
-  s.ckey = s.W + ef_cap;
-  s.kstage = s.ckey + 64;
-  s.crow = reinterpret_cast<uint32_t*>(s.kstage + 64);
-  s.cidk = s.crow + 64;
-  s.vis = s.cidk + 64;
+  s.lane = lane_id();
+  if constexpr (NB == 0) {
+    s.W = reinterpret_cast<uint64_t*>(base);
+    s.ckey = s.W + ef_cap;
+    s.kstage = s.ckey + 64;
+    s.csc = reinterpret_cast<float*>(s.kstage);
+    s.crow = reinterpret_cast<uint32_t*>(s.kstage + 64);
+    s.cidk = s.crow + 64;
+    s.vis = s.cidk + 64;
+  } else {
+    s.ckey = reinterpret_cast<uint64_t*>(base);
+    s.kstage = nullptr;
+    s.csc = reinterpret_cast<float*>(s.ckey + 64);
+    s.crow = reinterpret_cast<uint32_t*>(s.csc + 64);
+    s.cidk = s.crow + 64;
+    s.vis = s.cidk + 64;
+    s.W = static_cast<uint64_t*>(s.vis);
+  }
   return s;
 }
 
-// Visited table slot and stored value of id u (see vis_tag_bytes).
-__device__ inline void vis_slot(int32_t u, int bits, int vis_bytes, uint32_t& h, uint32_t& tag) {
-  if (vis_bytes < 4) {
-    h = (uint32_t)u & ((1u << bits) - 1u);
-    tag = ((uint32_t)u >> bits) + 1u;
-  } else {
-    h = ((uint32_t)u * 2654435761u) >> (32 - bits);
-    tag = (uint32_t)u;
-  }
-}
-__device__ inline uint32_t vis_get(const void* vis, int vis_bytes, uint32_t h) {
-  if (vis_bytes == 1) return static_cast<const uint8_t*>(vis)[h];
-  if (vis_bytes == 2) return static_cast<const uint16_t*>(vis)[h];
-  return static_cast<const uint32_t*>(vis)[h];
-}
-__device__ inline void vis_put(void* vis, int vis_bytes, uint32_t h, uint32_t tag) {
-  if (vis_bytes == 1)
-    static_cast<uint8_t*>(vis)[h] = (uint8_t)tag;
-  else if (vis_bytes == 2)
-    static_cast<uint16_t*>(vis)[h] = (uint16_t)tag;
-  else
-    static_cast<uint32_t*>(vis)[h] = tag;
+// The beam's list in registers: 64 NB positions, position 64 b + l in lane l
+// of w[b], ascending (distance, id) keys without the expanded flag; ex[b]
+// holds one bit per position (uniform), set where there is nothing to expand.
+// A list of width efl <= 64 NB occupies the last efl positions: the ones
+// below hold a key under every real one, the ones not filled yet a key above
+// every real one.  So the last position is the threshold a new key has to
+// beat, whether the list is full or not, and an evicted entry falls off the
+// end.
+template <int NB>
+struct RegList {
+  uint64_t w[NB];
+  uint64_t ex[NB];
+};
+
+__device__ inline uint64_t readlane_u64(uint64_t v, int l) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
+  return ((uint64_t)hi << 32) | lo;
 }
 
+// Value of the next lower lane (DPP wave_shr:1); lane 0 gets first.
+__device__ inline uint64_t lane_above(uint64_t v, uint64_t first) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(
+      (int)(uint32_t)first, (int)(uint32_t)v, 0x138, 0xF, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(
+      (int)(uint32_t)(first >> 32), (int)(uint32_t)(v >> 32), 0x138, 0xF, 0xF, false);
+  return ((uint64_t)hi << 32) | lo;
+}
+// The same where lane 0's value does not matter.
+__device__ inline uint64_t lane_above_any(uint64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)v, 0x138, 0xF, 0xF, true);
+  const uint32_t hi =
+      (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(v >> 32), 0x138, 0xF, 0xF, true);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// An empty list of width efl holding the one unexpanded entry `key`.
+template <int NB>
+__device__ inline void list_start(RegList<NB>& L, int lane, int efl, uint64_t key) {
+  const int off = 64 * NB - efl;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int pos = 64 * b + lane;
+    L.w[b] = pos < off ? 1ull : pos == off ? key : ~0ull;
+    L.ex[b] = ~ballot(pos == off);
+  }
+}
+
+// Inserts the uniform key k below the list's threshold; false when it is
+// there already (a row the visited table forgot).  One compare gives every
+// position's side of k; the positions above move up by one lane.
+template <int NB>
+__device__ inline bool list_insert(RegList<NB>& L, int off, uint64_t k) {
+  bool lt[NB];
+  uint64_t m[NB], dup = 0;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    lt[b] = L.w[b] < k;
+    m[b] = ballot(lt[b]);
+    dup |= ballot((uint32_t)L.w[b] == (uint32_t)k);  // ids are unique; the fillers' are odd
+  }
+  if (dup) return false;
+#pragma unroll
+  for (int b = NB - 1; b >= 0; --b) {
+    if (m[b] == ~0ull) continue;
+    const uint64_t e = L.ex[b];
+    if (b == 0 || m[b > 0 ? b - 1 : 0] == ~0ull) {
+      // k lands in this block, at its first position not below it
+      const uint64_t at = ~m[b] & (m[b] + 1);
+      const uint64_t up = lane_above_any(L.w[b]);
+      const uint64_t v = __builtin_amdgcn_inverse_ballot_w64(at) ? k : up;
+      L.w[b] = lt[b] ? L.w[b] : v;
+      L.ex[b] = (e & m[b]) | ((e & ~m[b]) << 1);
+    } else {
+      const int pb = b > 0 ? b - 1 : 0;
+      L.w[b] = lane_above(L.w[b], readlane_u64(L.w[pb], 63));
+      L.ex[b] = (e << 1) | (L.ex[pb] >> 63);
+    }
+  }
+  return true;
+}
+
+// The list's entries, flagged as in the LDS form, to / from n entries of
+// memory (LDS or HBM).
+template <int NB>
+__device__ inline void list_store(const RegList<NB>& L, int lane, int efl, int n, uint64_t* out, bool flags) {
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int i = 64 * b + lane - (64 * NB - efl);
+    const uint64_t f = (flags && __builtin_amdgcn_inverse_ballot_w64(L.ex[b])) ? 1ull : 0ull;
+    if (i >= 0 && i < n) out[i] = L.w[b] | f;
+  }
+}
+template <int NB>
+__device__ inline void list_load(RegList<NB>& L, int lane, int efl, int n, const uint64_t* in) {
+  const int off = 64 * NB - efl;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int i = 64 * b + lane - off;
+    uint64_t v = i < 0 ? 1ull : ~0ull;
+    if (i >= 0 && i < n) v = in[i];
+    L.ex[b] = ballot((v & 1ull) != 0);
+    L.w[b] = (i >= 0 && i < n) ? wkey_strip(v) : v;
+  }
+}
 
 // Largest power of two <= v (0 for v <= 0).
 __device__ inline int pow2_floor(int v) { return v <= 0 ? 0 : 1 << (31 - __clz(v)); }
@@ -252,9 +364,9 @@ bool launch_root_scan(int storage, const SearchArgs& a, int splits, int64_t rows
 // position) key.
 template <int KIND, int LPN, int CPL>
 __device__ uint64_t root_scan_wave(const SearchArgs& a, const SearchLayer& R,
-                                   const float (&q)[CPL][8]) {
+                                   const float (&q)[CPL][8], int lane) {
   constexpr int G = 64 / LPN;
-  const int lane = lane_id(), t = lane % LPN, g = lane / LPN;
+  const int t = lane % LPN, g = lane / LPN;
   uint64_t best = ~0ull;
   for (int base = 0; base < R.size; base += 2 * G) {
     const int c0 = base + g, c1 = base + G + g;
@@ -329,7 +441,7 @@ __global__ __launch_bounds__(256) void k_root_check(SearchArgs a, RootShortlist 
   for (int hq = 0; hq < 2; ++hq) {
     if (ovm & (1ull << (32 * hq))) {
       load_query<CPL>(a.Q + (qi - half + hq) * a.d, a.d, t, q);
-      const uint64_t k = root_scan_wave<KIND, LPN, CPL>(a, R, q);
+      const uint64_t k = root_scan_wave<KIND, LPN, CPL>(a, R, q, lane);
       if (half == hq) best_over = k;
     }
   }
@@ -382,11 +494,14 @@ __global__ __launch_bounds__(256) void k_root_check(SearchArgs a, RootShortlist 
 // when given).
 template <int KIND, int LPN, int CPL>
 __device__ void start_query(const SearchArgs& a, int64_t qi, const float (&q)[CPL][8],
-                            QState& st) {
+                            int lane, QState& st) {
   constexpr int G = 64 / LPN;
-  const int lane = lane_id(), t = lane % LPN, g = lane / LPN;
-  int k = uni(a.k_arr ? a.k_arr[qi] : a.k_all);
-  const int ef = uni(a.ef_arr ? a.ef_arr[qi] : a.ef_all);
+  const int t = lane % LPN, g = lane / LPN;
+  // (written as two reads: a select between the addresses would make it a
+  // vector load from the argument segment)
+  int k = uni(a.k_all), ef = uni(a.ef_all);
+  if (a.k_arr) k = uni(a.k_arr[qi]);
+  if (a.ef_arr) ef = uni(a.ef_arr[qi]);
   k = min(max(k, 1), a.k_max);
   st.k = k;
   st.ef0 = min(max(ef, k), a.ef_cap);
@@ -410,7 +525,7 @@ __device__ void start_query(const SearchArgs& a, int64_t qi, const float (&q)[CP
   } else if (a.root_complete && top >= 1) {
     // complete graph on the root: exhaustive scan for its nearest member
     const SearchLayer& R = a.layer[top];
-    const uint64_t best = uni_u64(root_scan_wave<KIND, LPN, CPL>(a, R, q));
+    const uint64_t best = uni_u64(root_scan_wave<KIND, LPN, CPL>(a, R, q, lane));
     st.evals = R.size;
     st.cur = uni(R.down[wkey_id(best)]);
     st.cur_d = wkey_dist(best);
@@ -485,97 +600,45 @@ __device__ inline float fp8_chunk_ip(const uint2 w, const h2_t (&qh)[4]) {
 
 // One chunk's partial distance in the traversal: the canonical FP32 sum
 // (henn_device.h) for FP32 and BF16 rows, the f16 form above for FP8 rows.
-template <int KIND>
+template <int KIND, bool L2>
 __device__ inline float traversal_chunk(const ChunkRaw<KIND>& raw, const float (&q)[8],
-                                        const h2_t (&qh)[4], float sc, h2_t nm, int metric) {
+                                        const h2_t (&qh)[4], float sc, h2_t nm) {
   if constexpr (KIND == kFP8) {
-    return metric == 0 ? fp8_chunk_l2(raw.a, qh, sc, nm) : fp8_chunk_ip(raw.a, qh);
+    return L2 ? fp8_chunk_l2(raw.a, qh, sc, nm) : fp8_chunk_ip(raw.a, qh);
   } else {
     float x[8];
     raw.decode(x);
-    return metric == 0 ? chunk_l2(q, x, 1.0f, false) : chunk_ip(q, x);
+    return L2 ? chunk_l2(q, x, 1.0f, false) : chunk_ip(q, x);
   }
 }
 
-// One gather pass: rows [base, base + NR * G) of this expansion's fresh
-// candidates (crow / cidk / csc), their distances, and their keys into ckey.
-// FULL: the row has exactly LPN * CPL chunks, so lane t's chunks
-// t * CPL .. t * CPL + CPL - 1 are contiguous and read at constant offsets
-// from one pointer; otherwise chunk indices past the row are clamped to
-// chunk 0 and their sums dropped (group_distances).  Every lane of the
-// wave takes part (butterflies); a slot at or past cnt computes the pass's
-// first row again and writes nothing.  Distances are the canonical sums of
-// henn_device.h.
-template <int KIND, int LPN, int CPL, int NR, bool FULL>
-__device__ inline void gather_pass(const SearchArgs& a, const SearchLayer& L,
-                                   const float (&q)[CPL][8], const h2_t (&qh)[CPL][4],
-                                   const WaveLds& s, const float* csc, int base, int cnt, int t,
-                                   int g) {
-  constexpr int G = 64 / LPN;
-  constexpr int CB = KIND == kF32 ? 32 : KIND == kBF16 ? 16 : 8;  // bytes per chunk
-  const char* vec = static_cast<const char*>(L.vec);
-  const void* rows[NR];
-  float sc[NR];
-  bool vd[NR];
-  uint32_t idk[NR];
+// This lane's chunk sums of NR fetched rows (tree over its CPL chunks; chunks
+// past the row are dropped unless FULL), and their lane-group sums: rows 2p
+// and 2p + 1 share one butterfly (group_distances_paired), after which the
+// even lanes of a group hold row 2p's sum and the odd lanes row 2p + 1's, in
+// d[2p]; an odd last row's sum is in d[NR - 1].
+template <int KIND, int LPN, int CPL, int NR, bool FULL, bool L2>
+__device__ inline void gather_sums(const ChunkRaw<KIND> (&raw)[NR][CPL], const float (&q)[CPL][8],
+                                   const h2_t (&qh)[CPL][4], const float (&sc)[NR], int t,
+                                   int nchunks, float (&d)[NR]) {
+  float ts[NR];
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    const int ci = base + r * G + g;
-    vd[r] = ci < cnt;
-    // an empty slot re-reads the pass's first row, which its group reads anyway
-    const int e = vd[r] ? ci : base;
-    const uint32_t ch = s.crow[e] + (FULL ? (uint32_t)(t * CPL) : 0u);
-    rows[r] = vec + (size_t)ch * CB;
-    idk[r] = s.cidk[e];
-    sc[r] = (KIND == kFP8) ? csc[e] : 1.0f;
-  }
-  // FP8: minus the mantissa of each row's scale (fp8_chunk_l2)
-  h2_t nm[NR];
+    // FP8: minus the mantissa of the row's scale (fp8_chunk_l2)
+    const h2_t nm = (KIND == kFP8 && L2) ? -scale_mantissa(sc[r]) : h2_t{0, 0};
+    float part[CPL];
 #pragma unroll
-  for (int r = 0; r < NR; ++r) nm[r] = (KIND == kFP8) ? -scale_mantissa(sc[r]) : h2_t{0, 0};
-  // this lane's chunk sums of each row (tree over its CPL chunks)
-  float ts[NR];
-  if constexpr (FULL) {
-    ChunkRaw<KIND> raw[NR][CPL];
-#pragma unroll
-    for (int r = 0; r < NR; ++r)
-#pragma unroll
-      for (int i = 0; i < CPL; ++i) raw[r][i].fetch(rows[r], i);
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      float part[CPL];
-#pragma unroll
-      for (int i = 0; i < CPL; ++i)
-        part[i] = traversal_chunk<KIND>(raw[r][i], q[i], qh[i], sc[r], nm[r], a.metric);
-      ts[r] = tree_sum<CPL>(part);
+    for (int i = 0; i < CPL; ++i) {
+      const float v = traversal_chunk<KIND, L2>(raw[r][i], q[i], qh[i], sc[r], nm);
+      part[i] = (FULL || t * CPL + i < nchunks) ? v : 0.0f;
     }
-  } else {
-    ChunkRaw<KIND> raw[NR][CPL];
-#pragma unroll
-    for (int r = 0; r < NR; ++r)
-#pragma unroll
-      for (int i = 0; i < CPL; ++i) {
-        const int c = t * CPL + i;
-        raw[r][i].fetch(rows[r], c < a.nchunks ? c : 0);
-      }
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      float part[CPL];
-#pragma unroll
-      for (int i = 0; i < CPL; ++i) {
-        const int c = t * CPL + i;
-        const float v = traversal_chunk<KIND>(raw[r][i], q[i], qh[i], sc[r], nm[r], a.metric);
-        part[i] = c < a.nchunks ? v : 0.0f;
-      }
-      ts[r] = tree_sum<CPL>(part);
-    }
+    ts[r] = tree_sum<CPL>(part);
+    // wide rows: one row's arithmetic at a time, or the rows' decoded values
+    // overflow the registers
+    if constexpr (CPL * NR >= 16) __builtin_amdgcn_sched_barrier(0);
   }
-  // lane-group sums; rows 2p and 2p + 1 share one butterfly
-  // (group_distances_paired): the even lanes of a group end with row 2p's
-  // sum, the odd lanes with row 2p + 1's
   constexpr int NP = (LPN >= 2) ? NR / 2 : 0;  // row pairs
   const bool odd = (lane_id() & 1) != 0;
-  float d[NR];
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     float v = (odd ? ts[2 * p + 1] : ts[2 * p]) + dpp_mov<0xB1>(odd ? ts[2 * p] : ts[2 * p + 1]);
@@ -583,50 +646,257 @@ __device__ inline void gather_pass(const SearchArgs& a, const SearchLayer& L,
   }
 #pragma unroll
   for (int r = 2 * NP; r < NR; ++r) d[r] = group_sum<LPN>(ts[r]);
+}
+
+// What every expansion needs of the arguments, read once per query: a read
+// inside the loop would be a scalar-memory round trip in the chain.
+struct StepArgs {
+  int vis_bits, vis_bytes, nchunks, metric;
+  __device__ explicit StepArgs(const SearchArgs& a)
+      : vis_bits(uni(a.vis_bits)), vis_bytes(uni(a.vis_bytes)), nchunks(uni(a.nchunks)),
+        metric(uni(a.metric)) {}
+};
+
+// Visited table: byte offset of id u's entry and the value stored there (see
+// vis_tag_bytes; 4-byte entries hold the id itself, at a hashed slot).
+__device__ inline void vis_slot(const StepArgs& a, int32_t u, uint32_t& at, uint32_t& tag) {
+  uint32_t h = (uint32_t)u & ((1u << a.vis_bits) - 1u);
+  tag = ((uint32_t)u >> a.vis_bits) + 1u;
+  if (a.vis_bytes == 4) {
+    h = ((uint32_t)u * 2654435761u) >> (32 - a.vis_bits);
+    tag = (uint32_t)u;
+  }
+  at = h << (a.vis_bytes >> 1);
+}
+
+// Stores the tag where mark is set.  The width is decided outside of the
+// predicated stores, so that those are single instructions.
+__device__ inline void vis_mark(const StepArgs& a, const WaveLds& s, uint32_t at, uint32_t tag,
+                                bool mark) {
+  char* e = static_cast<char*>(s.vis) + at;
+  if (a.vis_bytes == 1) {
+    if (mark) *reinterpret_cast<uint8_t*>(e) = (uint8_t)tag;
+  } else {
+    if (mark) *reinterpret_cast<uint16_t*>(e) = (uint16_t)tag;
+    if (a.vis_bytes == 4 && mark) *reinterpret_cast<uint16_t*>(e + 2) = (uint16_t)(tag >> 16);
+  }
+}
+
+// One gather pass: rows [base, base + NR * G) of this expansion's fresh
+// candidates (crow / cidk / csc of s), their distances, and their keys into ckey.
+// FULL: the row has exactly LPN * CPL chunks, so lane t's chunks
+// t * CPL .. t * CPL + CPL - 1 are contiguous and read at constant offsets
+// from one pointer; otherwise chunk indices past the row are clamped to
+// chunk 0 and their sums dropped (group_distances).  Every lane of the
+// wave takes part (butterflies); a slot at or past cnt computes the pass's
+// first row again and writes nothing.  Distances are the canonical sums of
+// henn_device.h.
+// after_issue() runs once every load of the pass is issued and before the
+// first is waited for: loads return in order, so what it issues does not
+// delay them, and is itself back by the time they have been used.
+template <int KIND, int LPN, int CPL, int NR, bool FULL, bool L2, typename F>
+__device__ inline void gather_pass(const StepArgs& a, const SearchLayer& L,
+                                   const float (&q)[CPL][8], const h2_t (&qh)[CPL][4],
+                                   const WaveLds& s, int base, int cnt, int t, int g,
+                                   F&& after_issue) {
+  constexpr int G = 64 / LPN;
+  constexpr int CB = KIND == kF32 ? 32 : KIND == kBF16 ? 16 : 8;  // bytes per chunk
+  const char* vec = static_cast<const char*>(L.vec);
+  const void* rows[NR];
+  float sc[NR];
+  uint32_t idk[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int ci = base + r * G + g;
+    // an empty slot re-reads the pass's first row, which its group reads anyway
+    const int e = ci < cnt ? ci : base;
+    const uint32_t ch = s.crow[e] + (FULL ? (uint32_t)(t * CPL) : 0u);
+    rows[r] = vec + (size_t)ch * CB;
+    idk[r] = s.cidk[e];
+    sc[r] = (KIND == kFP8) ? s.csc[e] : 1.0f;
+  }
+  ChunkRaw<KIND> raw[NR][CPL];
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int i = 0; i < CPL; ++i) {
+      const int c = t * CPL + i;
+      raw[r][i].fetch(rows[r], FULL ? i : c < a.nchunks ? c : 0);
+    }
+  after_issue();
   // keys: (ordered distance bits << 32) | (id << 1).  Squared L2 distances
   // are sums of squares, never negative or -0, so their ordered bits are
-  // the float bits with the sign bit set (ordered_bits on that range).
-  auto key_of = [&](float dist, float scale, uint32_t idk_) -> uint64_t {
-    uint32_t ob;
-    if (a.metric == 0) {
-      ob = __float_as_uint(dist) | 0x80000000u;
-    } else {
-      ob = ordered_bits((KIND == kFP8) ? -(scale * dist) : -dist);
-    }
-    return ((uint64_t)ob << 32) | idk_;
-  };
+  // the float bits with the sign bit set (ordered_bits on that range).  For
+  // inner products 0 (a NaN of all ones) would fall below the register list's
+  // fillers, and becomes 1.
+  constexpr int NP = (LPN >= 2) ? NR / 2 : 0;  // row pairs (gather_sums)
+  const bool odd = (lane_id() & 1) != 0;
+  float d[NR];
+  uint32_t ob[NR];
+  gather_sums<KIND, LPN, CPL, NR, FULL, L2>(raw, q, qh, sc, t, a.nchunks, d);
 #pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    const int r = 2 * p + (odd ? 1 : 0);
-    if (t < 2 && vd[r]) s.ckey[base + r * G + g] = key_of(d[2 * p], sc[r], idk[r]);
+  for (int r = 0; r < NR; ++r) {
+    if constexpr (L2) {
+      ob[r] = __float_as_uint(d[r]) | 0x80000000u;
+    } else {
+      constexpr int last = NR - 1;
+      const float s0 = sc[r], s1 = sc[r < last ? r + 1 : last];
+      const float scale = (r < 2 * NP && (r & 1) == 0 && odd) ? s1 : s0;
+      ob[r] = max(ordered_bits((KIND == kFP8) ? -(scale * d[r]) : -d[r]), 1u);
+    }
   }
 #pragma unroll
-  for (int r = 2 * NP; r < NR; ++r)
-    if (t == 0 && vd[r]) s.ckey[base + r * G + g] = key_of(d[r], sc[r], idk[r]);
+  for (int p = 0; p < NP; ++p) {
+    const int r = 2 * p;
+    const int ci = base + (r + (odd ? 1 : 0)) * G + g;
+    // (a select between array elements would put the array into memory)
+    const uint32_t id = idk[r] ^ ((idk[r] ^ idk[r + 1]) & (odd ? 0xffffffffu : 0u));
+    if (t < 2 && ci < cnt) s.ckey[ci] = ((uint64_t)ob[r] << 32) | id;
+  }
+#pragma unroll
+  for (int r = 2 * NP; r < NR; ++r) {
+    const int ci = base + r * G + g;
+    if (t == 0 && ci < cnt) s.ckey[ci] = ((uint64_t)ob[r] << 32) | idk[r];
+  }
 }
 
 // All gather passes of one expansion, each with every load of its rows in
 // flight together: up to kGatherRows * G rows per pass, the last pass sized
-// to the rows left.
-template <int KIND, int LPN, int CPL, bool FULL>
-__device__ inline void gather_all(const SearchArgs& a, const SearchLayer& L,
-                                  const float (&q)[CPL][8], const h2_t (&qh)[CPL][4],
-                                  const WaveLds& s, const float* csc, int cnt, int t, int g) {
+// to the rows left.  after_issue: in the first pass (see gather_pass), also
+// when there is no row.
+template <int KIND, int LPN, int CPL, bool FULL, bool L2, typename F>
+__device__ inline void gather_metric(const StepArgs& a, const SearchLayer& L,
+                                     const float (&q)[CPL][8], const h2_t (&qh)[CPL][4],
+                                     const WaveLds& s, int cnt, int t, int g, F&& after_issue) {
   constexpr int G = 64 / LPN;
   static_assert(kGatherRows == 3, "pass sizes below");
-  for (int base = 0; base < cnt;) {
+  // three FP32 rows of eight chunks a lane do not fit the registers
+  constexpr bool kThree = !(KIND == kF32 && CPL >= 8);
+  auto pass = [&](int base, auto&& f) -> int {
     const int rest = cnt - base;
-    if (rest > 2 * G) {
-      gather_pass<KIND, LPN, CPL, 3, FULL>(a, L, q, qh, s, csc, base, cnt, t, g);
-      base += 3 * G;
-    } else if (rest > G) {
-      gather_pass<KIND, LPN, CPL, 2, FULL>(a, L, q, qh, s, csc, base, cnt, t, g);
-      base += 2 * G;
-    } else {
-      gather_pass<KIND, LPN, CPL, 1, FULL>(a, L, q, qh, s, csc, base, cnt, t, g);
-      base += G;
+    if constexpr (kThree) {
+      if (rest > 2 * G) {
+        gather_pass<KIND, LPN, CPL, 3, FULL, L2>(a, L, q, qh, s, base, cnt, t, g, f);
+        return 3 * G;
+      }
     }
+    if (rest > G) {
+      gather_pass<KIND, LPN, CPL, 2, FULL, L2>(a, L, q, qh, s, base, cnt, t, g, f);
+      return 2 * G;
+    }
+    gather_pass<KIND, LPN, CPL, 1, FULL, L2>(a, L, q, qh, s, base, cnt, t, g, f);
+    return G;
+  };
+  if (cnt == 0) {
+    after_issue();
+    return;
   }
+  for (int base = pass(0, after_issue); base < cnt;) base += pass(base, [] {});
+}
+
+template <int KIND, int LPN, int CPL, bool FULL, typename F>
+__device__ inline void gather_all(const StepArgs& a, const SearchLayer& L,
+                                  const float (&q)[CPL][8], const h2_t (&qh)[CPL][4],
+                                  const WaveLds& s, int cnt, int t, int g, F&& after_issue) {
+  // the metric outside of the passes: inside, the two forms' common decoding
+  // is done ahead of the branch and held
+  if (a.metric == 0)
+    gather_metric<KIND, LPN, CPL, FULL, true>(a, L, q, qh, s, cnt, t, g, after_issue);
+  else
+    gather_metric<KIND, LPN, CPL, FULL, false>(a, L, q, qh, s, cnt, t, g, after_issue);
+}
+
+// Starts a layer: the visited set emptied and the entry st.cur marked in it;
+// for FP8 rows the entry's distance in the traversal's own form: the one
+// handed down (a root scan, or the first distance of the root) is the
+// canonical FP32 sum, and the list's duplicate check compares keys.
+template <int KIND, int LPN, int CPL, bool FULL, bool EXACT>
+__device__ inline void layer_begin(const StepArgs& a, const SearchLayer& L,
+                                   const float (&q)[CPL][8], const h2_t (&qh)[CPL][4],
+                                   const WaveLds& s, QState& st, int t, int g, uint32_t* vis_bm) {
+  const int lane = s.lane;
+  if (st.li == 0) {
+    st.exps0 = st.exps;
+    st.evals0 = st.evals;
+  }
+  st.evals += 1;  // the entry (its distance is carried down, counted per layer)
+  if constexpr (EXACT) {
+    // the exact set: one bit per member of the layer, in the workspace
+    const int64_t words = ((int64_t)L.size + 31) >> 5;
+    for (int64_t i = lane; i < words; i += 64) vis_bm[i] = 0u;
+    __builtin_amdgcn_s_waitcnt(0);  // cleared before the first bit is set
+  } else {
+    // empty: tag 0 (8 / 16-bit) or id -1 (32-bit); at least 256 bytes, so
+    // whole 16-byte words
+    const int n16 = (a.vis_bytes << a.vis_bits) >> 4;
+    const uint32_t e = a.vis_bytes < 4 ? 0u : 0xffffffffu;
+    for (int i = lane; i < n16; i += 64) static_cast<uint4*>(s.vis)[i] = make_uint4(e, e, e, e);
+  }
+  if constexpr (KIND == kFP8) {
+    if (lane == 0) {
+      s.crow[0] = (uint32_t)st.cur * (uint32_t)a.nchunks;
+      s.cidk[0] = (uint32_t)st.cur << 1;
+      s.csc[0] = L.scale[st.cur];
+    }
+    wave_sync();
+    gather_all<KIND, LPN, CPL, FULL>(a, L, q, qh, s, 1, t, g, [] {});
+    wave_sync();
+    st.cur_d = wkey_dist(uni_u64(s.ckey[0]));
+  }
+  wave_sync();
+  if constexpr (EXACT) {
+    if (lane == 0) atomicOr(vis_bm + (st.cur >> 5), 1u << (st.cur & 31));
+  } else {
+    uint32_t at, tag;
+    vis_slot(a, st.cur, at, tag);
+    vis_mark(a, s, at, tag, lane == 0);
+  }
+  st.wsize = 1;
+  st.need_init = 0;
+}
+
+// The lanes whose neighbour u (-1: none) the visited table does not hold; it
+// holds them afterwards.  Every lane reads the word that holds its entry (-1
+// has a slot too), whatever an entry's width, so that the read needs no
+// branches.
+__device__ inline uint64_t vis_filter(const StepArgs& a, const WaveLds& s, int32_t u) {
+  uint32_t at, tag;
+  vis_slot(a, u, at, tag);
+  const uint32_t word = *reinterpret_cast<const uint32_t*>(static_cast<char*>(s.vis) + (at & ~3u));
+  const uint32_t old = (word >> ((at & 3u) * 8)) & (0xffffffffu >> (32 - 8 * a.vis_bytes));
+  const bool fresh = (u >= 0) & (old != tag);
+  const uint64_t fm = ballot(fresh);
+  wave_sync();
+  vis_mark(a, s, at, tag, fresh);
+  return fm;
+}
+
+// The fresh ones of this expansion's neighbours (u, -1: none; usc: its FP8
+// scale) take the compacted slots 0, 1, ...; returns how many.
+template <int KIND, bool EXACT>
+__device__ inline int take_fresh(const StepArgs& a, const WaveLds& s, int32_t u, float usc,
+                                 uint32_t* vis_bm) {
+  uint64_t fm;
+  if constexpr (EXACT) {
+    // exact set: the bit's old value says whether u was seen (the
+    // update is atomic, so of lanes holding one id only one finds it new)
+    bool fresh = false;
+    if (u >= 0) {
+      const uint32_t bit = 1u << (u & 31);
+      fresh = !(atomicOr(vis_bm + (u >> 5), bit) & bit);
+    }
+    fm = ballot(fresh);
+  } else {
+    fm = vis_filter(a, s, u);
+  }
+  const int rb = rank_below(fm);
+  if (__builtin_amdgcn_inverse_ballot_w64(fm)) {
+    s.crow[rb] = (uint32_t)u * (uint32_t)a.nchunks;
+    s.cidk[rb] = (uint32_t)u << 1;
+    if (KIND == kFP8) s.csc[rb] = usc;
+  }
+  wave_sync();
+  return popc64(fm);
 }
 
 // Runs up to `budget` expansions from the current state (layer changes are
@@ -634,60 +904,19 @@ __device__ inline void gather_all(const SearchArgs& a, const SearchLayer& L,
 // W (this wave's LDS list) holds the final list (st.wsize entries).  q: this
 // lane's FP32 query slice; qh: the same in f16 pairs (read by the FP8 form
 // only, which then never reads q).
+// This form keeps the list in LDS: beams wider than the register form's 256,
+// and the exact visited set (an analysis form).
 template <int KIND, int LPN, int CPL, bool FULL, bool EXACT = false>
 __device__ bool advance(const SearchArgs& a, const float (&q)[CPL][8], const h2_t (&qh)[CPL][4],
                         WaveLds s, uint64_t* W, QState& st, int budget, uint32_t* vis_bm) {
-  constexpr int G = 64 / LPN;
-  const int lane = lane_id(), t = lane % LPN, g = lane / LPN;
-  const int vis_n = 1 << a.vis_bits;
+  const int lane = s.lane, t = lane % LPN, g = lane / LPN;
+  const StepArgs h(a);
   for (;;) {
     const SearchLayer L = a.layer[st.li];
     const int efl = st.li == 0 ? st.ef0 : min(a.ef_upper, a.ef_cap);
     if (st.need_init) {
-      if (st.li == 0) {
-        st.exps0 = st.exps;
-        st.evals0 = st.evals;
-      }
-      st.evals += 1;  // the entry (its distance is carried down, counted per layer)
-      if constexpr (EXACT) {
-        // the exact set: one bit per member of the layer, in the workspace
-        const int64_t words = ((int64_t)L.size + 31) >> 5;
-        for (int64_t i = lane; i < words; i += 64) vis_bm[i] = 0u;
-        __builtin_amdgcn_s_waitcnt(0);  // cleared before the first bit is set
-      } else {
-        // empty: tag 0 (8 / 16-bit) or id -1 (32-bit); cleared as 32-bit words
-        const int vis_words = vis_n * a.vis_bytes / 4;
-        const uint32_t empty = a.vis_bytes < 4 ? 0u : 0xffffffffu;
-        for (int i = lane; i < vis_words; i += 64) static_cast<uint32_t*>(s.vis)[i] = empty;
-      }
-      if constexpr (KIND == kFP8) {
-        // the entry's distance in the traversal's own form: the one handed
-        // down (a root scan, or the first distance of the root) is the
-        // canonical FP32 sum, and the list's duplicate check compares keys
-        if (lane == 0) {
-          s.crow[0] = (uint32_t)st.cur * (uint32_t)a.nchunks;
-          s.cidk[0] = (uint32_t)st.cur << 1;
-          reinterpret_cast<float*>(s.kstage)[0] = L.scale[st.cur];
-        }
-        wave_sync();
-        gather_pass<KIND, LPN, CPL, 1, FULL>(a, L, q, qh, s, reinterpret_cast<float*>(s.kstage),
-                                             0, 1, t, g);
-        wave_sync();
-        st.cur_d = wkey_dist(uni_u64(s.ckey[0]));
-      }
-      wave_sync();
-      if (lane == 0) {
-        W[0] = wkey(st.cur_d, st.cur);
-        if constexpr (EXACT) {
-          atomicOr(vis_bm + (st.cur >> 5), 1u << (st.cur & 31));
-        } else {
-          uint32_t h0, t0;
-          vis_slot(st.cur, a.vis_bits, a.vis_bytes, h0, t0);
-          vis_put(s.vis, a.vis_bytes, h0, t0);
-        }
-      }
-      st.wsize = 1;
-      st.need_init = 0;
+      layer_begin<KIND, LPN, CPL, FULL, EXACT>(h, L, q, qh, s, st, t, g, vis_bm);
+      if (lane == 0) W[0] = wkey(st.cur_d, st.cur);
       wave_sync();
     }
     int wsize = st.wsize;
@@ -722,38 +951,11 @@ __device__ bool advance(const SearchArgs& a, const float (&q)[CPL][8], const h2_
         u = L.adj[(int64_t)c * L.deg + lane];
         if (KIND == kFP8) usc = L.adj_scale[(int64_t)c * L.deg + lane];
       }
-      bool fresh = false;
-      if constexpr (EXACT) {
-        // exact set: the bit's old value says whether u was seen (the
-        // update is atomic, so of lanes holding one id only one finds it new)
-        if (u >= 0) {
-          const uint32_t bit = 1u << (u & 31);
-          fresh = !(atomicOr(vis_bm + (u >> 5), bit) & bit);
-        }
-      } else {
-        uint32_t h = 0, tag = 0;
-        if (u >= 0) {
-          vis_slot(u, a.vis_bits, a.vis_bytes, h, tag);
-          fresh = vis_get(s.vis, a.vis_bytes, h) != tag;
-        }
-        wave_sync();
-        if (fresh) vis_put(s.vis, a.vis_bytes, h, tag);
-      }
-      const uint64_t fm = ballot(fresh);
-      const int cnt = popc64(fm);
-      // the scales ride in kstage, which is free until the merge below
-      float* csc = reinterpret_cast<float*>(s.kstage);
-      if (fresh) {
-        const int rb = rank_below(fm);
-        s.crow[rb] = (uint32_t)u * (uint32_t)a.nchunks;
-        s.cidk[rb] = (uint32_t)u << 1;
-        if (KIND == kFP8) csc[rb] = usc;
-      }
-      wave_sync();
+      const int cnt = take_fresh<KIND, EXACT>(h, s, u, usc, vis_bm);
       st.evals += cnt;
 
-      // gather + distance
-      gather_all<KIND, LPN, CPL, FULL>(a, L, q, qh, s, csc, cnt, t, g);
+      // gather + distance (the scales ride in kstage, free until the merge)
+      gather_all<KIND, LPN, CPL, FULL>(h, L, q, qh, s, cnt, t, g, [] {});
       wave_sync();
 
       // merge the new keys into W (truncated to efl)
@@ -843,14 +1045,118 @@ __device__ bool advance(const SearchArgs& a, const float (&q)[CPL][8], const h2_
   }
 }
 
+// The same traversal with the list in registers (ef_cap <= 64 NB; the caller
+// holds it in R).  An expansion is a chain of two memory round trips (the
+// adjacency row, then the fresh rows) and the list work between them, and a
+// launch that does not fill the chip runs at that chain's latency.  Here the
+// list costs no LDS round trip, only compares, ballots and lane moves, and the
+// neighbours of the entry that comes next as the list stands are read while
+// this one's rows are: unless a new key overtakes it, the next expansion
+// starts with its adjacency row at hand.  Against the list in LDS and no
+// reading ahead, k_search with its root scan: one query on 10,000 x 32 FP32,
+// beam 32, 77 -> 54 us; 48 queries on 300,000 x 128 FP8, beam 84, 260 -> 194;
+// 100,000 with mixed beams on 1.2M x 128 FP8 7.08 -> 5.68 ms.
+template <int KIND, int LPN, int CPL, bool FULL, int NB>
+__device__ bool advance_reg(const SearchArgs& a, const float (&q)[CPL][8],
+                            const h2_t (&qh)[CPL][4], WaveLds s, RegList<NB>& R, QState& st,
+                            int budget) {
+  const int lane = s.lane, t = lane % LPN, g = lane / LPN;
+  const StepArgs h(a);
+  for (;;) {
+    const SearchLayer L = a.layer[st.li];
+    const int efl = st.li == 0 ? st.ef0 : min(a.ef_upper, a.ef_cap);
+    const int off = 64 * NB - efl;
+    if (st.need_init) {
+      layer_begin<KIND, LPN, CPL, FULL, false>(h, L, q, qh, s, st, t, g, nullptr);
+      uint64_t k0 = wkey(st.cur_d, st.cur);
+      if ((k0 >> 32) == 0) k0 |= 1ull << 32;  // above the fillers (see gather_pass)
+      list_start(R, lane, efl, uni_u64(k0));
+      wave_sync();
+    }
+    // lanes past the row read its last entry and drop it
+    const int al = min(lane, L.deg - 1);
+    auto read_row = [&](int32_t c, int32_t& u, float& usc) {
+      u = L.adj[(int64_t)c * L.deg + al];
+      if (KIND == kFP8) usc = L.adj_scale[(int64_t)c * L.deg + al];
+    };
+    // the first unexpanded entry's id, -1 for none, and its place (b_out,
+    // bit); every block's candidate is read and one selected, which is
+    // cheaper than a branch
+    auto first_open = [&](int& b_out, uint64_t& bit) -> int32_t {
+      int32_t id = -1;
+      bit = 0;
+      b_out = 0;
+#pragma unroll
+      for (int b = NB - 1; b >= 0; --b) {
+        const uint64_t m = ~R.ex[b];
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)R.w[b],
+                                                                m ? __builtin_ctzll(m) : 0);
+        id = m ? (int32_t)(lo >> 1) : id;
+        bit = m ? m & (0ull - m) : bit;
+        b_out = m ? b : b_out;
+      }
+      return id;
+    };
+    bool layer_done = false;
+    int32_t next = -1, next_u = -1;  // the entry read ahead, its neighbours
+    float next_usc = 1.0f;
+    while (budget > 0) {
+      int b = 0;
+      uint64_t bit = 0;
+      const int32_t c = first_open(b, bit);
+      if (c < 0) {
+        layer_done = true;
+        break;
+      }
+      --budget;
+      ++st.exps;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) R.ex[i] |= i == b ? bit : 0ull;
+      int32_t u = next_u;
+      float usc = next_usc;
+      if (c != next) read_row(c, u, usc);
+      next = first_open(b, bit);
+      const int cnt = take_fresh<KIND, false>(h, s, lane < L.deg ? u : -1, usc, nullptr);
+      st.evals += cnt;
+      gather_all<KIND, LPN, CPL, FULL>(h, L, q, qh, s, cnt, t, g,
+                                       [&] { read_row(next >= 0 ? next : c, next_u, next_usc); });
+      wave_sync();
+      const uint64_t key = lane < cnt ? s.ckey[lane] : ~0ull;
+      uint64_t open = ballot(key < readlane_u64(R.w[NB - 1], 63));
+      while (open) {
+        const uint64_t k = readlane_u64(key, __builtin_ctzll(open));
+        open &= open - 1;
+        if (list_insert(R, off, k)) {
+          st.wsize += 1;
+          open &= ballot(key < readlane_u64(R.w[NB - 1], 63));
+        }
+      }
+      wave_sync();  // the candidate slots are read before the next expansion writes them
+    }
+    st.wsize = min(st.wsize, efl);
+    if (!layer_done) return false;
+    if (st.li == 0) return true;
+    // hand the best node down the inter-layer edge
+    uint64_t best = 0;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      if (off >> 6 == b) best = readlane_u64(R.w[b], off & 63);
+    st.cur = uni(L.down[wkey_id(best)]);
+    st.cur_d = wkey_dist(best);
+    st.li -= 1;
+    st.need_init = 1;
+    wave_sync();
+  }
+}
+
 // Writes the first k results (after the FP32 re-rank for the precision
 // forms) to out_ids / out_dist (k_max entries, padded) and the counters.
 template <int KIND, int LPN, int CPL>
-__device__ void finish_query(const SearchArgs& a, const float (&q)[CPL][8], uint64_t* W,
-                             const QState& st, int32_t* out_ids, float* out_dist,
+__device__ void finish_query(const SearchArgs& a, const float (&q)[CPL][8], int lane,
+                             uint64_t* W, const QState& st, int32_t* out_ids, float* out_dist,
                              int32_t* counters) {
   constexpr int G = 64 / LPN;
-  const int lane = lane_id(), t = lane % LPN, g = lane / LPN;
+  const int t = lane % LPN, g = lane / LPN;
   const int k = st.k, wsize = st.wsize;
   if (a.rerank_vec == nullptr) {
     for (int j = lane; j < a.k_max; j += 64) {
@@ -903,40 +1209,48 @@ __device__ void finish_query(const SearchArgs& a, const float (&q)[CPL][8], uint
 
 // The per-query time output, read from the kernel's argument segment at the
 // point of use (SearchArgs is the first argument of every kernel that calls
-// search_one, so it starts the segment).  A volatile read: the traversal keeps
-// its scalar registers full, and a pointer held across it would spill.
+// search_one, so it starts the segment) through an opaque pointer: the
+// traversal keeps its scalar registers full, and a pointer held across it
+// would spill.
 __device__ __forceinline__ int64_t* query_ns_arg() {
-  const SearchArgs* ka = reinterpret_cast<const SearchArgs*>(
-      (const char*)__builtin_amdgcn_kernarg_segment_ptr());
-  return *reinterpret_cast<int64_t* const volatile*>(&ka->query_ns);
+  auto* kp = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(kp));
+  return reinterpret_cast<const SearchArgs*>((const char*)kp)->query_ns;
 }
 
-template <int KIND, int LPN, int CPL, bool FULL, bool EXACT>
+template <int KIND, int LPN, int CPL, bool FULL, bool EXACT, int NB>
 __device__ void search_one(const SearchArgs& a, int64_t qi, WaveLds s) {
+  s.lane = fresh_lane();
   // the constant-rate clock when times are asked for; the start waits in the
   // query's output word (volatile: a memory round trip, so no register stays
   // live across the traversal)
-  if (lane_id() == 0) {
-    int64_t* qt = query_ns_arg();
-    if (qt) *reinterpret_cast<volatile int64_t*>(qt + qi) = (int64_t)wall_clock64();
+  if (int64_t* qt = query_ns_arg()) {
+    if (s.lane == 0) *reinterpret_cast<volatile int64_t*>(qt + qi) = (int64_t)wall_clock64();
   }
-  const int t = lane_id() % LPN;
+  const int t = s.lane % LPN;
   float q[CPL][8];
   load_query<CPL>(a.Q + qi * a.d, a.d, t, q);
   QState st;
-  start_query<KIND, LPN, CPL>(a, qi, q, st);
+  start_query<KIND, LPN, CPL>(a, qi, q, s.lane, st);
   h2_t qh[CPL][4];
   if constexpr (KIND == kFP8) query_f16<CPL>(q, qh);
   uint64_t* W = s.W;
-  uint32_t* vis_bm = EXACT ? a.vis_exact + qi * a.vis_exact_words : nullptr;
-  advance<KIND, LPN, CPL, FULL, EXACT>(a, q, qh, s, W, st, 0x7fffffff, vis_bm);
+  if constexpr (NB == 0) {
+    uint32_t* vis_bm = EXACT ? a.vis_exact + qi * a.vis_exact_words : nullptr;
+    advance<KIND, LPN, CPL, FULL, EXACT>(a, q, qh, s, W, st, 0x7fffffff, vis_bm);
+  } else {
+    RegList<NB> R;
+    advance_reg<KIND, LPN, CPL, FULL, NB>(a, q, qh, s, R, st, 0x7fffffff);
+    list_store(R, s.lane, st.ef0, st.wsize, W, false);
+    wave_sync();
+  }
   // the FP8 traversal holds only the f16 query; the FP32 re-rank reads it again
   if constexpr (KIND == kFP8) load_query<CPL>(a.Q + qi * a.d, a.d, t, q);
-  finish_query<KIND, LPN, CPL>(a, q, W, st, a.out_ids + qi * a.k_max,
+  finish_query<KIND, LPN, CPL>(a, q, s.lane, W, st, a.out_ids + qi * a.k_max,
                                a.out_dist + qi * a.k_max,
                                a.counters ? a.counters + qi * 4 : nullptr);
-  int64_t* qt = lane_id() == 0 ? query_ns_arg() : nullptr;
-  if (qt) {
+  int64_t* qt = query_ns_arg();
+  if (qt && s.lane == 0) {
     volatile int64_t* slot = reinterpret_cast<volatile int64_t*>(qt + qi);
     const uint32_t ticks = (uint32_t)((uint64_t)wall_clock64() - (uint64_t)*slot);
     *slot = (int64_t)((double)ticks * a.clock_ns);
@@ -951,17 +1265,17 @@ __device__ void search_one(const SearchArgs& a, int64_t qi, WaveLds s) {
 // finishes appends its slot and result row to the tick's compact completion
 // list.  The traversal is the batch kernel's own code, so
 // a request's result does not depend on which others share its ticks.
-template <int KIND, int LPN, int CPL, bool FULL>
+template <int KIND, int LPN, int CPL, bool FULL, int NB>
 __device__ __forceinline__ void serve_step_body(const SearchArgs& a, const ServeArgs& sv,
                                                 int per_wave_bytes, int waves_per_block) {
   extern __shared__ __align__(16) char smem[];
-  const int wave = threadIdx.x >> 6;
+  const int wave = uni(threadIdx.x >> 6);
   const int64_t idx = (int64_t)blockIdx.x * waves_per_block + wave;
   if (blockIdx.x == 0 && threadIdx.x == 0) *sv.done_clear = 0;
   if (idx >= sv.n_active) return;
   const int lane = lane_id(), t = lane % LPN;
   const int32_t slot = uni(sv.active[idx]);
-  WaveLds s = carve(smem + (size_t)wave * per_wave_bytes, a.ef_cap, a.vis_bits, a.vis_bytes);
+  WaveLds s = carve<NB>(smem + (size_t)wave * per_wave_bytes, a.ef_cap);
   float q[CPL][8];
   load_query<CPL>(a.Q + (int64_t)slot * a.d, a.d, t, q);
   QState st = sv.states[slot];
@@ -976,17 +1290,33 @@ __device__ __forceinline__ void serve_step_body(const SearchArgs& a, const Serve
   uint64_t* gW = reinterpret_cast<uint64_t*>(base);
   uint32_t* gvis = reinterpret_cast<uint32_t*>(base + (size_t)sv.cap[slot] * 8);
   const int vis_n = (1 << a.vis_bits) * a.vis_bytes / 4;  // 32-bit words of the table
+  // the list's width in the layer the state was saved in
+  auto width = [&]() { return st.li == 0 ? st.ef0 : min(a.ef_upper, a.ef_cap); };
+  RegList<NB == 0 ? 1 : NB> R;
   if (st.li == kSlotNew) {
-    start_query<KIND, LPN, CPL>(a, slot, q, st);
+    start_query<KIND, LPN, CPL>(a, slot, q, lane, st);
   } else if (!st.need_init) {
-    for (int i = lane; i < st.wsize; i += 64) s.W[i] = gW[i];
+    if constexpr (NB == 0) {
+      for (int i = lane; i < st.wsize; i += 64) s.W[i] = gW[i];
+    } else {
+      list_load(R, lane, width(), st.wsize, gW);
+    }
     for (int i = lane; i < vis_n; i += 64) static_cast<uint32_t*>(s.vis)[i] = gvis[i];
     wave_sync();
   }
   uint64_t* W = s.W;
   h2_t qh[CPL][4];
   if constexpr (KIND == kFP8) query_f16<CPL>(q, qh);
-  const bool done = advance<KIND, LPN, CPL, FULL>(a, q, qh, s, W, st, sv.budget, nullptr);
+  bool done;
+  if constexpr (NB == 0) {
+    done = advance<KIND, LPN, CPL, FULL>(a, q, qh, s, W, st, sv.budget, nullptr);
+  } else {
+    done = advance_reg<KIND, LPN, CPL, FULL, NB>(a, q, qh, s, R, st, sv.budget);
+    if (done) {
+      list_store(R, s.lane, st.ef0, st.wsize, W, false);
+      wave_sync();
+    }
+  }
   if (done) {
     if constexpr (KIND == kFP8) load_query<CPL>(a.Q + (int64_t)slot * a.d, a.d, t, q);
     // finished: append (slot, row) to this tick's compact completion list
@@ -994,41 +1324,45 @@ __device__ __forceinline__ void serve_step_body(const SearchArgs& a, const Serve
     if (lane == 0) pos = atomicAdd(sv.done_count, 1);
     pos = __shfl(pos, 0);
     int32_t* row = sv.done_rows + (int64_t)pos * (1 + 2 * a.k_max);
-    finish_query<KIND, LPN, CPL>(a, q, W, st, row + 1,
+    finish_query<KIND, LPN, CPL>(a, q, s.lane, W, st, row + 1,
                                  reinterpret_cast<float*>(row + 1 + a.k_max), nullptr);
     st.li = kSlotDone;
     if (lane == 0) row[0] = slot;
   } else if (!st.need_init) {
-    for (int i = lane; i < st.wsize; i += 64) gW[i] = W[i];
+    if constexpr (NB == 0) {
+      for (int i = lane; i < st.wsize; i += 64) gW[i] = W[i];
+    } else {
+      list_store(R, lane, width(), st.wsize, gW, true);
+    }
     for (int i = lane; i < vis_n; i += 64) gvis[i] = static_cast<uint32_t*>(s.vis)[i];
   }
   if (lane == 0) sv.states[slot] = st;
 }
 
-template <int KIND, int LPN, int CPL, bool FULL>
+template <int KIND, int LPN, int CPL, bool FULL, int NB>
 __global__ __launch_bounds__(512) void k_serve_step(SearchArgs a, ServeArgs sv, int per_wave_bytes,
                                                     int waves_per_block) {
-  serve_step_body<KIND, LPN, CPL, FULL>(a, sv, per_wave_bytes, waves_per_block);
+  serve_step_body<KIND, LPN, CPL, FULL, NB>(a, sv, per_wave_bytes, waves_per_block);
 }
 
 // The FP8 form with at most two chunks per lane fits 80 registers without
 // spilling in the traversal loop; held to that, six waves share a SIMD (the
 // LDS of a wave at the usual beam widths also allows six).
-template <int KIND, int CPL>
-constexpr bool six_waves() { return KIND == kFP8 && CPL <= 2; }
+template <int KIND, int CPL, int NB>
+constexpr bool six_waves() { return KIND == kFP8 && CPL <= 2 && NB <= 2; }
 
-template <int KIND, int LPN, int CPL, bool FULL>
+template <int KIND, int LPN, int CPL, bool FULL, int NB>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void k_serve_step6(
     SearchArgs a, ServeArgs sv, int per_wave_bytes, int waves_per_block) {
-  serve_step_body<KIND, LPN, CPL, FULL>(a, sv, per_wave_bytes, waves_per_block);
+  serve_step_body<KIND, LPN, CPL, FULL, NB>(a, sv, per_wave_bytes, waves_per_block);
 }
 
-template <int KIND, int LPN, int CPL, bool FULL>
+template <int KIND, int LPN, int CPL, bool FULL, int NB>
 static auto serve_kernel() {
-  if constexpr (six_waves<KIND, CPL>())
-    return &k_serve_step6<KIND, LPN, CPL, FULL>;
+  if constexpr (six_waves<KIND, CPL, NB>())
+    return &k_serve_step6<KIND, LPN, CPL, FULL, NB>;
   else
-    return &k_serve_step<KIND, LPN, CPL, FULL>;
+    return &k_serve_step<KIND, LPN, CPL, FULL, NB>;
 }
 
 static __global__ void k_serve_admit(const float* staged_q, const int32_t* meta, int n_new, int d,
@@ -1055,66 +1389,74 @@ static __global__ void k_serve_admit(const float* staged_q, const int32_t* meta,
   }
 }
 
-template <int KIND, int LPN, int CPL, bool FULL>
+template <int KIND, int LPN, int CPL, bool FULL, int NB>
 static void launch_serve_one(const SearchArgs& a, const ServeArgs& sv, int wpb, hipStream_t st) {
   const size_t per_wave = search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes);
   const unsigned blocks = (unsigned)((sv.n_active + wpb - 1) / wpb);
-  auto kern = serve_kernel<KIND, LPN, CPL, FULL>();
+  auto kern = serve_kernel<KIND, LPN, CPL, FULL, NB>();
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * wpb), per_wave * wpb, st, a, sv,
                      (int)per_wave, wpb);
 }
 
-template <int KIND, int LPN, int CPL, bool FULL, bool EXACT>
+template <int KIND, int LPN, int CPL, bool FULL, bool EXACT, int NB>
 __device__ __forceinline__ void search_kernel_body(const SearchArgs& a, int per_wave_bytes,
                                                    int waves_per_block, int persistent) {
   extern __shared__ __align__(16) char smem[];
-  const int wave = threadIdx.x >> 6;
-  WaveLds s = carve(smem + (size_t)wave * per_wave_bytes, a.ef_cap, a.vis_bits, a.vis_bytes);
-  if (persistent) {
-    for (;;) {
-      uint32_t qi = 0;
-      if (lane_id() == 0) qi = atomicAdd(a.work_counter, 1u);
-      qi = (uint32_t)uni((int32_t)qi);
-      if ((int64_t)qi >= a.nq) break;
-      search_one<KIND, LPN, CPL, FULL, EXACT>(a, (int64_t)qi, s);
+  const int wave = uni(threadIdx.x >> 6);
+  WaveLds s = carve<NB>(smem + (size_t)wave * per_wave_bytes, a.ef_cap);
+  // one copy of the search for both forms: the one-shot form makes one pass
+  // of the loop.  The arguments are read afresh in each pass (the pointer is
+  // opaque), or the compiler holds them all in registers across the passes.
+  for (;;) {
+    int64_t qi = (int64_t)blockIdx.x * waves_per_block + wave;
+    auto* kp = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(kp));
+    const SearchArgs& aa = *reinterpret_cast<const SearchArgs*>((const char*)kp);
+    if (persistent) {
+      uint32_t w = 0;
+      if (lane_id() == 0) w = atomicAdd(aa.work_counter, 1u);
+      qi = (int64_t)(uint32_t)uni((int32_t)w);
     }
-  } else {
-    const int64_t qi = (int64_t)blockIdx.x * waves_per_block + wave;
-    if (qi < a.nq) search_one<KIND, LPN, CPL, FULL, EXACT>(a, qi, s);
+    if (qi >= aa.nq) break;
+    search_one<KIND, LPN, CPL, FULL, EXACT, NB>(aa, qi, s);
+    if (!persistent) break;
   }
 }
 
-template <int KIND, int LPN, int CPL, bool FULL, bool EXACT = false>
+template <int KIND, int LPN, int CPL, bool FULL, int NB, bool EXACT = false>
 __global__ __launch_bounds__(512) void k_search(SearchArgs a, int per_wave_bytes,
                                                 int waves_per_block, int persistent) {
-  search_kernel_body<KIND, LPN, CPL, FULL, EXACT>(a, per_wave_bytes, waves_per_block, persistent);
+  search_kernel_body<KIND, LPN, CPL, FULL, EXACT, NB>(a, per_wave_bytes, waves_per_block, persistent);
 }
 
 // The same kernel held to 80 registers (see six_waves).
-template <int KIND, int LPN, int CPL, bool FULL>
+template <int KIND, int LPN, int CPL, bool FULL, int NB>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) void k_search6(
     SearchArgs a, int per_wave_bytes, int waves_per_block, int persistent) {
-  search_kernel_body<KIND, LPN, CPL, FULL, false>(a, per_wave_bytes, waves_per_block, persistent);
+  search_kernel_body<KIND, LPN, CPL, FULL, false, NB>(a, per_wave_bytes, waves_per_block, persistent);
 }
 
-template <int KIND, int LPN, int CPL, bool FULL>
+template <int KIND, int LPN, int CPL, bool FULL, int NB>
 static auto search_kernel(bool exact) {
   // the exact visited set (an analysis form) runs the general-width kernel
-  if (exact) return &k_search<KIND, LPN, CPL, false, true>;
-  if constexpr (six_waves<KIND, CPL>())
-    return &k_search6<KIND, LPN, CPL, FULL>;
+  if constexpr (NB == 0) {
+    if (exact) return &k_search<KIND, LPN, CPL, false, 0, true>;
+  }
+  if constexpr (six_waves<KIND, CPL, NB>())
+    return &k_search6<KIND, LPN, CPL, FULL, NB>;
   else
-    return &k_search<KIND, LPN, CPL, FULL>;
+    return &k_search<KIND, LPN, CPL, FULL, NB>;
 }
 
 static __global__ void k_reset_counter(uint32_t* c) { *c = 0u; }
 
-template <int KIND, int LPN, int CPL, bool FULL>
+template <int KIND, int LPN, int CPL, bool FULL, int NB>
 static void launch_one(const SearchArgs& a, const LaunchShape& sh, hipStream_t st) {
-  const size_t per_wave = search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes);
+  const bool exact = a.vis_exact != nullptr;
+  const size_t per_wave = search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes, exact);
   const int wpb = sh.waves_per_block;
   const size_t lds = per_wave * wpb;
-  auto kern = search_kernel<KIND, LPN, CPL, FULL>(a.vis_exact != nullptr);
+  auto kern = search_kernel<KIND, LPN, CPL, FULL, NB>(exact);
   if (sh.persistent) {
     int blocks = sh.blocks;
     if (blocks <= 0) {
@@ -1138,14 +1480,14 @@ static void launch_one(const SearchArgs& a, const LaunchShape& sh, hipStream_t s
   X(1, 1) X(2, 1) X(4, 1) X(2, 2) X(4, 2) X(8, 1) X(2, 4) X(4, 4) X(8, 2) X(16, 1) X(8, 4) \
   X(16, 2) X(4, 8) X(16, 4) X(16, 8)
 
-template <int KIND>
-static bool dispatch(const SearchArgs& a, const LaunchShape& sh, hipStream_t st) {
+template <int KIND, int NB>
+bool search_dispatch(const SearchArgs& a, const LaunchShape& sh, hipStream_t st) {
 #define HENN_TRY(LPN, CPL)                              \
   if (sh.lanes_per_vec == LPN && sh.chunks_per_lane == CPL) { \
     if (a.nchunks == LPN * CPL)                         \
-      launch_one<KIND, LPN, CPL, true>(a, sh, st);      \
+      launch_one<KIND, LPN, CPL, true, NB>(a, sh, st);  \
     else                                                \
-      launch_one<KIND, LPN, CPL, false>(a, sh, st);     \
+      launch_one<KIND, LPN, CPL, false, NB>(a, sh, st); \
     return true;                                        \
   }
   HENN_SEARCH_COMBOS(HENN_TRY)
@@ -1153,40 +1495,15 @@ static bool dispatch(const SearchArgs& a, const LaunchShape& sh, hipStream_t st)
   return false;
 }
 
-#if HENN_COMMON_PART
-// The gather addresses a row by its 32-bit first-chunk index.
-bool rows_addressable(const SearchArgs& a) {
-  for (int i = 0; i < a.num_layers; ++i)
-    if ((int64_t)a.layer[i].size * a.nchunks >= (1ll << 32)) return false;
-  return true;
-}
-#endif
-
-#if HENN_KIND_PART(0)  // kF32
-bool launch_search_f32(const SearchArgs& a, const LaunchShape& s, hipStream_t st) {
-  return dispatch<kF32>(a, s, st);
-}
-#endif
-#if HENN_KIND_PART(1)  // kBF16
-bool launch_search_bf16(const SearchArgs& a, const LaunchShape& s, hipStream_t st) {
-  return dispatch<kBF16>(a, s, st);
-}
-#endif
-#if HENN_KIND_PART(2)  // kFP8
-bool launch_search_fp8(const SearchArgs& a, const LaunchShape& s, hipStream_t st) {
-  return dispatch<kFP8>(a, s, st);
-}
-#endif
-
-template <int KIND>
-static bool dispatch_serve(const SearchArgs& a, const ServeArgs& sv, const LaunchShape& sh,
-                           hipStream_t st) {
+template <int KIND, int NB>
+bool serve_dispatch(const SearchArgs& a, const ServeArgs& sv, const LaunchShape& sh,
+                    hipStream_t st) {
 #define HENN_TRY(LPN, CPL)                                        \
   if (sh.lanes_per_vec == LPN && sh.chunks_per_lane == CPL) {     \
     if (a.nchunks == LPN * CPL)                                   \
-      launch_serve_one<KIND, LPN, CPL, true>(a, sv, sh.waves_per_block, st);  \
+      launch_serve_one<KIND, LPN, CPL, true, NB>(a, sv, sh.waves_per_block, st);  \
     else                                                          \
-      launch_serve_one<KIND, LPN, CPL, false>(a, sv, sh.waves_per_block, st); \
+      launch_serve_one<KIND, LPN, CPL, false, NB>(a, sv, sh.waves_per_block, st); \
     return true;                                                  \
   }
   HENN_SEARCH_COMBOS(HENN_TRY)
@@ -1194,33 +1511,87 @@ static bool dispatch_serve(const SearchArgs& a, const ServeArgs& sv, const Launc
   return false;
 }
 
-#if HENN_KIND_PART(0)  // kF32
-bool launch_serve_f32(const SearchArgs& a, const ServeArgs& sv, const LaunchShape& sh,
-                      hipStream_t st) {
-  return dispatch_serve<kF32>(a, sv, sh, st);
-}
+// One translation unit per (rows, list) pair instantiates its kernels; the
+// common part only refers to them.
+#define HENN_INST(PART, KIND, NB, EXT)                                                       \
+  EXT template bool search_dispatch<KIND, NB>(const SearchArgs&, const LaunchShape&,         \
+                                              hipStream_t);                                  \
+  EXT template bool serve_dispatch<KIND, NB>(const SearchArgs&, const ServeArgs&,            \
+                                             const LaunchShape&, hipStream_t);
+#if HENN_PART < 0 || HENN_PART == 1
+HENN_INST(1, kF32, 0, )
 #endif
-#if HENN_KIND_PART(1)  // kBF16
-bool launch_serve_bf16(const SearchArgs& a, const ServeArgs& sv, const LaunchShape& sh,
-                       hipStream_t st) {
-  return dispatch_serve<kBF16>(a, sv, sh, st);
-}
+#if HENN_PART < 0 || HENN_PART == 2
+HENN_INST(2, kF32, 2, )
 #endif
-#if HENN_KIND_PART(2)  // kFP8
-bool launch_serve_fp8(const SearchArgs& a, const ServeArgs& sv, const LaunchShape& sh,
-                      hipStream_t st) {
-  return dispatch_serve<kFP8>(a, sv, sh, st);
-}
+#if HENN_PART < 0 || HENN_PART == 3
+HENN_INST(3, kF32, 4, )
+#endif
+#if HENN_PART < 0 || HENN_PART == 4
+HENN_INST(4, kBF16, 0, )
+#endif
+#if HENN_PART < 0 || HENN_PART == 5
+HENN_INST(5, kBF16, 2, )
+#endif
+#if HENN_PART < 0 || HENN_PART == 6
+HENN_INST(6, kBF16, 4, )
+#endif
+#if HENN_PART < 0 || HENN_PART == 7
+HENN_INST(7, kFP8, 0, )
+#endif
+#if HENN_PART < 0 || HENN_PART == 8
+HENN_INST(8, kFP8, 2, )
+#endif
+#if HENN_PART < 0 || HENN_PART == 9
+HENN_INST(9, kFP8, 4, )
 #endif
 
 #if HENN_COMMON_PART
+#if HENN_PART == 0
+HENN_INST(1, kF32, 0, extern)
+HENN_INST(2, kF32, 2, extern)
+HENN_INST(3, kF32, 4, extern)
+HENN_INST(4, kBF16, 0, extern)
+HENN_INST(5, kBF16, 2, extern)
+HENN_INST(6, kBF16, 4, extern)
+HENN_INST(7, kFP8, 0, extern)
+HENN_INST(8, kFP8, 2, extern)
+HENN_INST(9, kFP8, 4, extern)
+#endif
+
+// The gather addresses a row by its 32-bit first-chunk index.
+bool rows_addressable(const SearchArgs& a) {
+  for (int i = 0; i < a.num_layers; ++i)
+    if ((int64_t)a.layer[i].size * a.nchunks >= (1ll << 32)) return false;
+  return true;
+}
+
+template <int KIND>
+static bool launch_search_kind(const SearchArgs& a, const LaunchShape& s, hipStream_t st) {
+  switch (a.vis_exact ? 0 : list_blocks(a.ef_cap)) {
+    case 2: return search_dispatch<KIND, 2>(a, s, st);
+    case 4: return search_dispatch<KIND, 4>(a, s, st);
+    default: return search_dispatch<KIND, 0>(a, s, st);
+  }
+}
+
 bool launch_search(int storage, const SearchArgs& a, const LaunchShape& s, hipStream_t st) {
   if (!rows_addressable(a)) return false;
   switch (storage) {
-    case kF32: return launch_search_f32(a, s, st);
-    case kBF16: return launch_search_bf16(a, s, st);
-    case kFP8: return launch_search_fp8(a, s, st);
+    case kF32: return launch_search_kind<kF32>(a, s, st);
+    case kBF16: return launch_search_kind<kBF16>(a, s, st);
+    case kFP8: return launch_search_kind<kFP8>(a, s, st);
     default: return false;
+  }
+}
+
+template <int KIND>
+static bool launch_serve_kind(const SearchArgs& a, const ServeArgs& sv, const LaunchShape& sh,
+                              hipStream_t st) {
+  switch (list_blocks(a.ef_cap)) {
+    case 2: return serve_dispatch<KIND, 2>(a, sv, sh, st);
+    case 4: return serve_dispatch<KIND, 4>(a, sv, sh, st);
+    default: return serve_dispatch<KIND, 0>(a, sv, sh, st);
   }
 }
 
@@ -1229,9 +1600,9 @@ bool launch_serve_step(int storage, const SearchArgs& a, const ServeArgs& sv,
   if (sv.n_active <= 0) return true;
   if (!rows_addressable(a)) return false;
   switch (storage) {
-    case kF32: return launch_serve_f32(a, sv, sh, st);
-    case kBF16: return launch_serve_bf16(a, sv, sh, st);
-    case kFP8: return launch_serve_fp8(a, sv, sh, st);
+    case kF32: return launch_serve_kind<kF32>(a, sv, sh, st);
+    case kBF16: return launch_serve_kind<kBF16>(a, sv, sh, st);
+    case kFP8: return launch_serve_kind<kFP8>(a, sv, sh, st);
     default: return false;
   }
 }

@@ -1120,3 +1120,30 @@ def test_delete_argument_errors(hn):
     with pytest.raises(hn.HennError):
         hn.henn_delete(knn, [1])
     knn.free()
+
+
+# ---------------------------------------- the beam's list in registers ----
+
+@pytest.mark.parametrize("storage", ["f32", "bf16", "fp8"])
+@pytest.mark.parametrize("metric", [0, 1])
+def test_register_list_equals_lds_list_at_block_edges(hn, storage, metric):
+    """Beams up to 256 keep their list in registers, 64 positions a block,
+    wider ones and the exact visited set in LDS: both give the same bits.  Beam
+    widths around the blocks' edges, an upper beam wider than the layer-0 one,
+    and every width of the visited table's entries."""
+    X = wl.expskew(3000, 20, 32.0, 51)
+    Q = wl.expskew(65, 20, 32.0, 52)
+    idx = hn.henn_build(to_dev(X), degree=16, max_degree=28, graph="knn_sym", metric=metric,
+                        storage=storage)
+    Qd = to_dev(Q)
+    for ef in (1, 2, 63, 64, 65, 127, 128, 129, 191, 192, 255, 256, 257):
+        k = min(ef, 100)
+        for kw in (dict(), dict(vis16=True), dict(vis32=True, ef_upper=70), dict(vis_bits=8)):
+            a_i, a_d = hn.henn_search_batch(idx, Qd, k=k, ef=ef, **kw)
+            b_i, b_d = hn.henn_search_batch(idx, Qd, k=k, ef=ef, exact_visited=True,
+                                            ef_upper=kw.get("ef_upper", 1))
+            _sync()
+            assert np.array_equal(a_i.cpu().numpy(), b_i.cpu().numpy()), (ef, kw)
+            assert np.array_equal(a_d.cpu().numpy().view(np.uint32),
+                                  b_d.cpu().numpy().view(np.uint32)), (ef, kw)
+    idx.free()
