@@ -1092,6 +1092,21 @@ static int device_clock_khz() {
   return r;
 }
 
+// Compute units of the current device (read once per device).
+static int device_cus() {
+  static std::atomic<int> cus[64];
+  int dev = 0;
+  HENN_HIP(hipGetDevice(&dev));
+  if (dev < 0 || dev >= 64) throw HipError{hipErrorInvalidDevice, "device index"};
+  int c = cus[dev].load(std::memory_order_relaxed);
+  if (c <= 0) {
+    HENN_HIP(hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev));
+    if (c <= 0) throw HipError{hipErrorInvalidValue, "compute units"};
+    cus[dev].store(c, std::memory_order_relaxed);
+  }
+  return c;
+}
+
 // The search behind henn_search_batch and henn_search_batch_noalloc.
 // Scratch (the persistent work counter, then the root-scan keys) comes from
 // `fixed` when given (fixed_bytes must hold search_workspace_bytes), else from
@@ -1170,6 +1185,7 @@ static henn_status search_impl(const henn_index* idx, const float* Q, int64_t nq
     // autotuned shape for this (storage, beam bucket, k bucket), if cached
     int want_lpn = sp->lanes_per_vec, want_wpb = sp->waves_per_block;
     bool want_pers = (sp->flags & HENN_SEARCH_PERSISTENT) != 0;
+    bool own_vis = sp->vis_bits != 0;  // the caller's or the tuner's table size
     {
       std::lock_guard<std::mutex> lk(const_cast<henn_index*>(idx)->tune_mu);
       for (const TuneEntry& te : idx->tune) {
@@ -1177,7 +1193,8 @@ static henn_status search_impl(const henn_index* idx, const float* Q, int64_t nq
             te.k_bucket == next_pow2(sp->k_max)) {
           if (!want_lpn) want_lpn = te.lanes_per_vec;
           if (!want_wpb) want_wpb = te.waves_per_block;
-          if (!sp->vis_bits) a.vis_bits = te.vis_bits;
+          if (!own_vis) a.vis_bits = te.vis_bits;
+          own_vis = true;
           if (te.persistent && !(sp->flags & HENN_SEARCH_PERSISTENT)) want_pers = true;
           break;
         }
@@ -1185,10 +1202,13 @@ static henn_status search_impl(const henn_index* idx, const float* Q, int64_t nq
     }
     LaunchShape sh;
     int lpn = 0, cpl = 0;
-    pick_lanes(idx->nchunks, want_lpn, &lpn, &cpl);
+    pick_search_lanes(idx->storage, idx->nchunks, nq, device_cus(), want_lpn, &lpn, &cpl);
     if (lpn == 0) return fail(HENN_E_INVAL, "lanes_per_vec not available for this dimension");
     sh.lanes_per_vec = lpn;
     sh.chunks_per_lane = cpl;
+    if (!own_vis && !(sp->flags & (HENN_SEARCH_VIS16 | HENN_SEARCH_VIS32 | HENN_SEARCH_EXACT_VISITED)))
+      a.vis_bits = pick_vis_bits(idx->storage, cpl, ef_need, idx->L[0].deg, idx->n, nq,
+                                 device_cus(), a.vis_bits);
     sh.vis_bits = a.vis_bits;
     a.vis_bytes = (sp->flags & HENN_SEARCH_VIS32) ? 4 : vis_tag_bytes(idx->n, a.vis_bits);
     if (a.vis_bytes == 1 && (sp->flags & HENN_SEARCH_VIS16)) a.vis_bytes = 2;

@@ -386,4 +386,25 @@ void prune_graph(const float* vec, int64_t size, int dpad, int nchunks, int metr
 // Picks (lanes per vector, chunks per lane) for a dimension.
 void pick_lanes(int nchunks, int requested_lpn, int* lpn, int* cpl);
 
+// The same for a search of nq queries.  Few lanes a row put more rows into
+// one pass of loads, which is what a batch that does not fill the chip waits
+// for; many lanes leave a wave fewer registers, and more waves fit.  So a
+// lane takes up to four chunks (two of FP32, 64 bytes) until the batch is
+// past what that shape keeps resident, two from there on.  300,000 x 128,
+// beam 84, us for four / two chunks a lane: FP8 199 / 217 at 48 queries,
+// 318 / 311 at 3,000, 508 / 448 at 6,000, 1923 / 1709 at 30,000; BF16 219 /
+// 249, 363 / 373, 626 / 699, 2551 / 2512 (950 / 916 at 10,000); FP32 261 /
+// 248, 657 / 549, 1132 / 1000, 5101 / 4632.
+void pick_search_lanes(int storage, int nchunks, int64_t nq, int cus, int requested_lpn, int* lpn,
+                       int* cpl);
+
+// log2 of the visited table's entries for a search of nq queries, at least
+// `base`: the largest table (to 2^14) that costs no resident wave its LDS,
+// and no more than eight entries per possible evaluation of the beam.  A
+// larger table forgets fewer rows: 300,000 x 128, beam 84, 3315 evaluations
+// a query at 2^12 one-byte entries against 2995 distinct rows; 60,000 x 768,
+// beam 256, 8197 against 6210.
+int pick_vis_bits(int storage, int cpl, int ef_need, int deg, int64_t n, int64_t nq, int cus,
+                  int base);
+
 }  // namespace henn

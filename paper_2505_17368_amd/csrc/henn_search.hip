@@ -29,6 +29,8 @@
 // HENN_PART one translation unit holds everything.
 #include <math.h>
 
+#include <algorithm>
+
 #include "henn_device.h"
 #include "henn_internal.h"
 
@@ -1644,27 +1646,55 @@ bool launch_root_check(int storage, const SearchArgs& a, const RootShortlist& sl
   }
 }
 
-void pick_lanes(int nchunks, int requested_lpn, int* lpn, int* cpl) {
+// instantiated (LPN, CPL) pairs
+static const int kCombos[][2] = {{1, 1}, {2, 1},  {4, 1},  {2, 2}, {4, 2},  {8, 1},
+                                 {2, 4}, {4, 4},  {8, 2},  {16, 1}, {8, 4},  {16, 2},
+                                 {4, 8}, {16, 4}, {16, 8}};
+
+// The pair with LPN * CPL = P: the requested lanes, else the fewest lanes
+// with at most max_cpl chunks per lane (or the most lanes there are).
+static void pick_lanes_at_most(int nchunks, int requested_lpn, int max_cpl, int* lpn, int* cpl) {
   const int P = next_pow2(nchunks);
-  // instantiated (LPN, CPL) pairs with LPN * CPL == P
-  static const int combos[][2] = {{1, 1}, {2, 1},  {4, 1},  {2, 2}, {4, 2},  {8, 1},
-                                  {2, 4}, {4, 4},  {8, 2},  {16, 1}, {8, 4},  {16, 2},
-                                  {4, 8}, {16, 4}, {16, 8}};
   int best_l = 0, best_c = 0;
-  for (auto& c : combos) {
+  for (auto& c : kCombos) {
     if (c[0] * c[1] != P) continue;
     if (requested_lpn > 0) {
       if (c[0] == requested_lpn) { best_l = c[0]; best_c = c[1]; }
       continue;
     }
-    // default: the fewest lanes with at most 4 chunks per lane
-    if (best_l == 0 || (c[1] <= 4 && (best_c > 4 || c[0] < best_l))) {
+    if (best_l == 0 || (c[1] <= max_cpl ? best_c > max_cpl || c[0] < best_l : c[1] < best_c)) {
       best_l = c[0];
       best_c = c[1];
     }
   }
   *lpn = best_l;
   *cpl = best_c;
+}
+
+void pick_lanes(int nchunks, int requested_lpn, int* lpn, int* cpl) {
+  pick_lanes_at_most(nchunks, requested_lpn, 4, lpn, cpl);
+}
+
+void pick_search_lanes(int storage, int nchunks, int64_t nq, int cus, int requested_lpn, int* lpn,
+                       int* cpl) {
+  const int64_t simds = 4ll * cus;
+  const bool many = storage == kFP8 ? nq > 3 * simds : nq > 8 * simds;
+  pick_lanes_at_most(nchunks, requested_lpn, storage == kF32 || many ? 2 : 4, lpn, cpl);
+}
+
+int pick_vis_bits(int storage, int cpl, int ef_need, int deg, int64_t n, int64_t nq, int cus,
+                  int base) {
+  // resident waves of a CU: what the registers of the shape leave room for,
+  // or what the batch gives it
+  const int simd = cpl >= 8 ? 2 : storage == kFP8 ? (cpl <= 2 ? 6 : 4) : cpl == 1 ? 5 : cpl == 2 ? 3 : 2;
+  const int64_t waves = std::min<int64_t>(4 * simd, (nq + cus - 1) / cus);
+  const int ef_cap = next_pow2(ef_need);
+  int bits = base;
+  for (int b = base + 1; b <= 14 && (1ll << b) <= 8ll * ef_need * deg; ++b) {
+    if ((int64_t)search_lds_per_wave(ef_cap, b, vis_tag_bytes(n, b)) * waves > 160 * 1024) break;
+    bits = b;
+  }
+  return bits;
 }
 #endif  // HENN_COMMON_PART
 

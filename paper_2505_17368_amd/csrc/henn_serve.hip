@@ -293,7 +293,9 @@ henn_status henn_server_create(const henn_index* idx, const henn_server_params* 
       }
     }
     int lpn = 0, cpl = 0;
-    pick_lanes(idx->nchunks, want_lpn, &lpn, &cpl);
+    int cus = 0;
+    HENN_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, idx->device));
+    pick_search_lanes(idx->storage, idx->nchunks, p->max_slots, cus, want_lpn, &lpn, &cpl);
     if (!lpn) throw HipError{hipErrorInvalidValue, "lanes_per_vec"};
     s->shape.lanes_per_vec = lpn;
     s->shape.chunks_per_lane = cpl;

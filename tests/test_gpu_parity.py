@@ -1147,3 +1147,21 @@ def test_register_list_equals_lds_list_at_block_edges(hn, storage, metric):
             assert np.array_equal(a_d.cpu().numpy().view(np.uint32),
                                   b_d.cpu().numpy().view(np.uint32)), (ef, kw)
     idx.free()
+
+
+def test_default_shape_does_not_change_results(hn):
+    """The default lanes and visited table follow the number of queries: the
+    first queries of batches on either side of each line get the same bits."""
+    X = wl.gauss_mix(4000, 100, 10, 0.3, 53)
+    Q = wl.gauss_mix(8300, 100, 10, 0.3, 54)
+    Qd = to_dev(Q)
+    for storage in ("f32", "bf16", "fp8"):
+        idx = hn.henn_build(to_dev(X), degree=8, storage=storage)
+        ref_i, ref_d = hn.henn_search_batch(idx, Qd[:1], k=10, ef=40)
+        for nq in (257, 3072, 3073, 8192, 8193):
+            i, d = hn.henn_search_batch(idx, Qd[:nq], k=10, ef=40)
+            _sync()
+            assert np.array_equal(i[:1].cpu().numpy(), ref_i.cpu().numpy()), (storage, nq)
+            assert np.array_equal(d[:1].cpu().numpy().view(np.uint32),
+                                  ref_d.cpu().numpy().view(np.uint32)), (storage, nq)
+        idx.free()
