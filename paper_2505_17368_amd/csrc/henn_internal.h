@@ -343,11 +343,12 @@ void launch_decode_rows(int storage, const void* vq, const float* scale, int64_t
 void launch_adj_scale(const int32_t* adj, int64_t n, const float* scale, float* out,
                       hipStream_t st);
 
-// kNN graph of one layer: FP32 MFMA Gram shortlist + exact re-rank + exact
+// kNN graph of one layer: MFMA Gram shortlist + exact re-rank + exact
 // fallback for rows whose shortlist cannot be proven to hold the top R.
 // Returns the number of fallback rows.
-// gram: 0 = split-BF16 matrix-core tiles (d <= 128), 1 = FP32 tiles; the
-// graph is the same exact kNN graph either way
+// gram: 0 = FP16 matrix-core tiles, then split-BF16 (d <= 128) and FP32 ones
+// for the rows those leave unproven, 1 = FP32 tiles; the graph is the same
+// exact kNN graph either way
 int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, int metric, int R,
                         int lpn, int cpl, int32_t* adj, int gram, hipStream_t st);
 

@@ -2,9 +2,11 @@
 // "knn" graph of App. G.4): every member's R nearest other members in
 // (distance, id) order.
 //
-// Three steps:
-//  1. k_gram_topk / k_knn_gram_wide (MFMA): all-pairs Gram tiles on FP32
-//     matrix cores (the wide form streams K in slices for d > 128).  A
+// Three steps (build_knn_graph gives the order of the Gram forms):
+//  1. All-pairs Gram tiles on matrix cores leave a shortlist per row:
+//     k_gram_topk_h / k_knn_gram_wide_h from one FP16 product a coordinate,
+//     k_gram_topk_x3 from split BF16, k_gram_topk / k_knn_gram_wide from FP32
+//     (the wide forms stream K in slices for d > 128).  In the FP32 form a
 //     workgroup owns 128 rows (4 waves x 32); candidate tiles of 32 rows are
 //     staged in LDS and multiplied with v_mfma_f32_32x32x2f32, the K split
 //     as (lane half h) x (step kk) over the two halves of each row.  Rows are
@@ -18,14 +20,18 @@
 //     proven to contain the true top R: when neither the bound with the
 //     layer's largest norm nor (L2) the bound relative to each candidate's
 //     own distance puts every left-out candidate beyond the R-th exact
-//     distance.
-//  3. k_knn_exact: the exact brute force for those rows.
+//     distance.  Such rows go through the next, more exact Gram form on a
+//     gathered row list.
+//  3. k_knn_exact: the exact brute force for rows that no form proves.
 #include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
 
+#include <string.h>
+
 #include <algorithm>
 #include <chrono>
+#include <memory>
 
 #include "henn_device.h"
 #include "henn_internal.h"
@@ -57,14 +63,17 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // value beats the current KS-th.  Output: per (row, lane half) the KS
 // smallest (value, candidate index) pairs, ascending.
 // row_list: when given, the block's rows are row_list[i] for i < n_rows
-// (the rows the split form could not prove) and the shortlists go to
+// (the rows another form could not prove) and the shortlists go to
 // position i; otherwise rows 0 .. size - 1 in order (n_rows = size).
+// blockIdx.y: the split of the candidates this block takes (split_rows of
+// them, a multiple of the tile); row i's shortlist of split y is number
+// i * gridDim.y + y.
 template <int KH, int KS>
 __global__ __launch_bounds__(256, 2) void k_gram_topk(const float* vec, int64_t size, int dpad,
                                                       const float* norms, const float* mean,
                                                       int metric, float* sl_d, int32_t* sl_i,
                                                       int64_t block0, const int32_t* row_list,
-                                                      int64_t n_rows) {
+                                                      int64_t n_rows, int64_t split_rows) {
   // two LDS buffers of [kTileC][2 * KH + 4] candidates + their norms; the
   // next tile is fetched into registers while the current one is multiplied
   extern __shared__ __align__(16) float tile[];
@@ -75,7 +84,8 @@ __global__ __launch_bounds__(256, 2) void k_gram_topk(const float* vec, int64_t 
   const int64_t qi = (block0 + blockIdx.x) * 128 + wave * 32 + qc;
   const bool qvalid = qi < n_rows;
   const int64_t qrow = !qvalid ? -1 : row_list ? (int64_t)row_list[qi] : qi;
-  const int64_t cb = 0, ce = size;
+  const int64_t cb = min((int64_t)blockIdx.y * split_rows, size);
+  const int64_t ce = min(cb + split_rows, size);
   const bool l2 = metric == 0;
   const float qscale = l2 ? -2.0f : -1.0f;
 
@@ -227,7 +237,7 @@ __global__ __launch_bounds__(256, 2) void k_gram_topk(const float* vec, int64_t 
     cur ^= 1;
   }
   if (qvalid) {
-    const int64_t o = qi * (2 * KS) + h * KS;
+    const int64_t o = (qi * gridDim.y + blockIdx.y) * (2 * KS) + h * KS;
 #pragma unroll
     for (int j = 0; j < KS; ++j) {
       sl_d[o + j] = td[j];
@@ -237,8 +247,8 @@ __global__ __launch_bounds__(256, 2) void k_gram_topk(const float* vec, int64_t 
 }
 
 // ------------------------------------------------------------------------
-// The same shortlist on BF16 matrix cores with split operands (the default
-// build for d <= 128).  Each centred row x' = fl(x - mean) is stored once as
+// The same shortlist on BF16 matrix cores with split operands (d <= 128, the
+// rows that the FP16 form further down could not prove).  Each centred row x' = fl(x - mean) is stored once as
 // hi = bf16(x') and lo = bf16(x' - hi) (k_split_rows), and every product is
 // taken as y_h b_h + y_h b_l + y_l b_h, three v_mfma_f32_32x32x16_bf16 per
 // 16 coordinates, each product exact in FP32.  Error of one Gram value G
@@ -315,7 +325,8 @@ template <int S, int KS>
 __global__ __launch_bounds__(256, 2) void k_gram_topk_x3(const uint16_t* rows, int64_t size,
                                                          const float* norms, const float* tnorms,
                                                          int metric, float* sl_d, int32_t* sl_i,
-                                                         int64_t block0) {
+                                                         int64_t block0, const int32_t* row_list,
+                                                         int64_t n_rows, int64_t split_rows) {
   constexpr int KP = 16 * S;
   constexpr int kHalfU4 = KP / 8;           // uint4 per half row
   constexpr int kRowU4 = 2 * kHalfU4 + 1;   // staged row: hi, lo, pad
@@ -333,8 +344,9 @@ __global__ __launch_bounds__(256, 2) void k_gram_topk_x3(const uint16_t* rows, i
   __shared__ uint2 cand_all[4 * 64 * kX3Cand];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int qc = lane & 31, h = lane >> 5;
-  const int64_t qrow = (block0 + blockIdx.x) * 128 + wave * 32 + qc;
-  const bool qvalid = qrow < size;
+  const int64_t qi = (block0 + blockIdx.x) * 128 + wave * 32 + qc;
+  const bool qvalid = qi < n_rows;
+  const int64_t qrow = !qvalid ? -1 : row_list ? (int64_t)row_list[qi] : qi;
   const bool l2 = metric == 0;
 
   // the row operand: coordinates 16 s + 8 h .. + 8 of row qc, hi and lo,
@@ -481,18 +493,19 @@ __global__ __launch_bounds__(256, 2) void k_gram_topk_x3(const uint16_t* rows, i
   };
 
   // every wave of the block walks the same tiles (the barriers need all of
-  // them); the padded layer holds nt whole tiles
-  const int64_t nt = (size + kTileC - 1) / kTileC;
-  issue(0, buf0);
-  if (nt > 1) issue(kTileC, buf1);
+  // them); the padded layer holds whole tiles, and every split at least one
+  const int64_t cb = (int64_t)blockIdx.y * split_rows;
+  const int64_t nt = (min(cb + split_rows, size) - cb + kTileC - 1) / kTileC;
+  issue(cb, buf0);
+  if (nt > 1) issue(cb + kTileC, buf1);
   for (int64_t t = 0; t < nt; t += 3) {
 #define HENN_X3_STEP(I, CUR, NEXT2)                                                      \
   {                                                                                      \
     const int64_t tt_ = t + (I);                                                         \
     wait_copies(tt_ + 1 < nt ? per_tile : 0);                                            \
     lds_barrier();                                                                       \
-    if (tt_ + 2 < nt) issue((tt_ + 2) * kTileC, NEXT2);                                  \
-    body(tt_ * kTileC, CUR);                                                             \
+    if (tt_ + 2 < nt) issue(cb + (tt_ + 2) * kTileC, NEXT2);                             \
+    body(cb + tt_ * kTileC, CUR);                                                             \
   }
     HENN_X3_STEP(0, buf0, buf2)
     if (t + 1 >= nt) break;
@@ -503,11 +516,398 @@ __global__ __launch_bounds__(256, 2) void k_gram_topk_x3(const uint16_t* rows, i
   }
   merge();
   if (qvalid) {
-    const int64_t o = qrow * (2 * KS) + h * KS;
+    const int64_t o = (qi * gridDim.y + blockIdx.y) * (2 * KS) + h * KS;
 #pragma unroll
     for (int j = 0; j < KS; ++j) {
       sl_d[o + j] = td[j];
       sl_i[o + j] = ti[j];
+    }
+  }
+}
+
+// ------------------------------------------------------------------------
+// The shortlist from one FP16 product per coordinate (the default's first
+// pass, any d).  A third of the split form's matrix work; its wider error
+// bound proves most rows, and the rest take the split form (d <= 128) or the
+// FP32 tiles on a gathered row list.
+//
+// Each centred row x' is stored as fp16(s x'), s the power of two that takes
+// the layer's largest norm to 2^14 (subnormal results flushed to zero), and
+// the residual norm r_x = |x' - fp16(s x') / s| with it.  With G the value
+// assembled from the products (in units of s^2) and D the canonical distance,
+//   |G / s^2 - D| <= m (r_x |y'| + |x'| r_y + r_x r_y) + c (|x'|^2 + |y'|^2),
+// m = 2 (L2) or 1 (IP), by Cauchy-Schwarz on the dropped terms; c covers the
+// FP32 accumulation, the norms, the centring and the canonical distance's own
+// rounding as in the split form.  The residuals are the actual ones, so a
+// coordinate that FP16 cannot hold only widens the bound.
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+
+// What k_half_rows leaves of a layer: the largest residual norm and the
+// largest ratio of a row's residual to its norm, as float bits.
+struct HalfStats {
+  uint32_t rmax, ratio;
+};
+
+// One wave a row: rows [size_pad][kp] FP16, zero past dpad and for the
+// padding rows; yterm [size_pad]: s^2 |y'|^2 (L2) or 0 (IP), +inf for the
+// padding rows; rres [size]: the residual norms.
+__global__ __launch_bounds__(256) void k_half_rows(const float* vec, const float* mean,
+                                                   const float* norms, int metric, int64_t size,
+                                                   int64_t size_pad, int dpad, int kp, float s,
+                                                   uint16_t* out, float* yterm, float* rres,
+                                                   HalfStats* stats) {
+  const int lane = lane_id();
+  const float inv = 1.0f / s;  // a power of two: exact
+  float rm = 0.0f, ra = 0.0f;
+  for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < size_pad;
+       r += (int64_t)gridDim.x * 4) {
+    float r2 = 0.0f;
+    for (int c = lane; c < kp; c += 64) {
+      const float v =
+          (r < size && c < dpad) ? vec[r * dpad + c] - (mean ? mean[c] : 0.0f) : 0.0f;
+      const float sv = v * s;
+      const _Float16 hv = fabsf(sv) < 0x1p-14f ? (_Float16)0.0f : (_Float16)sv;
+      out[r * kp + c] = __builtin_bit_cast(uint16_t, hv);
+      const float d = v - (float)hv * inv;
+      r2 = __builtin_fmaf(d, d, r2);
+    }
+    for (int m = 32; m > 0; m >>= 1) r2 += __shfl_xor(r2, m);
+    const float n = r < size ? norms[r] : 0.0f;
+    const float res = sqrtf(r2);
+    if (lane == 0) {
+      yterm[r] = r < size ? (metric == 0 ? n * s * s : 0.0f) : INFINITY;
+      if (r < size) rres[r] = res;
+    }
+    if (res <= 3.0e38f) rm = fmaxf(rm, res);
+    if (n > 0.0f && n <= 3.0e38f) ra = fmaxf(ra, res / sqrtf(n));
+  }
+  // few waves raise the maxima: a look at the current value (which only
+  // grows) saves thousands of atomics on two words
+  if (lane == 0) {
+    const uint32_t rb = __float_as_uint(rm), ab = __float_as_uint(ra);
+    if (rb > __hip_atomic_load(&stats->rmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(&stats->rmax, rb);
+    if (ab > __hip_atomic_load(&stats->ratio, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(&stats->ratio, ab);
+  }
+}
+
+// A lane's sorted shortlist and its staged candidates, shared by the FP16
+// kernels: values below the list's last entry are staged in LDS (slot i of
+// lane l at i * 64 + l) and merged a slot at a time for all lanes.
+template <int KS>
+struct LaneList {
+  float d[KS];
+  int32_t i[KS];
+  int n = 0;  // staged
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int j = 0; j < KS; ++j) {
+      d[j] = INFINITY;
+      i[j] = -1;
+    }
+  }
+  // self: the row itself, dropped here
+  __device__ __forceinline__ void merge(const uint2* cand, int lane, int64_t self) {
+    int m = n;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) m = max(m, __shfl_xor(m, o));
+    m = __builtin_amdgcn_readfirstlane(m);
+    for (int k = 0; k < m; ++k) {
+      const uint2 e = cand[k * 64 + lane];
+      float nd = (k < n && (int64_t)e.y != self) ? __uint_as_float(e.x) : INFINITY;
+      if (__builtin_amdgcn_ballot_w64(nd < d[KS - 1])) {
+        int32_t ni = (int32_t)e.y;
+#pragma unroll
+        for (int j = 0; j < KS; ++j) {
+          const bool sw = nd < d[j];
+          const float od = d[j];
+          const int32_t oi = i[j];
+          d[j] = sw ? nd : od;
+          i[j] = sw ? ni : oi;
+          nd = sw ? od : nd;
+          ni = sw ? oi : ni;
+        }
+      }
+    }
+    n = 0;
+  }
+  // one 32-candidate block's values (acc[v]: candidate c0 + 8 (v >> 2) +
+  // 4 h + (v & 3)); most blocks hold nothing for any lane
+  __device__ __forceinline__ void offer(const floatx16& acc, uint32_t c0, int h, uint2* cand, int lane,
+                        int64_t self) {
+    float lo = acc[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) lo = fminf(lo, acc[v]);
+    if (!__builtin_amdgcn_ballot_w64(lo < d[KS - 1])) return;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      if (__builtin_amdgcn_ballot_w64(n > kX3Cand - 4)) merge(cand, lane, self);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (acc[4 * g + u] < d[KS - 1]) {
+          cand[n * 64 + lane] = make_uint2(__float_as_uint(acc[4 * g + u]), c0 + 8 * g + 4 * h + u);
+          ++n;
+        }
+      }
+    }
+  }
+};
+
+// d <= 128.  500,000 x 128: layer 0 in 115.7 ms (553 TFLOP/s of distance work)
+// against 193 ms for the split form; what is left above the products is the
+// staging of values that enter a list and the LDS reads.
+// A block takes 128 rows (32 a wave, their operand in registers) and streams its split of the layer through LDS in steps of 64 candidates,
+// copied by global_load_lds into a ring of three buffers (see
+// k_gram_topk_x3).  The accumulators start at the candidates' norm terms, read
+// from LDS straight into them; the row's own norm is added when the list is
+// written, so a step's arithmetic besides the products is one minimum over
+// the values and one compare.  Two independent 32-candidate accumulators
+// keep the products from waiting on each other.
+constexpr int kHalfStep = 64;
+
+template <int S, int KS>
+__global__ __launch_bounds__(256, 2) void k_gram_topk_h(const uint16_t* rows, int64_t size,
+                                                        const float* norms, const float* yterm,
+                                                        int metric, float s2, float* sl_d,
+                                                        int32_t* sl_i, int64_t block0,
+                                                        int64_t split_rows) {
+  constexpr int kRowU4 = 2 * S + 1;                         // staged row: 2 S chunks, one pad
+  constexpr int kJ = (kHalfStep * kRowU4 + 63) / 64;        // copy instructions a step
+  constexpr int kSlots = 64 * kJ;
+  constexpr int kBufU4 = kSlots + kHalfStep / 4;            // slots, then the norm terms
+  constexpr int kMaxJ = (kJ + 3) / 4;
+  static_assert(kMaxJ <= 5, "the waits below count at most six copies per wave and step");
+  __shared__ uint4 buf0[kBufU4], buf1[kBufU4], buf2[kBufU4];
+  __shared__ uint2 cand_all[4 * 64 * kX3Cand];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int qc = lane & 31, h = lane >> 5;
+  const int64_t qrow = (block0 + blockIdx.x) * 128 + wave * 32 + qc;
+  const bool qvalid = qrow < size;
+  const bool l2 = metric == 0;
+
+  // the row operand, coordinates 16 s + 8 h .. + 8, times -2 (L2) or -1 (IP):
+  // exact (the stored values are normal and at most 2^14)
+  half8 bq[S];
+  {
+    const half8* qr = reinterpret_cast<const half8*>(rows + (qvalid ? qrow : 0) * (16 * S));
+    const _Float16 f = qvalid ? (l2 ? (_Float16)-2.0f : (_Float16)-1.0f) : (_Float16)0.0f;
+#pragma unroll
+    for (int k = 0; k < S; ++k) bq[k] = qr[2 * k + h] * f;
+  }
+  const float qn = (l2 && qvalid) ? norms[qrow] * s2 : 0.0f;
+
+  LaneList<KS> list;
+  list.clear();
+  uint2* cand = cand_all + wave * (kX3Cand * 64);
+
+  int off0 = 0, off1 = 0, off2 = 0, off3 = 0, off4 = 0;
+#define HENN_H_OFF(U)                                                                    \
+  if constexpr (U < kMaxJ) {                                                             \
+    const int p_ = 64 * (wave + 4 * U) + lane, r_ = p_ / kRowU4, c_ = p_ - r_ * kRowU4;  \
+    off##U = min(r_, kHalfStep - 1) * 2 * S +                                            \
+             ((p_ < kHalfStep * kRowU4 && c_ < 2 * S) ? c_ : 0);                         \
+  }
+  HENN_H_OFF(0) HENN_H_OFF(1) HENN_H_OFF(2) HENN_H_OFF(3) HENN_H_OFF(4)
+#undef HENN_H_OFF
+  const int per_step = (kJ - wave + 3) / 4 + 1;  // this wave's copies per step, norms included
+  typedef __attribute__((address_space(3))) void* lds_ptr;
+  auto issue = [&](int64_t c0, uint4* tile) {
+    const uint4* src = reinterpret_cast<const uint4*>(rows + c0 * (16 * S));
+#define HENN_H_COPY(U)                                                                   \
+  if constexpr (U < kMaxJ)                                                               \
+    if (wave + 4 * U < kJ)                                                               \
+      __builtin_amdgcn_global_load_lds(src + off##U, (lds_ptr)(tile + 64 * (wave + 4 * U)), \
+                                       16, 0, 0);
+    HENN_H_COPY(0) HENN_H_COPY(1) HENN_H_COPY(2) HENN_H_COPY(3) HENN_H_COPY(4)
+#undef HENN_H_COPY
+    if (lane < 16)
+      __builtin_amdgcn_global_load_lds(
+          yterm + c0 + 16 * wave + lane,
+          (lds_ptr)(reinterpret_cast<float*>(tile + kSlots) + 16 * wave), 4, 0, 0);
+  };
+  auto wait_copies = [](int n) {
+    switch (n) {
+      case 0: __builtin_amdgcn_s_waitcnt(0xF70); break;
+      case 1: __builtin_amdgcn_s_waitcnt(0xF71); break;
+      case 2: __builtin_amdgcn_s_waitcnt(0xF72); break;
+      case 3: __builtin_amdgcn_s_waitcnt(0xF73); break;
+      case 4: __builtin_amdgcn_s_waitcnt(0xF74); break;
+      case 5: __builtin_amdgcn_s_waitcnt(0xF75); break;
+      default: __builtin_amdgcn_s_waitcnt(0xF76); break;
+    }
+  };
+  auto lds_barrier = []() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+  auto body = [&](int64_t c0, const uint4* buf) {
+    const float4* tn = reinterpret_cast<const float4*>(buf + kSlots);
+    floatx16 acc0, acc1;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 a = tn[2 * g + h], b = tn[8 + 2 * g + h];
+      acc0[4 * g + 0] = a.x; acc0[4 * g + 1] = a.y; acc0[4 * g + 2] = a.z; acc0[4 * g + 3] = a.w;
+      acc1[4 * g + 0] = b.x; acc1[4 * g + 1] = b.y; acc1[4 * g + 2] = b.z; acc1[4 * g + 3] = b.w;
+    }
+    const uint4* arow = buf + qc * kRowU4 + h;
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+      const half8 a0 = __builtin_bit_cast(half8, arow[2 * k]);
+      const half8 a1 = __builtin_bit_cast(half8, arow[32 * kRowU4 + 2 * k]);
+      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, bq[k], acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, bq[k], acc1, 0, 0, 0);
+    }
+    list.offer(acc0, (uint32_t)c0, h, cand, lane, qrow);
+    list.offer(acc1, (uint32_t)c0 + 32, h, cand, lane, qrow);
+  };
+
+  const int64_t cb = (int64_t)blockIdx.y * split_rows;
+  const int64_t nt = (min(cb + split_rows, size) - cb + kHalfStep - 1) / kHalfStep;
+  issue(cb, buf0);
+  if (nt > 1) issue(cb + kHalfStep, buf1);
+  for (int64_t t = 0; t < nt; t += 3) {
+#define HENN_H_STEP(I, CUR, NEXT2)                                                       \
+  {                                                                                      \
+    const int64_t tt_ = t + (I);                                                         \
+    wait_copies(tt_ + 1 < nt ? per_step : 0);                                            \
+    lds_barrier();                                                                       \
+    if (tt_ + 2 < nt) issue(cb + (tt_ + 2) * kHalfStep, NEXT2);                          \
+    body(cb + tt_ * kHalfStep, CUR);                                                     \
+  }
+    HENN_H_STEP(0, buf0, buf2)
+    if (t + 1 >= nt) break;
+    HENN_H_STEP(1, buf1, buf0)
+    if (t + 2 >= nt) break;
+    HENN_H_STEP(2, buf2, buf1)
+#undef HENN_H_STEP
+  }
+  list.merge(cand, lane, qrow);
+  if (qvalid) {
+    const int64_t o = (qrow * gridDim.y + blockIdx.y) * (2 * KS) + h * KS;
+#pragma unroll
+    for (int j = 0; j < KS; ++j) {
+      sl_d[o + j] = list.d[j] + qn;
+      sl_i[o + j] = list.i[j];
+    }
+  }
+}
+
+// d > 128: GEMM-shaped.  60,000 x 768: layer 0 in 12.4 ms (446 TFLOP/s)
+// against 65 ms for the FP32 tiles.  A block owns 128 rows (32 a wave) and walks its
+// split of the layer in tiles of 128 candidates; the K dimension streams
+// through LDS in slices of 64 coordinates of both operands, copied by
+// global_load_lds into two buffers, one slice ahead.  Each wave multiplies
+// its 32 rows against four 32-candidate blocks.  rows are [size_pad][kp] with
+// kp a multiple of 64 and size_pad of 128.  A staged row slice is its eight
+// chunks, chunk c in slot c ^ (row & 7), so that eight rows' reads of one
+// chunk fall on different banks without a pad: the two buffers and the staged
+// candidates are exactly half of a CU's LDS.
+constexpr int kWideHRow = 8;
+constexpr int kWideHSlots = 128 * kWideHRow;  // one operand slice, a multiple of 64
+
+__global__ __launch_bounds__(256, 2) void k_knn_gram_wide_h(const uint16_t* rows, int64_t size,
+                                                            int kp, const float* norms,
+                                                            const float* yterm, int metric,
+                                                            float s2, float* sl_d, int32_t* sl_i,
+                                                            int64_t block0, int64_t split_rows) {
+  constexpr int kCopies = 2 * kWideHSlots / 64;  // instructions a slice, a quarter a wave
+  static_assert(kCopies % 4 == 0, "the same number for every wave");
+  __shared__ uint4 buf0[2 * kWideHSlots], buf1[2 * kWideHSlots];
+  __shared__ uint2 cand_all[4 * 64 * kX3Cand];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int qc = lane & 31, h = lane >> 5;
+  const int64_t qbase = (block0 + blockIdx.x) * 128;
+  const int64_t qrow = qbase + wave * 32 + qc;
+  const bool qvalid = qrow < size;
+  const bool l2 = metric == 0;
+  const _Float16 f = l2 ? (_Float16)-2.0f : (_Float16)-1.0f;
+  const float qn = (l2 && qvalid) ? norms[qrow] * s2 : 0.0f;
+  LaneList<kShort> list;
+  list.clear();
+  uint2* cand = cand_all + wave * (kX3Cand * 64);
+
+  typedef __attribute__((address_space(3))) void* lds_ptr;
+  const uint4* base = reinterpret_cast<const uint4*>(rows);
+  const int row_u4 = kp / 8;
+  auto issue = [&](int64_t c0, int ks, uint4* buf) {
+#pragma unroll
+    for (int u = 0; u < kCopies / 4; ++u) {
+      const int j = wave + 4 * u;
+      const int p = 64 * j + lane;
+      const bool own = p >= kWideHSlots;
+      const int pp = own ? p - kWideHSlots : p;
+      const int r = pp / kWideHRow, c = (pp ^ r) & 7;
+      const int64_t row = (own ? qbase : c0) + r;
+      __builtin_amdgcn_global_load_lds(base + row * row_u4 + 8 * ks + c, (lds_ptr)(buf + 64 * j),
+                                       16, 0, 0);
+    }
+  };
+  auto slice_barrier = []() {
+    // this wave's copies and LDS reads are done; the barrier covers the others
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  };
+  floatx16 acc[4];
+  auto multiply = [&](const uint4* buf) {
+    const uint4* brow = buf + kWideHSlots + (wave * 32 + qc) * kWideHRow;
+    const uint4* arow = buf + qc * kWideHRow;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int c = (2 * k + h) ^ (qc & 7);
+      const half8 b = __builtin_bit_cast(half8, brow[c]) * f;  // a power of two: exact
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const half8 a = __builtin_bit_cast(half8, arow[32 * q * kWideHRow + c]);
+        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, acc[q], 0, 0, 0);
+      }
+    }
+  };
+  const int nsl = kp / 64;
+  const int64_t cb = (int64_t)blockIdx.y * split_rows;
+  const int64_t ce = min(cb + split_rows, size);
+  int64_t c0 = cb;
+  int ks = 0;
+  // one slice of the walk: the next slice's copies go out first
+  auto step = [&](const uint4* cur, uint4* nxt) {
+    const bool last = ks + 1 == nsl;
+    const int64_t nc0 = last ? c0 + 128 : c0;
+    if (nc0 < ce) issue(nc0, last ? 0 : ks + 1, nxt);
+    if (ks == 0) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4* tn = reinterpret_cast<const float4*>(yterm + c0 + 32 * q);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const float4 y = tn[2 * g + h];
+          acc[q][4 * g + 0] = y.x; acc[q][4 * g + 1] = y.y;
+          acc[q][4 * g + 2] = y.z; acc[q][4 * g + 3] = y.w;
+        }
+      }
+    }
+    multiply(cur);
+    if (last) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        list.offer(acc[q], (uint32_t)c0 + 32 * q, h, cand, lane, qrow);
+    }
+    ks = last ? 0 : ks + 1;
+    c0 = nc0;
+  };
+  issue(cb, 0, buf0);
+  slice_barrier();
+  while (c0 < ce) {
+    step(buf0, buf1);
+    slice_barrier();
+    if (c0 >= ce) break;
+    step(buf1, buf0);
+    slice_barrier();
+  }
+  list.merge(cand, lane, qrow);
+  if (qvalid) {
+    const int64_t o = (qrow * gridDim.y + blockIdx.y) * (2 * kShort) + h * kShort;
+#pragma unroll
+    for (int j = 0; j < kShort; ++j) {
+      sl_d[o + j] = list.d[j] + qn;
+      sl_i[o + j] = list.i[j];
     }
   }
 }
@@ -532,7 +932,8 @@ __global__ __launch_bounds__(256) void k_knn_gram_wide(const float* vec, int64_t
                                                           int dpad, const float* mean,
                                                           const float* norms, int metric,
                                                           float* sl_d, int32_t* sl_i,
-                                                          int64_t block0) {
+                                                          int64_t block0, const int32_t* row_list,
+                                                          int64_t n_rows, int64_t split_rows) {
   extern __shared__ __align__(16) float lds[];
   constexpr int kHalf = kWideC * kSStride;  // one operand slice
   constexpr int kBuf = 2 * kHalf;           // candidate slice + row slice
@@ -540,8 +941,11 @@ __global__ __launch_bounds__(256) void k_knn_gram_wide(const float* vec, int64_t
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int qc = lane & 31, h = lane >> 5;
   const int64_t qbase = (block0 + blockIdx.x) * 128;
-  const int64_t qrow = qbase + wave * 32 + qc;
-  const bool qvalid = qrow < size;
+  const int64_t qi = qbase + wave * 32 + qc;
+  const bool qvalid = qi < n_rows;
+  const int64_t qrow = !qvalid ? -1 : row_list ? (int64_t)row_list[qi] : qi;
+  const int64_t cb = min((int64_t)blockIdx.y * split_rows, size);
+  const int64_t ce = min(cb + split_rows, size);
   const bool l2 = metric == 0;
   const float qscale = l2 ? -2.0f : -1.0f;
   const float b_extra = h == 0 ? 1.0f : (l2 && qvalid ? norms[qrow] : 0.0f);
@@ -565,13 +969,20 @@ __global__ __launch_bounds__(256) void k_knn_gram_wide(const float* vec, int64_t
   const int lrow = threadIdx.x / kF4Row, lc4 = threadIdx.x % kF4Row;
   const int nsl = (dpad + kSlice - 1) / kSlice;
   float4 pre[2 * kPass];
+  // the block's rows this thread stages (clamped to a valid one)
+  int32_t brow[kPass];
+#pragma unroll
+  for (int u = 0; u < kPass; ++u) {
+    const int64_t i = min(qbase + lrow + kRowsPerPass * u, n_rows - 1);
+    brow[u] = row_list ? row_list[i] : (int32_t)i;
+  }
   auto fetch = [&](int64_t c0, int ks) {
     const int col = ks * kSlice + 4 * lc4;
     const int colc = col < dpad ? col : 0;
 #pragma unroll
     for (int u = 0; u < 2 * kPass; ++u) {
-      const int64_t base = u < kPass ? c0 : qbase;
-      const int64_t row = min(base + lrow + kRowsPerPass * (u % kPass), size - 1);
+      const int64_t row =
+          u < kPass ? min(c0 + lrow + kRowsPerPass * u, size - 1) : (int64_t)brow[u % kPass];
       pre[u] = *reinterpret_cast<const float4*>(vec + row * dpad + colc);
     }
   };
@@ -597,17 +1008,17 @@ __global__ __launch_bounds__(256) void k_knn_gram_wide(const float* vec, int64_t
     for (int b = 0; b < 4; ++b) {
       const int64_t row = c0 + 32 * b + qc;
       const float nv = norms[min(row, size - 1)];
-      cn[b] = row < size ? (l2 ? nv : 0.0f) : INFINITY;
+      cn[b] = row < ce ? (l2 ? nv : 0.0f) : INFINITY;
     }
   };
 
   __syncthreads();
-  fetch(0, 0);
+  fetch(cb, 0);
   stash(lds, 0);
   __syncthreads();
 
   int cur = 0;
-  for (int64_t c0 = 0; c0 < size; c0 += kWideC) {
+  for (int64_t c0 = cb; c0 < ce; c0 += kWideC) {
     float cn[4];
     tile_norms(c0, cn);
     floatx16 acc[4];
@@ -621,7 +1032,7 @@ __global__ __launch_bounds__(256) void k_knn_gram_wide(const float* vec, int64_t
       const bool last = ks + 1 == nsl;
       const int nks = last ? 0 : ks + 1;
       const int64_t nc0 = last ? c0 + kWideC : c0;
-      const bool more = nc0 < size;
+      const bool more = nc0 < ce;
       if (more) fetch(nc0, nks);
 
       const float* buf = lds + cur * kBuf;
@@ -687,8 +1098,9 @@ __global__ __launch_bounds__(256) void k_knn_gram_wide(const float* vec, int64_t
     }
   }
   if (qvalid) {
-    float* od = sl_d + qrow * (2 * kShort) + h * kShort;
-    int32_t* oi = sl_i + qrow * (2 * kShort) + h * kShort;
+    const int64_t o = (qi * gridDim.y + blockIdx.y) * (2 * kShort) + h * kShort;
+    float* od = sl_d + o;
+    int32_t* oi = sl_i + o;
 #pragma unroll
     for (int j = 0; j < kShort; ++j) {
       od[j] = td[j];
@@ -711,52 +1123,100 @@ __device__ inline uint64_t wave_sort64(uint64_t key) {
   return key;
 }
 
+// The error bound of the shortlists' Gram values against the canonical
+// distance D: |gscale G - D| <= mult (r_x |y'| + |x'| r_y + r_x r_y) +
+// coef (|x'|^2 + |y'|^2), the first term with the residual norms rres of the
+// FP16 rows (nullptr: none); coef_rel bounds it by the squared norms alone.
+struct GramErr {
+  const float* rres;
+  float mult, rmax, nmax, coef, coef_rel, gscale;
+};
+
+// One wave a row: the canonical distances of its shortlists (one of 64
+// entries per split), the R nearest of them, and the proof that nothing left
+// out belongs among them.  With several splits, an entry whose Gram value
+// already puts it beyond the R-th of those seen is not evaluated.
 template <int LPN, int CPL>
 __global__ __launch_bounds__(256) void k_knn_rerank(const float* vec, int64_t size, int dpad,
                                                     int nchunks, int metric, const float* sl_d,
-                                                    const int32_t* sl_i, const float* norms,
-                                                    float nmax, float coef, int R, int32_t* adj,
-                                                    int32_t* fb_rows, uint32_t* fb_count,
-                                                    const int32_t* row_list, int64_t n_rows) {
+                                                    const int32_t* sl_i, int splits,
+                                                    const float* norms, GramErr err, int R,
+                                                    int32_t* adj, int32_t* fb_rows,
+                                                    uint32_t* fb_count, const int32_t* row_list,
+                                                    int64_t row0, int64_t n_rows) {
   constexpr int G = 64 / LPN;
   __shared__ uint64_t keys[4][64];
+  __shared__ int32_t cids[4][64];
   const int wave = threadIdx.x >> 6;
   // shortlist i belongs to row row_list[i] (or row i)
-  const int64_t li = (int64_t)blockIdx.x * 4 + wave;
-  if (li >= n_rows) return;
+  const int64_t li = row0 + (int64_t)blockIdx.x * 4 + wave;
+  if (li >= row0 + n_rows) return;
   const int64_t row = row_list ? (int64_t)row_list[li] : li;
   const int lane = lane_id(), t = lane % LPN, g = lane / LPN;
   float q[CPL][8];
   load_query<CPL>(vec + row * dpad, dpad, t, q);
-  for (int base = 0; base < 2 * kShort; base += G) {
-    const int ci = base + g;
-    const int32_t id = sl_i[li * (2 * kShort) + ci];
-    const bool valid = id >= 0;
-    const float dist = group_distance<kF32, LPN, CPL>(q, vec + (int64_t)(valid ? id : 0) * dpad,
-                                                      1.0f, t, nchunks, metric, valid);
-    if (t == 0) keys[wave][ci] = valid ? dkey(dist, id) : ~0ull;
+  const float nrow = norms[row];
+  // the bound with the layer's largest norm and residual; the factors leave
+  // room for the rounding of these few operations
+  float delta = err.coef * (nrow + err.nmax);
+  if (err.rres) {
+    const float rx = err.rres[row];
+    delta += 1.002f * err.mult *
+             (rx * sqrtf(err.nmax) + sqrtf(nrow) * err.rmax + rx * err.rmax);
   }
-  wave_sync();
-  const uint64_t key = wave_sort64(keys[wave][lane]);
+  float cut = INFINITY;
+  uint64_t best = ~0ull;
+  for (int sp = 0; sp < splits; ++sp) {
+    const int64_t o = (li * splits + sp) * (2 * kShort);
+    const float gv = sl_d[o + lane] * err.gscale;
+    cut = fminf(cut, fminf(__shfl(gv, kShort - 1), __shfl(gv, 2 * kShort - 1)));
+    const int32_t id = sl_i[o + lane];
+    const uint64_t kr = shfl_u64(best, R - 1);
+    const float rth = kr == ~0ull ? INFINITY : from_ordered((uint32_t)(kr >> 32));
+    const uint64_t take = ballot(id >= 0 && !(gv - delta > rth));
+    const int cnt = popc64(take);
+    if (cnt == 0) continue;
+    if (id >= 0 && !(gv - delta > rth)) cids[wave][rank_below(take)] = id;
+    if (lane >= cnt) keys[wave][lane] = ~0ull;
+    wave_sync();
+    for (int base = 0; base < cnt; base += G) {
+      const int ci = base + g;
+      const bool valid = ci < cnt;
+      const int32_t c = cids[wave][valid ? ci : 0];
+      const float dist = group_distance<kF32, LPN, CPL>(q, vec + (int64_t)c * dpad, 1.0f, t,
+                                                        nchunks, metric, valid);
+      if (t == 0 && valid) keys[wave][ci] = dkey(dist, c);
+    }
+    wave_sync();
+    uint64_t m = wave_sort64(keys[wave][lane]);
+    if (sp > 0) {
+      // the lowest 64 of the running list and these, sorted (half-cleaner)
+      const uint64_t rc = shfl_u64(m, 63 - lane);
+      m = rc < best ? rc : best;
+      for (int stride = 32; stride > 0; stride >>= 1) {
+        const uint64_t ot = shfl_xor_u64(m, stride);
+        const bool lower = (lane & stride) == 0;
+        m = lower ? (ot < m ? ot : m) : (ot < m ? m : ot);
+      }
+    }
+    best = m;
+    wave_sync();
+  }
+  const uint64_t key = best;
   if (lane < R) adj[row * R + lane] = key == ~0ull ? -1 : (int32_t)(uint32_t)key;
-  const float cut =
-      fminf(sl_d[li * (2 * kShort) + kShort - 1], sl_d[li * (2 * kShort) + 2 * kShort - 1]);
   const uint64_t kr = shfl_u64(key, R - 1);
   if (lane == 0 && isfinite(cut)) {
-    // every candidate left out of the shortlist has a Gram value >= cut, and
-    // |G - D| <= coef (|x'|^2 + |y'|^2) for its canonical distance D
+    // every candidate left out of the shortlists has a Gram value >= cut
     const float exact_r = kr == ~0ull ? INFINITY : from_ordered((uint32_t)(kr >> 32));
-    const float nrow = norms[row];
-    // (a) with |y'|^2 <= max_y |y'|^2: D >= cut - delta
-    const float delta = coef * (nrow + nmax);
+    // (a) with the largest |y'| and r_y: D >= cut - delta
     const bool proof_a = exact_r + delta < cut - delta;
     // (b) L2 only, relative to the candidate's own distance: |y'|^2 <=
     // 2 |x'|^2 + 2 |y - x|^2, so |G - D| <= coef (3 |x'|^2 + 2.1 D) and
     // D >= (cut - 3 coef |x'|^2) / (1 + 2.1 coef); the factors 3 and 4 below
     // leave room for the rounding of this test.  Rows of small norm in
     // multi-scale data pass here where (a) charges them the layer's largest.
-    const bool proof_b =
-        metric == 0 && exact_r * (1.0f + 3.0f * coef) + 4.0f * coef * nrow < cut;
+    const float c = err.coef_rel;
+    const bool proof_b = metric == 0 && exact_r * (1.0f + 3.0f * c) + 4.0f * c * nrow < cut;
     if (!(proof_a || proof_b)) fb_rows[atomicAdd(fb_count, 1u)] = (int32_t)row;
   }
 }
@@ -1218,135 +1678,240 @@ void launch_root_gram(const float* Q, int64_t nq, int d, const RootAux& r, int d
   HENN_HIP(hipGetLastError());
 }
 
+// Gram passes a layer's rows can take, cheapest first.
+enum class Gram { kHalf, kSplit, kFp32 };
+
+// Splits of the candidates for n_rows rows: about two 256-thread blocks fit a
+// CU, so 512 run at once.  The count with the shortest makespan, (rounds of
+// 512 blocks) x (candidates of a split + the 1,024 that filling its lists
+// costs about as much as), the fewest among equals; whole 128-candidate
+// tiles.  10,000 x 32: 79 blocks on 256 CUs took 1,142 us with the split
+// form's one pass over the layer.
+static int gram_splits(int64_t n_rows, int64_t size, int64_t* split_rows) {
+  const int64_t blocks = (n_rows + 127) / 128, tiles = (size + 127) / 128;
+  const int64_t most = std::min<int64_t>({32, tiles, std::max<int64_t>(1, (1 << 21) / n_rows)});
+  int64_t splits = 1, best = -1;
+  for (int64_t sp = 1; sp <= most; ++sp) {
+    const int64_t span = (blocks * sp + 511) / 512 * ((tiles + sp - 1) / sp + 8);
+    if (best < 0 || span < best) {
+      best = span;
+      splits = sp;
+    }
+  }
+  *split_rows = (tiles + splits - 1) / splits * 128;
+  return (int)((size + *split_rows - 1) / *split_rows);
+}
+
 int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, int metric, int R,
                         int lpn, int cpl, int32_t* adj, int gram, hipStream_t st) {
   if (size <= 0) return 0;
   if (dpad > 1024) throw HipError{hipErrorInvalidValue, "kNN build supports d <= 1024"};
-  DevBuf<float> norms_buf(size), sl_d_buf(size * 2 * kShort), mean_buf(metric == 0 ? dpad : 1);
-  DevBuf<int32_t> sl_i_buf(size * 2 * kShort), fb_rows_buf(size);
+  DevBuf<float> norms_buf(size), mean_buf(metric == 0 ? dpad : 1);
+  // rows left to the next pass (two lists used in turn) and their number
+  DevBuf<int32_t> fb_a(size), fb_b(size);
   DevBuf<uint32_t> fb_count_buf(1);
-  float *norms = norms_buf.get(), *sl_d = sl_d_buf.get();
+  float* norms = norms_buf.get();
   float* mean = metric == 0 ? mean_buf.get() : nullptr;
-  int32_t *sl_i = sl_i_buf.get(), *fb_rows = fb_rows_buf.get();
   uint32_t* fb_count = fb_count_buf.get();
-  HENN_HIP(hipMemsetAsync(fb_count, 0, sizeof(uint32_t), st));
   if (metric == 0) layer_mean(vec, size, dpad, mean, st);
   launch_row_norms(vec, mean, size, dpad, norms, st);
   const float nmax = max_norm(norms, size, st);
 
   const int kh = dpad <= 32 ? 16 : dpad <= 64 ? 32 : 64;
   const bool wide = dpad > 128;
-  // the split-BF16 form for d <= 128 unless FP32 tiles are asked for
-  const bool split = !wide && gram == 0;
-  const int kp = (dpad + 15) / 16 * 16;
-  // the FP32 tiles' bound: 4 (dpad + 8) 2^-24 (|x'|^2 + max |y'|^2)
-  const float coef = split ? x3_split_coef(dpad) : 4.0f * (float)(dpad + 8) * 0x1p-24f;
-  // the split rows and their tile norms, padded to whole tiles
-  const int64_t size_pad = (size + kTileC - 1) / kTileC * kTileC;
-  DevBuf<uint16_t> split_buf(split ? size_pad * 2 * kp : 1);
-  DevBuf<float> tnorm_buf(split ? size_pad : 1);
-  if (split) {
+  const int kp = wide ? (dpad + 63) / 64 * 64 : (dpad + 15) / 16 * 16;
+  // rows and norm terms of the FP16 and split forms, padded to whole tiles
+  const int64_t size_pad = (size + 127) / 128 * 128;
+
+  // FP16 rows: the scale takes the largest norm to 2^13 .. 2^14
+  const bool half = gram == 0 && isfinite(nmax);
+  float s = 1.0f;
+  HalfStats hs{0, 0};
+  DevBuf<uint16_t> half_buf(half ? size_pad * kp : 1);
+  DevBuf<float> half_term(half ? size_pad : 1), rres(half ? size : 1);
+  if (half) {
+    if (nmax > 0.0f) {
+      int e = 0;
+      (void)frexpf(sqrtf(nmax), &e);
+      s = ldexpf(1.0f, std::max(-60, std::min(60, 14 - e)));
+    }
+    DevBuf<HalfStats> stats(1);
+    HENN_HIP(hipMemsetAsync(stats.get(), 0, sizeof(HalfStats), st));
+    const unsigned nb = (unsigned)std::min<int64_t>((size_pad + 3) / 4, 2048);
+    hipLaunchKernelGGL(k_half_rows, dim3(nb), dim3(256), 0, st, vec, mean, norms, metric, size,
+                       size_pad, dpad, kp, s, half_buf.get(), half_term.get(), rres.get(),
+                       stats.get());
+    HENN_HIP(hipGetLastError());
+    HENN_HIP(hipMemcpyAsync(&hs, stats.get(), sizeof(hs), hipMemcpyDeviceToHost, st));
+    HENN_HIP(hipStreamSynchronize(st));
+  }
+  // split BF16 rows, made when a pass first needs them
+  std::unique_ptr<DevBuf<uint16_t>> split_buf;
+  std::unique_ptr<DevBuf<float>> split_term;
+  auto need_split = [&]() {
+    if (split_buf) return;
+    split_term.reset(new DevBuf<float>(size_pad));
+    split_buf.reset(new DevBuf<uint16_t>(size_pad * 2 * kp));
     const int64_t n = size_pad * kp;
     hipLaunchKernelGGL(k_split_rows, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, vec,
-                       mean, norms, metric, size, size_pad, dpad, kp, split_buf.get(),
-                       tnorm_buf.get());
+                       mean, norms, metric, size, size_pad, dpad, kp, split_buf->get(),
+                       split_term->get());
     HENN_HIP(hipGetLastError());
-  }
-  const size_t lds = wide    ? sizeof(float) * (4 * kWideC * kSStride + dpad)
-                     : split ? 0  // static LDS
-                             : sizeof(float) * (2 * (kTileC * (2 * kh + 4) + kTileC) + dpad);
-  // FP32 Gram tiles over row blocks [b0, b0 + nbs) of the given rows
-  auto launch_fp32_gram = [&](int64_t b0, unsigned nbs, const int32_t* row_list,
-                              int64_t n_rows) {
-    const size_t lds32 = sizeof(float) * (2 * (kTileC * (2 * kh + 4) + kTileC) + dpad);
-    if (kh <= 16)
-      hipLaunchKernelGGL((k_gram_topk<16, kShort>), dim3(nbs), dim3(256), lds32, st, vec, size,
-                         dpad, norms, mean, metric, sl_d, sl_i, b0, row_list, n_rows);
-    else if (kh <= 32)
-      hipLaunchKernelGGL((k_gram_topk<32, kShort>), dim3(nbs), dim3(256), lds32, st, vec, size,
-                         dpad, norms, mean, metric, sl_d, sl_i, b0, row_list, n_rows);
-    else
-      hipLaunchKernelGGL((k_gram_topk<64, kShort>), dim3(nbs), dim3(256), lds32, st, vec, size,
-                         dpad, norms, mean, metric, sl_d, sl_i, b0, row_list, n_rows);
   };
-  const int64_t nb = (size + 127) / 128;
-  // Launch in slices of row blocks so that very large layers report progress
-  // (HENN_PROGRESS=1) between slices; each slice is a full-width Gram sweep.
-  const bool progress = getenv("HENN_PROGRESS") != nullptr;
-  const int64_t slice = std::max<int64_t>(4096, (int64_t)(2e13 / ((double)size * dpad * 256.0)));
-  auto t_last = std::chrono::steady_clock::now();
-  for (int64_t b0 = 0; b0 < nb; b0 += slice) {
-    const unsigned nbs = (unsigned)std::min<int64_t>(slice, nb - b0);
-    if (wide)
-      hipLaunchKernelGGL(k_knn_gram_wide, dim3(nbs), dim3(256), lds, st, vec, size, dpad, mean,
-                         norms, metric, sl_d, sl_i, b0);
-    else if (split) {
+
+  // Gram tiles of one form over row blocks [b0, b0 + nbs) of the rows
+  // (row_list, or all); the FP16 form takes no list
+  auto launch_gram = [&](Gram form, int64_t b0, unsigned nbs, const int32_t* row_list,
+                         int64_t n_rows, int splits, int64_t split_rows, float* sl_d,
+                         int32_t* sl_i) {
+    const dim3 grid(nbs, (unsigned)splits);
+    if (form == Gram::kHalf && wide) {
+      hipLaunchKernelGGL(k_knn_gram_wide_h, grid, dim3(256), 0, st, half_buf.get(), size, kp,
+                         norms, half_term.get(), metric, s * s, sl_d, sl_i, b0, split_rows);
+    } else if (form == Gram::kHalf) {
       switch (kp / 16) {
-#define HENN_X3(S_)                                                                           \
-  case S_:                                                                                    \
-    hipLaunchKernelGGL((k_gram_topk_x3<S_, kShort>), dim3(nbs), dim3(256), lds, st,           \
-                       split_buf.get(), size, norms, tnorm_buf.get(), metric, sl_d, sl_i, b0); \
+#define HENN_H(S_)                                                                              \
+  case S_:                                                                                      \
+    hipLaunchKernelGGL((k_gram_topk_h<S_, kShort>), grid, dim3(256), 0, st, half_buf.get(),     \
+                       size, norms, half_term.get(), metric, s * s, sl_d, sl_i, b0, split_rows); \
+    break;
+        HENN_H(1) HENN_H(2) HENN_H(3) HENN_H(4) HENN_H(5) HENN_H(6) HENN_H(7) HENN_H(8)
+#undef HENN_H
+        default: throw HipError{hipErrorInvalidValue, "FP16 Gram: d <= 128"};
+      }
+    } else if (form == Gram::kSplit) {
+      need_split();
+      switch (kp / 16) {
+#define HENN_X3(S_)                                                                             \
+  case S_:                                                                                      \
+    hipLaunchKernelGGL((k_gram_topk_x3<S_, kShort>), grid, dim3(256), 0, st, split_buf->get(),  \
+                       size, norms, split_term->get(), metric, sl_d, sl_i, b0, row_list, n_rows, \
+                       split_rows);                                                             \
     break;
         HENN_X3(1) HENN_X3(2) HENN_X3(3) HENN_X3(4) HENN_X3(5) HENN_X3(6) HENN_X3(7) HENN_X3(8)
 #undef HENN_X3
-        default:
-          throw HipError{hipErrorInvalidValue, "split Gram: d <= 128"};
+        default: throw HipError{hipErrorInvalidValue, "split Gram: d <= 128"};
       }
+    } else if (wide) {
+      hipLaunchKernelGGL(k_knn_gram_wide, grid, dim3(256),
+                         sizeof(float) * (4 * kWideC * kSStride + dpad), st, vec, size, dpad, mean,
+                         norms, metric, sl_d, sl_i, b0, row_list, n_rows, split_rows);
     } else {
-      launch_fp32_gram(b0, nbs, nullptr, size);
+      const size_t lds = sizeof(float) * (2 * (kTileC * (2 * kh + 4) + kTileC) + dpad);
+#define HENN_F32(KH_)                                                                           \
+  hipLaunchKernelGGL((k_gram_topk<KH_, kShort>), grid, dim3(256), lds, st, vec, size, dpad,     \
+                     norms, mean, metric, sl_d, sl_i, b0, row_list, n_rows, split_rows)
+      if (kh <= 16) HENN_F32(16);
+      else if (kh <= 32) HENN_F32(32);
+      else HENN_F32(64);
+#undef HENN_F32
     }
     HENN_HIP(hipGetLastError());
-    if (progress && b0 + (int64_t)nbs < nb) {
-      HENN_HIP(hipStreamSynchronize(st));
-      const auto now = std::chrono::steady_clock::now();
-      if (std::chrono::duration<double>(now - t_last).count() > 20.0) {
-        fprintf(stderr, "[henn] kNN graph of %lld rows: %lld row blocks of %lld done\n",
-                (long long)size, (long long)(b0 + nbs), (long long)nb);
-        t_last = now;
-      }
+  };
+  // the forms' error bounds (c: the FP32 terms of the FP16 and split forms)
+  auto err_of = [&](Gram form) {
+    GramErr e{nullptr, metric == 0 ? 2.0f : 1.0f, 0.0f, nmax, 0.0f, 0.0f, 1.0f};
+    if (form == Gram::kHalf) {
+      const float c = (float)(2 * kp + 4 * dpad + 40) * 0x1p-24f;
+      float rmax, ratio;
+      memcpy(&rmax, &hs.rmax, sizeof(float));
+      memcpy(&ratio, &hs.ratio, sizeof(float));
+      e.rres = rres.get();
+      e.rmax = rmax;
+      e.coef = c;
+      // r <= ratio |.|, and 2 |x'| |y'| <= |x'|^2 + |y'|^2
+      e.coef_rel = 1.002f * 0.5f * e.mult * (2.0f * ratio + ratio * ratio) + c;
+      e.gscale = 1.0f / (s * s);
+    } else {
+      // FP32 tiles: 4 (dpad + 8) 2^-24 (|x'|^2 + |y'|^2)
+      e.coef = form == Gram::kSplit ? x3_split_coef(dpad) : 4.0f * (float)(dpad + 8) * 0x1p-24f;
+      e.coef_rel = e.coef;
     }
-  }
-
-  // re-rank and proof of n_rows shortlists (of rows row_list[i], or row i);
-  // unproven rows are appended to out_rows
-  auto rerank = [&](const int32_t* row_list, int64_t n_rows, float c, int32_t* out_rows,
-                    uint32_t* out_count) {
-    const unsigned nr = (unsigned)((n_rows + 3) / 4);
+    return e;
+  };
+  // re-rank and proof of the shortlists of rows [row0, row0 + n) (of
+  // row_list, or all); unproven rows are appended to out_rows
+  auto rerank = [&](Gram form, const int32_t* row_list, int64_t row0, int64_t n, int splits,
+                    const float* sl_d, const int32_t* sl_i, int32_t* out_rows) {
+    const unsigned nr = (unsigned)((n + 3) / 4);
+    const GramErr err = err_of(form);
     bool launched = false;
 #define HENN_TRY(L, C)                                                                         \
   if (!launched && lpn == L && cpl == C) {                                                     \
     hipLaunchKernelGGL((k_knn_rerank<L, C>), dim3(nr), dim3(256), 0, st, vec, size, dpad,      \
-                       nchunks, metric, sl_d, sl_i, norms, nmax, c, R, adj, out_rows,          \
-                       out_count, row_list, n_rows);                                           \
+                       nchunks, metric, sl_d, sl_i, splits, norms, err, R, adj, out_rows,      \
+                       fb_count, row_list, row0, n);                                           \
     launched = true;                                                                           \
   }
     HENN_KNN_COMBOS(HENN_TRY)
 #undef HENN_TRY
     if (!launched) throw HipError{hipErrorInvalidValue, "no rerank kernel for this lane shape"};
   };
-  auto count_of = [&](uint32_t* dev_count) {
+  auto left = [&]() {
     uint32_t n = 0;
-    HENN_HIP(hipMemcpyAsync(&n, dev_count, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    HENN_HIP(hipMemcpyAsync(&n, fb_count, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HENN_HIP(hipStreamSynchronize(st));
     return n;
   };
-  rerank(nullptr, size, coef, fb_rows, fb_count);
-  uint32_t nfb = count_of(fb_count);
-  if (nfb > 0 && split) {
-    // the rows the split form could not prove: FP32 tiles on just those rows
-    // (128 rows share each pass over the layer, where the brute force below
-    // reads the whole layer once per row), then the FP32 proof
-    DevBuf<int32_t> fb2_buf(nfb);
-    DevBuf<uint32_t> fb2_count(1);
-    HENN_HIP(hipMemsetAsync(fb2_count.get(), 0, sizeof(uint32_t), st));
-    launch_fp32_gram(0, (unsigned)((nfb + 127) / 128), fb_rows, nfb);
-    HENN_HIP(hipGetLastError());
-    rerank(fb_rows, nfb, 4.0f * (float)(dpad + 8) * 0x1p-24f, fb2_buf.get(), fb2_count.get());
-    nfb = count_of(fb2_count.get());
-    if (nfb > 0)
-      HENN_HIP(hipMemcpyAsync(fb_rows, fb2_buf.get(), sizeof(int32_t) * nfb,
-                              hipMemcpyDeviceToDevice, st));
+
+  // First pass, all rows.  Launched in slices of row blocks, so that very
+  // large layers report progress (HENN_PROGRESS=1); the first slice of the
+  // FP16 form is a small one, and when it leaves more than a quarter of its
+  // rows unproven (multi-scale data), the other rows take the next form at
+  // once.
+  Gram form = half ? Gram::kHalf : (!wide && gram == 0) ? Gram::kSplit : Gram::kFp32;
+  const Gram second = (!wide && gram == 0) ? Gram::kSplit : Gram::kFp32;
+  HENN_HIP(hipMemsetAsync(fb_count, 0, sizeof(uint32_t), st));
+  {
+    int64_t split_rows = 0;
+    const int splits = gram_splits(size, size, &split_rows);
+    DevBuf<float> sl_d(size * splits * 2 * kShort);
+    DevBuf<int32_t> sl_i(size * splits * 2 * kShort);
+    const int64_t nb = (size + 127) / 128;
+    const bool progress = getenv("HENN_PROGRESS") != nullptr;
+    const int64_t slice =
+        std::max<int64_t>(4096, (int64_t)(2e13 / ((double)size * dpad * 256.0)));
+    auto t_last = std::chrono::steady_clock::now();
+    for (int64_t b0 = 0; b0 < nb;) {
+      const bool pilot = form == Gram::kHalf && b0 == 0 && nb > 512;
+      const int64_t nbs = std::min<int64_t>(pilot ? 256 : slice, nb - b0);
+      launch_gram(form, b0, (unsigned)nbs, nullptr, size, splits, split_rows, sl_d.get(),
+                  sl_i.get());
+      rerank(form, nullptr, 128 * b0, std::min(128 * nbs, size - 128 * b0), splits, sl_d.get(),
+             sl_i.get(), fb_a.get());
+      b0 += nbs;
+      if (pilot && (int64_t)left() * 4 > 128 * nbs) form = second;
+      if (progress && b0 < nb) {
+        HENN_HIP(hipStreamSynchronize(st));
+        const auto now = std::chrono::steady_clock::now();
+        if (std::chrono::duration<double>(now - t_last).count() > 20.0) {
+          fprintf(stderr, "[henn] kNN graph of %lld rows: %lld row blocks of %lld done\n",
+                  (long long)size, (long long)b0, (long long)nb);
+          t_last = now;
+        }
+      }
+    }
   }
+  uint32_t nfb = left();
+  // the rows a pass could not prove run through the next form on just those
+  // rows (128 of them share each pass over the layer, where the brute force
+  // below reads the whole layer once per row)
+  int32_t *from = fb_a.get(), *to = fb_b.get();
+  auto retry = [&](Gram f) {
+    if (nfb == 0) return;
+    HENN_HIP(hipMemsetAsync(fb_count, 0, sizeof(uint32_t), st));
+    int64_t split_rows = 0;
+    const int splits = gram_splits(nfb, size, &split_rows);
+    DevBuf<float> sl_d((int64_t)nfb * splits * 2 * kShort);
+    DevBuf<int32_t> sl_i((int64_t)nfb * splits * 2 * kShort);
+    launch_gram(f, 0, (unsigned)((nfb + 127) / 128), from, nfb, splits, split_rows, sl_d.get(),
+                sl_i.get());
+    rerank(f, from, 0, nfb, splits, sl_d.get(), sl_i.get(), to);
+    nfb = left();
+    std::swap(from, to);
+  };
+  if (half) retry(second);
+  if (gram == 0 && !wide) retry(Gram::kFp32);
   if (nfb > 0) {
     const int G = 64 / lpn;
     const int rpad = R;
@@ -1357,7 +1922,7 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
 #define HENN_TRY(L, C)                                                                          \
   if (!launched && lpn == L && cpl == C) {                                                      \
     hipLaunchKernelGGL((k_knn_exact<L, C>), dim3(nfb), dim3(256), lds2, st, vec, size, dpad,    \
-                       nchunks, metric, fb_rows, R, rpad, adj);                                 \
+                       nchunks, metric, from, R, rpad, adj);                                    \
     launched = true;                                                                            \
   }
     HENN_KNN_COMBOS(HENN_TRY)

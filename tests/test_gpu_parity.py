@@ -484,6 +484,33 @@ def test_split_gram_on_layers_of_one_or_a_few_tiles(hn, ho, n, d, metric):
                 assert set(out[0][r].tolist()) == set(oadj[r].tolist())
 
 
+@pytest.mark.parametrize("n,d,metric", [
+    (1, 8, 0), (2, 129, 1), (63, 17, 0), (64, 16, 1), (65, 128, 0), (127, 144, 0),
+    (128, 129, 1), (129, 1, 0), (257, 192, 0), (257, 100, 1), (4097, 200, 1), (8321, 33, 0)])
+@pytest.mark.parametrize("kind", ["gauss", "scales", "copies"])
+def test_fp16_gram_equals_fp32_gram_at_tile_edges(hn, n, d, metric, kind):
+    """The FP16 first pass (steps of 64 candidates, wide tiles of 128 in K
+    slices of 64, candidates split over blocks when the layer is small)
+    against FP32 tiles.  Both end in the exact re-rank with its proof, so the
+    graphs are equal with no tolerance: also for rows of very different
+    scales, where FP16 proves few rows and the later forms take over, and for
+    copies and zero rows, where ids decide."""
+    g = np.random.default_rng(n * 1000 + d)
+    X = g.standard_normal((n, d)).astype(np.float32)
+    if kind == "scales":
+        X *= np.exp2(g.integers(-20, 21, size=(n, 1))).astype(np.float32)
+    elif kind == "copies":
+        X = X[g.integers(0, max(1, n // 40), size=n)]
+        X[:: 7] = 0.0
+    Xd = to_dev(X)
+    out = []
+    for gram in (0, 1):
+        idx = hn.henn_build(Xd, degree=16, metric=metric, max_layers=0, gram=gram)
+        out.append(idx.export_layer(0)[1])
+        idx.free()
+    assert np.array_equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("d,metric", [(200, 0), (768, 1)])
 def test_wide_rows_end_to_end(hn, ho, d, metric):
     """Rows wider than 128 coordinates (K-sliced Gram build, 16-lane gathers):
