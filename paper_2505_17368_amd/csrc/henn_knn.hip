@@ -549,12 +549,12 @@ struct HalfStats {
   uint32_t rmax, ratio;
 };
 
-// One wave a row: rows [size_pad][kp] FP16, zero past dpad and for the
+// One wave a row: rows [size_pad][ld] FP16, zero past dpad and for the
 // padding rows; yterm [size_pad]: s^2 |y'|^2 (L2) or 0 (IP), +inf for the
 // padding rows; rres [size]: the residual norms.
 __global__ __launch_bounds__(256) void k_half_rows(const float* vec, const float* mean,
                                                    const float* norms, int metric, int64_t size,
-                                                   int64_t size_pad, int dpad, int kp, float s,
+                                                   int64_t size_pad, int dpad, int ld, float s,
                                                    uint16_t* out, float* yterm, float* rres,
                                                    HalfStats* stats) {
   const int lane = lane_id();
@@ -563,12 +563,12 @@ __global__ __launch_bounds__(256) void k_half_rows(const float* vec, const float
   for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < size_pad;
        r += (int64_t)gridDim.x * 4) {
     float r2 = 0.0f;
-    for (int c = lane; c < kp; c += 64) {
+    for (int c = lane; c < ld; c += 64) {
       const float v =
           (r < size && c < dpad) ? vec[r * dpad + c] - (mean ? mean[c] : 0.0f) : 0.0f;
       const float sv = v * s;
       const _Float16 hv = fabsf(sv) < 0x1p-14f ? (_Float16)0.0f : (_Float16)sv;
-      out[r * kp + c] = __builtin_bit_cast(uint16_t, hv);
+      out[r * ld + c] = __builtin_bit_cast(uint16_t, hv);
       const float d = v - (float)hv * inv;
       r2 = __builtin_fmaf(d, d, r2);
     }
@@ -582,25 +582,34 @@ __global__ __launch_bounds__(256) void k_half_rows(const float* vec, const float
     if (res <= 3.0e38f) rm = fmaxf(rm, res);
     if (n > 0.0f && n <= 3.0e38f) ra = fmaxf(ra, res / sqrtf(n));
   }
-  // few waves raise the maxima: a look at the current value (which only
-  // grows) saves thousands of atomics on two words
+  // one pair of atomics a block: one a wave took most of the time (10,000
+  // rows: 110 us)
+  __shared__ float wmax[2][4];
   if (lane == 0) {
-    const uint32_t rb = __float_as_uint(rm), ab = __float_as_uint(ra);
-    if (rb > __hip_atomic_load(&stats->rmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(&stats->rmax, rb);
-    if (ab > __hip_atomic_load(&stats->ratio, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(&stats->ratio, ab);
+    wmax[0][threadIdx.x >> 6] = rm;
+    wmax[1][threadIdx.x >> 6] = ra;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    const float* w = wmax[threadIdx.x];
+    const float v = fmaxf(fmaxf(w[0], w[1]), fmaxf(w[2], w[3]));
+    atomicMax(threadIdx.x ? &stats->ratio : &stats->rmax, __float_as_uint(v));
   }
 }
 
 // A lane's sorted shortlist and its staged candidates, shared by the FP16
-// kernels: values below the list's last entry are staged in LDS (slot i of
-// lane l at i * 64 + l) and merged a slot at a time for all lanes.
-template <int KS>
+// kernels: values below `tau` are staged in LDS (slot i of lane l at
+// i * 64 + l) and merged a slot at a time for all lanes.  tau bounds what the
+// row still wants from both lane halves: when each half holds J + 1 values,
+// the larger of the two (J + 1)-th has 2 (J + 1) values of the row at or
+// below it, and nothing beyond it is taken.  A list without
+// that bound would keep twice the values (the KS-th of its own half alone).
+template <int KS, int J>
 struct LaneList {
   float d[KS];
   int32_t i[KS];
   int n = 0;  // staged
+  float tau = INFINITY;
   __device__ __forceinline__ void clear() {
 #pragma unroll
     for (int j = 0; j < KS; ++j) {
@@ -610,78 +619,114 @@ struct LaneList {
   }
   // self: the row itself, dropped here
   __device__ __forceinline__ void merge(const uint2* cand, int lane, int64_t self) {
-    int m = n;
+    int m = 0;  // the most any lane staged
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = max(m, __shfl_xor(m, o));
-    m = __builtin_amdgcn_readfirstlane(m);
-    for (int k = 0; k < m; ++k) {
-      const uint2 e = cand[k * 64 + lane];
-      float nd = (k < n && (int64_t)e.y != self) ? __uint_as_float(e.x) : INFINITY;
-      if (__builtin_amdgcn_ballot_w64(nd < d[KS - 1])) {
-        int32_t ni = (int32_t)e.y;
+    for (int k = 0; k < kX3Cand; ++k) m += __builtin_amdgcn_ballot_w64(k < n) ? 1 : 0;
+    const uint2* e = cand + lane;
+    for (int k = 0; k < m; ++k, e += 64) {
+      const float nd = (k < n && (int64_t)e->y != self) ? __uint_as_float(e->x) : INFINITY;
+      const int32_t ni = (int32_t)e->y;
+      // from the last entry up, in place: ascending order makes the new
+      // value of an entry the median of it, its predecessor and nd
+      bool below = nd < d[KS - 1];
 #pragma unroll
-        for (int j = 0; j < KS; ++j) {
-          const bool sw = nd < d[j];
-          const float od = d[j];
-          const int32_t oi = i[j];
-          d[j] = sw ? nd : od;
-          i[j] = sw ? ni : oi;
-          nd = sw ? od : nd;
-          ni = sw ? oi : ni;
-        }
+      for (int j = KS - 1; j > 0; --j) {
+        const bool up = nd < d[j - 1];
+        i[j] = up ? i[j - 1] : below ? ni : i[j];
+        d[j] = __builtin_amdgcn_fmed3f(nd, d[j - 1], d[j]);
+        below = up;
+        asm volatile("" : "+v"(d[j]), "+v"(i[j]));
       }
+      i[0] = below ? ni : i[0];
+      d[0] = below ? nd : d[0];
     }
     n = 0;
+    tau = fminf(d[KS - 1], J + 1 < KS ? fmaxf(d[J], __shfl_xor(d[J], 32)) : INFINITY);
   }
   // one 32-candidate block's values (acc[v]: candidate c0 + 8 (v >> 2) +
-  // 4 h + (v & 3)); most blocks hold nothing for any lane
+  // 4 h + (v & 3)); most blocks hold nothing for any lane, and of the others
+  // most groups of four
   __device__ __forceinline__ void offer(const floatx16& acc, uint32_t c0, int h, uint2* cand, int lane,
                         int64_t self) {
-    float lo = acc[0];
+    uint32_t todo = 0;
+    {
+      float lo[4];
 #pragma unroll
-    for (int v = 1; v < 16; ++v) lo = fminf(lo, acc[v]);
-    if (!__builtin_amdgcn_ballot_w64(lo < d[KS - 1])) return;
+      for (int g = 0; g < 4; ++g)
+        lo[g] = fminf(fminf(fminf(acc[4 * g], acc[4 * g + 1]), acc[4 * g + 2]), acc[4 * g + 3]);
+      if (!__builtin_amdgcn_ballot_w64(fminf(fminf(fminf(lo[0], lo[1]), lo[2]), lo[3]) < tau))
+        return;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      if (__builtin_amdgcn_ballot_w64(n > kX3Cand - 4)) merge(cand, lane, self);
+      for (int g = 0; g < 4; ++g) todo |= __builtin_amdgcn_ballot_w64(lo[g] < tau) ? 1u << g : 0u;
+    }
+    // a merge whenever some lane could not stage four more
+    for (;;) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (acc[4 * g + u] < d[KS - 1]) {
-          cand[n * 64 + lane] = make_uint2(__float_as_uint(acc[4 * g + u]), c0 + 8 * g + 4 * h + u);
-          ++n;
+      for (int g = 0; g < 4; ++g) {
+        if ((todo >> g & 1) && !__builtin_amdgcn_ballot_w64(n > kX3Cand - 4)) {
+          todo &= ~(1u << g);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (acc[4 * g + u] < tau) {
+              cand[n * 64 + lane] =
+                  make_uint2(__float_as_uint(acc[4 * g + u]), c0 + 8 * g + 4 * h + u);
+              ++n;
+            }
+          }
         }
       }
+      if (!todo) break;
+      merge(cand, lane, self);
+    }
+  }
+  // row li's shortlist of this lane half: the entries, then empty ones
+  __device__ __forceinline__ void store(float* sl_d, int32_t* sl_i, int64_t list, int h, float qn) const {
+    const int64_t o = list * (2 * kShort) + h * kShort;
+#pragma unroll
+    for (int j = 0; j < kShort; ++j) {
+      sl_d[o + j] = j < KS ? d[j < KS ? j : 0] + qn : INFINITY;
+      sl_i[o + j] = j < KS ? i[j < KS ? j : 0] : -1;
     }
   }
 };
 
-// d <= 128.  500,000 x 128: layer 0 in 115.7 ms (553 TFLOP/s of distance work)
-// against 193 ms for the split form; what is left above the products is the
-// staging of values that enter a list and the LDS reads.
-// A block takes 128 rows (32 a wave, their operand in registers) and streams its split of the layer through LDS in steps of 64 candidates,
-// copied by global_load_lds into a ring of three buffers (see
-// k_gram_topk_x3).  The accumulators start at the candidates' norm terms, read
-// from LDS straight into them; the row's own norm is added when the list is
-// written, so a step's arithmetic besides the products is one minimum over
-// the values and one compare.  Two independent 32-candidate accumulators
-// keep the products from waiting on each other.
+// d <= 128.  A block takes 128 rows (32 a wave, their operand in registers)
+// and streams its split of the layer through LDS in steps of 64 candidates,
+// copied by global_load_lds into two buffers.  The accumulators start at the
+// candidates' norm terms, read from LDS straight into them; the row's own
+// norm is added when the list is written, so a step's arithmetic besides the
+// products is one minimum over the values and one compare.  Two independent
+// 32-candidate accumulators keep the products from waiting on each other.
+// 500,000 x 128: layer 0 in 75 ms (850 TFLOP/s of distance work) against 193
+// ms for the split form.  Matrix cores are busy 39% of the time and vector
+// units 40% (staging and merging the values that enter a list);
+// two buffers and lists of 24 leave room for three blocks a CU, where three
+// buffers with two blocks took 85 ms and lists of 32 that take all their half
+// wants (no tau) 116 ms.
 constexpr int kHalfStep = 64;
+// 2 x 16 values bound a row's wants; at 500,000 x 128 the rows this leaves
+// unproven cost the next form 2 ms
+constexpr int kHalfKs = 24, kHalfJ = 15;
 
-template <int S, int KS>
-__global__ __launch_bounds__(256, 2) void k_gram_topk_h(const uint16_t* rows, int64_t size,
+template <int S, int KS, int J>
+__global__ __launch_bounds__(256, 3) void k_gram_topk_h(const uint16_t* rows, int64_t size,
                                                         const float* norms, const float* yterm,
                                                         int metric, float s2, float* sl_d,
                                                         int32_t* sl_i, int64_t block0,
                                                         int64_t split_rows) {
-  constexpr int kRowU4 = 2 * S + 1;                         // staged row: 2 S chunks, one pad
-  constexpr int kJ = (kHalfStep * kRowU4 + 63) / 64;        // copy instructions a step
-  constexpr int kSlots = 64 * kJ;
-  constexpr int kBufU4 = kSlots + kHalfStep / 4;            // slots, then the norm terms
-  constexpr int kMaxJ = (kJ + 3) / 4;
-  static_assert(kMaxJ <= 5, "the waits below count at most six copies per wave and step");
-  __shared__ uint4 buf0[kBufU4], buf1[kBufU4], buf2[kBufU4];
+  constexpr int kRowU4 = 2 * S + 1;  // staged row: 2 S chunks, one pad
+  // Copies a wave and step: a fixed number and no branch around them (with
+  // copies behind conditions the compiler cannot tell how many follow those
+  // of the buffer about to be read, and waits for all of them).  The kRowU4
+  // instructions of a step go round the waves; those of the last round that
+  // have no instruction left repeat its last, writing the same bytes.
+  constexpr int kJ = (kRowU4 + 3) / 4;
+  constexpr int kSlots = kHalfStep * kRowU4;
+  constexpr int kBufU4 = kSlots + kHalfStep / 4;  // then the norm terms
+  static_assert(kJ <= 5 && kHalfStep == 64, "the copies below");
+  __shared__ uint4 buf0[kBufU4], buf1[kBufU4];
   __shared__ uint2 cand_all[4 * 64 * kX3Cand];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int qc = lane & 31, h = lane >> 5;
   const int64_t qrow = (block0 + blockIdx.x) * 128 + wave * 32 + qc;
   const bool qvalid = qrow < size;
@@ -691,52 +736,31 @@ __global__ __launch_bounds__(256, 2) void k_gram_topk_h(const uint16_t* rows, in
   // exact (the stored values are normal and at most 2^14)
   half8 bq[S];
   {
-    const half8* qr = reinterpret_cast<const half8*>(rows + (qvalid ? qrow : 0) * (16 * S));
+    const half8* qr = reinterpret_cast<const half8*>(rows + (qvalid ? qrow : 0) * (8 * kRowU4));
     const _Float16 f = qvalid ? (l2 ? (_Float16)-2.0f : (_Float16)-1.0f) : (_Float16)0.0f;
 #pragma unroll
     for (int k = 0; k < S; ++k) bq[k] = qr[2 * k + h] * f;
   }
   const float qn = (l2 && qvalid) ? norms[qrow] * s2 : 0.0f;
 
-  LaneList<KS> list;
+  LaneList<KS, J> list;
   list.clear();
   uint2* cand = cand_all + wave * (kX3Cand * 64);
 
-  int off0 = 0, off1 = 0, off2 = 0, off3 = 0, off4 = 0;
-#define HENN_H_OFF(U)                                                                    \
-  if constexpr (U < kMaxJ) {                                                             \
-    const int p_ = 64 * (wave + 4 * U) + lane, r_ = p_ / kRowU4, c_ = p_ - r_ * kRowU4;  \
-    off##U = min(r_, kHalfStep - 1) * 2 * S +                                            \
-             ((p_ < kHalfStep * kRowU4 && c_ < 2 * S) ? c_ : 0);                         \
-  }
-  HENN_H_OFF(0) HENN_H_OFF(1) HENN_H_OFF(2) HENN_H_OFF(3) HENN_H_OFF(4)
-#undef HENN_H_OFF
-  const int per_step = (kJ - wave + 3) / 4 + 1;  // this wave's copies per step, norms included
+  // the rows lie in memory as they are staged, so a step is one run of bytes
   typedef __attribute__((address_space(3))) void* lds_ptr;
   auto issue = [&](int64_t c0, uint4* tile) {
-    const uint4* src = reinterpret_cast<const uint4*>(rows + c0 * (16 * S));
-#define HENN_H_COPY(U)                                                                   \
-  if constexpr (U < kMaxJ)                                                               \
-    if (wave + 4 * U < kJ)                                                               \
-      __builtin_amdgcn_global_load_lds(src + off##U, (lds_ptr)(tile + 64 * (wave + 4 * U)), \
-                                       16, 0, 0);
+    const char* src = reinterpret_cast<const char*>(rows + c0 * (8 * kRowU4));
+    const uint32_t l16 = 16u * lane, l4 = 4u * lane;
+#define HENN_H_COPY(U)                                                                      \
+  if constexpr (U < kJ) {                                                                   \
+    const int j_ = min(wave + 4 * U, kRowU4 - 1);                                           \
+    __builtin_amdgcn_global_load_lds(src + 1024 * j_ + l16, (lds_ptr)(tile + 64 * j_), 16, 0, 0); \
+  }
     HENN_H_COPY(0) HENN_H_COPY(1) HENN_H_COPY(2) HENN_H_COPY(3) HENN_H_COPY(4)
 #undef HENN_H_COPY
-    if (lane < 16)
-      __builtin_amdgcn_global_load_lds(
-          yterm + c0 + 16 * wave + lane,
-          (lds_ptr)(reinterpret_cast<float*>(tile + kSlots) + 16 * wave), 4, 0, 0);
-  };
-  auto wait_copies = [](int n) {
-    switch (n) {
-      case 0: __builtin_amdgcn_s_waitcnt(0xF70); break;
-      case 1: __builtin_amdgcn_s_waitcnt(0xF71); break;
-      case 2: __builtin_amdgcn_s_waitcnt(0xF72); break;
-      case 3: __builtin_amdgcn_s_waitcnt(0xF73); break;
-      case 4: __builtin_amdgcn_s_waitcnt(0xF74); break;
-      case 5: __builtin_amdgcn_s_waitcnt(0xF75); break;
-      default: __builtin_amdgcn_s_waitcnt(0xF76); break;
-    }
+    __builtin_amdgcn_global_load_lds(reinterpret_cast<const char*>(yterm + c0) + l4,
+                                     (lds_ptr)(tile + kSlots), 4, 0, 0);
   };
   auto lds_barrier = []() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
@@ -763,37 +787,31 @@ __global__ __launch_bounds__(256, 2) void k_gram_topk_h(const uint16_t* rows, in
 
   const int64_t cb = (int64_t)blockIdx.y * split_rows;
   const int64_t nt = (min(cb + split_rows, size) - cb + kHalfStep - 1) / kHalfStep;
-  issue(cb, buf0);
-  if (nt > 1) issue(cb + kHalfStep, buf1);
-  for (int64_t t = 0; t < nt; t += 3) {
-#define HENN_H_STEP(I, CUR, NEXT2)                                                       \
-  {                                                                                      \
-    const int64_t tt_ = t + (I);                                                         \
-    wait_copies(tt_ + 1 < nt ? per_step : 0);                                            \
-    lds_barrier();                                                                       \
-    if (tt_ + 2 < nt) issue(cb + (tt_ + 2) * kHalfStep, NEXT2);                          \
-    body(cb + tt_ * kHalfStep, CUR);                                                     \
+  // past the last step the copies repeat it: never read
+  auto at = [&](int64_t t) { return cb + (t < nt ? t : nt - 1) * kHalfStep; };
+  issue(at(0), buf0);
+  for (int64_t t = 0; t < nt; t += 2) {
+    // the wait is for this wave's copies, the barrier for the others', and
+    // for their reads of the buffer that the next copies go to
+#define HENN_H_STEP(I, CUR, NEXT)          \
+  {                                        \
+    __builtin_amdgcn_s_waitcnt(0xF70);     \
+    lds_barrier();                         \
+    issue(at(t + (I) + 1), NEXT);          \
+    body(cb + (t + (I)) * kHalfStep, CUR); \
   }
-    HENN_H_STEP(0, buf0, buf2)
+    HENN_H_STEP(0, buf0, buf1)
     if (t + 1 >= nt) break;
     HENN_H_STEP(1, buf1, buf0)
-    if (t + 2 >= nt) break;
-    HENN_H_STEP(2, buf2, buf1)
 #undef HENN_H_STEP
   }
+  // the block's LDS is not given back with copies under way
+  __builtin_amdgcn_s_waitcnt(0xF70);
   list.merge(cand, lane, qrow);
-  if (qvalid) {
-    const int64_t o = (qrow * gridDim.y + blockIdx.y) * (2 * KS) + h * KS;
-#pragma unroll
-    for (int j = 0; j < KS; ++j) {
-      sl_d[o + j] = list.d[j] + qn;
-      sl_i[o + j] = list.i[j];
-    }
-  }
+  if (qvalid) list.store(sl_d, sl_i, qrow * gridDim.y + blockIdx.y, h, qn);
 }
 
-// d > 128: GEMM-shaped.  60,000 x 768: layer 0 in 12.4 ms (446 TFLOP/s)
-// against 65 ms for the FP32 tiles.  A block owns 128 rows (32 a wave) and walks its
+// d > 128: GEMM-shaped.  A block owns 128 rows (32 a wave) and walks its
 // split of the layer in tiles of 128 candidates; the K dimension streams
 // through LDS in slices of 64 coordinates of both operands, copied by
 // global_load_lds into two buffers, one slice ahead.  Each wave multiplies
@@ -801,8 +819,13 @@ __global__ __launch_bounds__(256, 2) void k_gram_topk_h(const uint16_t* rows, in
 // kp a multiple of 64 and size_pad of 128.  A staged row slice is its eight
 // chunks, chunk c in slot c ^ (row & 7), so that eight rows' reads of one
 // chunk fall on different banks without a pad: the two buffers and the staged
-// candidates are exactly half of a CU's LDS.
+// candidates are exactly half of a CU's LDS.  60,000 x 768: layer 0 in 10.3 ms
+// (540 TFLOP/s) against 65 ms for the FP32 tiles; bound by the LDS reads (five
+// operand reads for four products) and the wait at each slice.
 constexpr int kWideHRow = 8;
+// no common bound: with lists of 24 bounded by 2 x 16 values most rows of
+// 60,000 x 768 unit vectors (inner product) stayed unproven
+constexpr int kWideKs = 32, kWideJ = 31;
 constexpr int kWideHSlots = 128 * kWideHRow;  // one operand slice, a multiple of 64
 
 __global__ __launch_bounds__(256, 2) void k_knn_gram_wide_h(const uint16_t* rows, int64_t size,
@@ -820,9 +843,9 @@ __global__ __launch_bounds__(256, 2) void k_knn_gram_wide_h(const uint16_t* rows
   const int64_t qrow = qbase + wave * 32 + qc;
   const bool qvalid = qrow < size;
   const bool l2 = metric == 0;
-  const _Float16 f = l2 ? (_Float16)-2.0f : (_Float16)-1.0f;
+  const float f = l2 ? -2.0f : -1.0f;
   const float qn = (l2 && qvalid) ? norms[qrow] * s2 : 0.0f;
-  LaneList<kShort> list;
+  LaneList<kWideKs, kWideJ> list;
   list.clear();
   uint2* cand = cand_all + wave * (kX3Cand * 64);
 
@@ -844,16 +867,23 @@ __global__ __launch_bounds__(256, 2) void k_knn_gram_wide_h(const uint16_t* rows
   };
   auto slice_barrier = []() {
     // this wave's copies and LDS reads are done; the barrier covers the others
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    // (the builtin: a wait inside the asm would be unknown to the compiler,
+    // which then waits again, with the next slice's copies under way)
+    __builtin_amdgcn_s_waitcnt(0xF70);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   };
   floatx16 acc[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[q][v] = 0.0f;
   auto multiply = [&](const uint4* buf) {
     const uint4* brow = buf + kWideHSlots + (wave * 32 + qc) * kWideHRow;
     const uint4* arow = buf + qc * kWideHRow;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int c = (2 * k + h) ^ (qc & 7);
-      const half8 b = __builtin_bit_cast(half8, brow[c]) * f;  // a power of two: exact
+      const half8 b = __builtin_bit_cast(half8, brow[c]);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const half8 a = __builtin_bit_cast(half8, arow[32 * q * kWideHRow + c]);
@@ -871,23 +901,25 @@ __global__ __launch_bounds__(256, 2) void k_knn_gram_wide_h(const uint16_t* rows
     const bool last = ks + 1 == nsl;
     const int64_t nc0 = last ? c0 + 128 : c0;
     if (nc0 < ce) issue(nc0, last ? 0 : ks + 1, nxt);
-    if (ks == 0) {
+    multiply(cur);
+    if (last) {
+      // the norm terms are read here, not into the accumulators when a tile
+      // starts: there the wait for them is one for the copies just issued too
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const float4* tn = reinterpret_cast<const float4*>(yterm + c0 + 32 * q);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const float4 y = tn[2 * g + h];
-          acc[q][4 * g + 0] = y.x; acc[q][4 * g + 1] = y.y;
-          acc[q][4 * g + 2] = y.z; acc[q][4 * g + 3] = y.w;
+          acc[q][4 * g + 0] = __builtin_fmaf(f, acc[q][4 * g + 0], y.x);
+          acc[q][4 * g + 1] = __builtin_fmaf(f, acc[q][4 * g + 1], y.y);
+          acc[q][4 * g + 2] = __builtin_fmaf(f, acc[q][4 * g + 2], y.z);
+          acc[q][4 * g + 3] = __builtin_fmaf(f, acc[q][4 * g + 3], y.w);
         }
-      }
-    }
-    multiply(cur);
-    if (last) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
         list.offer(acc[q], (uint32_t)c0 + 32 * q, h, cand, lane, qrow);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[q][v] = 0.0f;
+      }
     }
     ks = last ? 0 : ks + 1;
     c0 = nc0;
@@ -902,14 +934,7 @@ __global__ __launch_bounds__(256, 2) void k_knn_gram_wide_h(const uint16_t* rows
     slice_barrier();
   }
   list.merge(cand, lane, qrow);
-  if (qvalid) {
-    const int64_t o = (qrow * gridDim.y + blockIdx.y) * (2 * kShort) + h * kShort;
-#pragma unroll
-    for (int j = 0; j < kShort; ++j) {
-      sl_d[o + j] = list.d[j] + qn;
-      sl_i[o + j] = list.i[j];
-    }
-  }
+  if (qvalid) list.store(sl_d, sl_i, qrow * gridDim.y + blockIdx.y, h, qn);
 }
 
 // Shortlist pass for rows wider than 128 coordinates (up to 1024), where
@@ -1130,6 +1155,7 @@ __device__ inline uint64_t wave_sort64(uint64_t key) {
 struct GramErr {
   const float* rres;
   float mult, rmax, nmax, coef, coef_rel, gscale;
+  int ks, j;  // a list's entries, and the entry whose pair bounds it (LaneList)
 };
 
 // One wave a row: the canonical distances of its shortlists (one of 64
@@ -1169,7 +1195,8 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const float* vec, int64_t si
   for (int sp = 0; sp < splits; ++sp) {
     const int64_t o = (li * splits + sp) * (2 * kShort);
     const float gv = sl_d[o + lane] * err.gscale;
-    cut = fminf(cut, fminf(__shfl(gv, kShort - 1), __shfl(gv, 2 * kShort - 1)));
+    cut = fminf(cut, fminf(__shfl(gv, err.ks - 1), __shfl(gv, kShort + err.ks - 1)));
+    cut = fminf(cut, fmaxf(__shfl(gv, err.j), __shfl(gv, kShort + err.j)));
     const int32_t id = sl_i[o + lane];
     const uint64_t kr = shfl_u64(best, R - 1);
     const float rth = kr == ~0ull ? INFINITY : from_ordered((uint32_t)(kr >> 32));
@@ -1727,7 +1754,9 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
   const bool half = gram == 0 && isfinite(nmax);
   float s = 1.0f;
   HalfStats hs{0, 0};
-  DevBuf<uint16_t> half_buf(half ? size_pad * kp : 1);
+  // (d <= 128: as they are staged, with the pad of eight)
+  const int ld = wide ? kp : kp + 8;
+  DevBuf<uint16_t> half_buf(half ? size_pad * ld : 1);
   DevBuf<float> half_term(half ? size_pad : 1), rres(half ? size : 1);
   if (half) {
     if (nmax > 0.0f) {
@@ -1737,9 +1766,9 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
     }
     DevBuf<HalfStats> stats(1);
     HENN_HIP(hipMemsetAsync(stats.get(), 0, sizeof(HalfStats), st));
-    const unsigned nb = (unsigned)std::min<int64_t>((size_pad + 3) / 4, 2048);
+    const unsigned nb = (unsigned)std::min<int64_t>((size_pad + 3) / 4, 512);
     hipLaunchKernelGGL(k_half_rows, dim3(nb), dim3(256), 0, st, vec, mean, norms, metric, size,
-                       size_pad, dpad, kp, s, half_buf.get(), half_term.get(), rres.get(),
+                       size_pad, dpad, ld, s, half_buf.get(), half_term.get(), rres.get(),
                        stats.get());
     HENN_HIP(hipGetLastError());
     HENN_HIP(hipMemcpyAsync(&hs, stats.get(), sizeof(hs), hipMemcpyDeviceToHost, st));
@@ -1772,7 +1801,7 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
       switch (kp / 16) {
 #define HENN_H(S_)                                                                              \
   case S_:                                                                                      \
-    hipLaunchKernelGGL((k_gram_topk_h<S_, kShort>), grid, dim3(256), 0, st, half_buf.get(),     \
+    hipLaunchKernelGGL((k_gram_topk_h<S_, kHalfKs, kHalfJ>), grid, dim3(256), 0, st, half_buf.get(),     \
                        size, norms, half_term.get(), metric, s * s, sl_d, sl_i, b0, split_rows); \
     break;
         HENN_H(1) HENN_H(2) HENN_H(3) HENN_H(4) HENN_H(5) HENN_H(6) HENN_H(7) HENN_H(8)
@@ -1810,7 +1839,7 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
   };
   // the forms' error bounds (c: the FP32 terms of the FP16 and split forms)
   auto err_of = [&](Gram form) {
-    GramErr e{nullptr, metric == 0 ? 2.0f : 1.0f, 0.0f, nmax, 0.0f, 0.0f, 1.0f};
+    GramErr e{nullptr, metric == 0 ? 2.0f : 1.0f, 0.0f, nmax, 0.0f, 0.0f, 1.0f, kShort, kShort - 1};
     if (form == Gram::kHalf) {
       const float c = (float)(2 * kp + 4 * dpad + 40) * 0x1p-24f;
       float rmax, ratio;
@@ -1822,6 +1851,8 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
       // r <= ratio |.|, and 2 |x'| |y'| <= |x'|^2 + |y'|^2
       e.coef_rel = 1.002f * 0.5f * e.mult * (2.0f * ratio + ratio * ratio) + c;
       e.gscale = 1.0f / (s * s);
+      e.ks = wide ? kWideKs : kHalfKs;
+      e.j = wide ? kWideJ : kHalfJ;
     } else {
       // FP32 tiles: 4 (dpad + 8) 2^-24 (|x'|^2 + |y'|^2)
       e.coef = form == Gram::kSplit ? x3_split_coef(dpad) : 4.0f * (float)(dpad + 8) * 0x1p-24f;
