@@ -214,7 +214,7 @@ static void nsw_insert_batch(int device, const float* vec, int dpad, int nchunks
       throw HipError{hipErrorInvalidValue, "NSW insertion search"};
   }
   int lpn, cpl;
-  pick_lanes(nchunks, 0, &lpn, &cpl);
+  pick_row_lanes(nchunks, &lpn, &cpl);
   nsw_merge_batch(vec, dpad, nchunks, metric, w.res, lo, nb, R, adj, M, w.cnt, w.off, w.inl, lpn,
                   cpl, st);
 }
@@ -389,7 +389,7 @@ static void finish_layer(henn_index* ix, int i, hipStream_t st) {
   LayerDev& L = ix->L[i];
   const henn_build_params& p = ix->params;
   int lpn, cpl;
-  pick_lanes(ix->nchunks, 0, &lpn, &cpl);
+  pick_row_lanes(ix->nchunks, &lpn, &cpl);
   if (p.graph == HENN_GRAPH_NSW) {
     L.adj = nsw_graph(ix, L.vec32, L.size, st);
     L.deg = p.max_degree;
@@ -495,8 +495,10 @@ static int sample_layer(henn_index* ix, int i, hipStream_t st, int32_t* local_ou
       keys = dalloc<uint64_t>((int64_t)r * s);
       HENN_HIP(hipMemcpyAsync(d_centres, centres.data(), sizeof(int32_t) * r,
                               hipMemcpyHostToDevice, st));
-      launch_ring_keys(lpn, cpl, prev.vec32, ix->dpad, ix->nchunks, ix->metric, s, d_centres, r,
-                       keys, st);
+      int key_lpn, key_cpl;
+      pick_row_lanes(ix->nchunks, &key_lpn, &key_cpl);
+      launch_ring_keys(key_lpn, key_cpl, prev.vec32, ix->dpad, ix->nchunks, ix->metric, s,
+                       d_centres, r, keys, st);
       std::vector<uint64_t> ends((size_t)(2 * r));
       launch_radix_select(keys, s, r, ranks.data(), ends.data(), st);
       (void)hipFree(keys);
@@ -900,7 +902,7 @@ henn_status henn_delete(henn_index* idx, const int32_t* ids_host, int64_t count,
       return fail(HENN_E_INVAL, "deletion would leave the index empty");
     ++idx->updates;
     int lpn, cpl;
-    pick_lanes(idx->nchunks, 0, &lpn, &cpl);
+    pick_row_lanes(idx->nchunks, &lpn, &cpl);
     for (int i = 0; i < idx->num_layers; ++i) {
       LayerDev& L = idx->L[i];
       const int64_t s = L.size;

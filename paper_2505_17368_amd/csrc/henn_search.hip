@@ -1675,6 +1675,10 @@ void pick_lanes(int nchunks, int requested_lpn, int* lpn, int* cpl) {
   pick_lanes_at_most(nchunks, requested_lpn, 4, lpn, cpl);
 }
 
+void pick_row_lanes(int nchunks, int* lpn, int* cpl) {
+  pick_lanes_at_most(nchunks, 0, 2, lpn, cpl);
+}
+
 void pick_search_lanes(int storage, int nchunks, int64_t nq, int cus, int requested_lpn, int* lpn,
                        int* cpl) {
   const int64_t simds = 4ll * cus;
