@@ -152,6 +152,7 @@ struct NswWork {
   float* dist = nullptr;
   uint32_t* cnt = nullptr;
   uint32_t* off = nullptr;
+  uint32_t* bsum = nullptr;
   int32_t* inl = nullptr;
   NswWork(int64_t s, int64_t nb_max, int R) {
     try {
@@ -159,6 +160,7 @@ struct NswWork {
       dist = dalloc<float>(nb_max * R);
       cnt = dalloc<uint32_t>(s + 1);
       off = dalloc<uint32_t>(s + 1);
+      bsum = dalloc<uint32_t>(scan_scratch(s));
       inl = dalloc<int32_t>(nb_max * R);
     } catch (...) {
       release();
@@ -171,10 +173,11 @@ struct NswWork {
     (void)hipFree(dist);
     (void)hipFree(cnt);
     (void)hipFree(off);
+    (void)hipFree(bsum);
     (void)hipFree(inl);
     res = nullptr;
     dist = nullptr;
-    cnt = off = nullptr;
+    cnt = off = bsum = nullptr;
     inl = nullptr;
   }
 };
@@ -215,8 +218,8 @@ static void nsw_insert_batch(int device, const float* vec, int dpad, int nchunks
   }
   int lpn, cpl;
   pick_row_lanes(nchunks, &lpn, &cpl);
-  nsw_merge_batch(vec, dpad, nchunks, metric, w.res, lo, nb, R, adj, M, w.cnt, w.off, w.inl, lpn,
-                  cpl, st);
+  nsw_merge_batch(vec, dpad, nchunks, metric, w.res, lo, nb, R, adj, M, w.cnt, w.off, w.bsum,
+                  w.inl, lpn, cpl, st);
 }
 
 static int32_t* nsw_graph(henn_index* ix, const float* vec, int64_t s, hipStream_t st) {
@@ -598,7 +601,10 @@ static void prepare_root(henn_index* ix, hipStream_t st) {
   }
   if (ix->metric == HENN_L2) {
     r.mean = dalloc<float>(ix->dpad);
-    layer_mean(r.dec, R.size, ix->dpad, r.mean, st);
+    {
+      DevBuf<float> partial(mean_scratch(R.size, ix->dpad));
+      layer_mean(r.dec, R.size, ix->dpad, r.mean, partial.get(), st);
+    }
     std::vector<float> m((size_t)ix->dpad);
     HENN_HIP(hipMemcpyAsync(m.data(), r.mean, sizeof(float) * ix->dpad, hipMemcpyDeviceToHost,
                             st));
@@ -609,7 +615,10 @@ static void prepare_root(henn_index* ix, hipStream_t st) {
   }
   r.norm = dalloc<float>(R.size);
   launch_row_norms(r.dec, r.mean, R.size, ix->dpad, r.norm, st);
-  r.nmax = max_norm(r.norm, R.size, st);
+  {
+    DevBuf<uint32_t> word(1);
+    r.nmax = max_norm(r.norm, R.size, word.get(), st);
+  }
   prepare_root_bf16(r, ix->dpad, ix->metric, st);
 }
 

@@ -256,7 +256,7 @@ __global__ void k_block_sum_u32(const uint32_t* in, int64_t n, uint32_t* bsum) {
 }
 
 __global__ void k_block_scan_u32(const uint32_t* in, int64_t n, const uint32_t* boff,
-                                 const uint32_t* total, uint32_t* out) {
+                                 const uint32_t* total, uint32_t* out, uint32_t* out2) {
   __shared__ uint32_t scan[kScanBlock];
   const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
   const uint32_t v = i < n ? in[i] : 0u;
@@ -268,22 +268,24 @@ __global__ void k_block_scan_u32(const uint32_t* in, int64_t n, const uint32_t* 
     scan[threadIdx.x] += a;
     __syncthreads();
   }
-  if (i < n) out[i] = boff[blockIdx.x] + scan[threadIdx.x] - v;
+  const uint32_t x = boff[blockIdx.x] + scan[threadIdx.x] - v;
+  if (i < n) out[i] = x;
+  if (i < n && out2) out2[i] = x;
   if (i == 0) out[n] = *total;
 }
 
-int64_t exclusive_scan_u32(const uint32_t* in, int64_t n, uint32_t* out, hipStream_t st) {
-  const int64_t nb = std::max<int64_t>(1, (n + kScanBlock - 1) / kScanBlock);
-  DevBuf<uint32_t> bsum_buf(nb + 1);
-  uint32_t* bsum = bsum_buf.get();
+int64_t scan_scratch(int64_t n) {
+  return std::max<int64_t>(1, (n + kScanBlock - 1) / kScanBlock) + 1;
+}
+
+void exclusive_scan_u32(const uint32_t* in, int64_t n, uint32_t* out, uint32_t* out2,
+                        uint32_t* bsum, hipStream_t st) {
+  const int64_t nb = scan_scratch(n) - 1;
   hipLaunchKernelGGL(k_block_sum_u32, dim3((unsigned)nb), dim3(kScanBlock), 0, st, in, n, bsum);
   hipLaunchKernelGGL(k_scan_bsum, dim3(1), dim3(1024), 0, st, bsum, nb, bsum + nb);
   hipLaunchKernelGGL(k_block_scan_u32, dim3((unsigned)nb), dim3(kScanBlock), 0, st, in, n, bsum,
-                     bsum + nb, out);
-  uint32_t total = 0;
-  HENN_HIP(hipMemcpyAsync(&total, bsum + nb, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-  HENN_HIP(hipStreamSynchronize(st));
-  return (int64_t)total;
+                     bsum + nb, out, out2);
+  HENN_HIP(hipGetLastError());
 }
 
 __global__ void k_map_ids(const int32_t* prev_ids, const int32_t* local, int64_t count,
@@ -498,26 +500,43 @@ __global__ void k_col_partial(const float* vec, int64_t size, int dpad, int64_t 
   }
 }
 
-void layer_mean(const float* vec, int64_t size, int dpad, float* mean_dev, hipStream_t st) {
+// 32 columns a block, eight threads a column: the partial sums added up in
+// double.
+__global__ __launch_bounds__(256) void k_col_mean(const float* partial, int64_t nblk, int dpad,
+                                                  int64_t size, float* mean) {
+  __shared__ double part[8][32];
+  const int c = threadIdx.x & 31, g = threadIdx.x >> 5, j = blockIdx.x * 32 + c;
+  double acc = 0.0;
+  if (j < dpad)
+    for (int64_t b = g; b < nblk; b += 8) acc += partial[b * dpad + j];
+  part[g][c] = acc;
+  __syncthreads();
+  if (g == 0 && j < dpad) {
+    double sum = 0.0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum += part[i][c];
+    mean[j] = (float)(sum / (double)size);
+  }
+}
+
+static int64_t mean_rows_per_block(int64_t size) {
   const int64_t nb = std::min<int64_t>(size, 2048);
-  const int64_t per = (size + nb - 1) / nb;
-  const int64_t nblk = (size + per - 1) / per;
-  DevBuf<float> partial_buf(nblk * dpad);
-  float* partial = partial_buf.get();
+  return (size + nb - 1) / nb;
+}
+
+int64_t mean_scratch(int64_t size, int dpad) {
+  const int64_t per = mean_rows_per_block(size);
+  return (size + per - 1) / per * dpad;
+}
+
+void layer_mean(const float* vec, int64_t size, int dpad, float* mean_dev, float* partial,
+                hipStream_t st) {
+  const int64_t per = mean_rows_per_block(size), nblk = (size + per - 1) / per;
   hipLaunchKernelGGL(k_col_partial, dim3((unsigned)nblk), dim3(256), 0, st, vec, size, dpad, per,
                      partial);
-  std::vector<float> h((size_t)(nblk * dpad));
-  HENN_HIP(hipMemcpyAsync(h.data(), partial, sizeof(float) * nblk * dpad, hipMemcpyDeviceToHost,
-                          st));
-  HENN_HIP(hipStreamSynchronize(st));
-  std::vector<float> mean((size_t)dpad);
-  for (int j = 0; j < dpad; ++j) {
-    double acc = 0.0;
-    for (int64_t b = 0; b < nblk; ++b) acc += h[(size_t)(b * dpad + j)];
-    mean[(size_t)j] = (float)(acc / (double)size);
-  }
-  HENN_HIP(hipMemcpyAsync(mean_dev, mean.data(), sizeof(float) * dpad, hipMemcpyHostToDevice, st));
-  HENN_HIP(hipStreamSynchronize(st));
+  hipLaunchKernelGGL(k_col_mean, dim3((unsigned)((dpad + 31) / 32)), dim3(256), 0, st, partial,
+                     nblk, dpad, size, mean_dev);
+  HENN_HIP(hipGetLastError());
 }
 
 // A block's 64 rows go through LDS in slices of 32 coordinates, read along
@@ -568,14 +587,12 @@ __global__ void k_max_reduce(const float* v, int64_t n, unsigned int* out) {
   if ((threadIdx.x & 63) == 0) atomicMax(out, __float_as_uint(m));  // m >= 0: bits are monotone
 }
 
-float max_norm(const float* norms, int64_t size, hipStream_t st) {
-  DevBuf<unsigned int> d_buf(1);
-  unsigned int* d = d_buf.get();
-  HENN_HIP(hipMemsetAsync(d, 0, sizeof(unsigned int), st));
-  const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((size + 255) / 256, 1024));
-  hipLaunchKernelGGL(k_max_reduce, dim3(g), dim3(256), 0, st, norms, size, d);
-  unsigned int h = 0;
-  HENN_HIP(hipMemcpyAsync(&h, d, sizeof(unsigned int), hipMemcpyDeviceToHost, st));
+float max_norm(const float* norms, int64_t size, uint32_t* word, hipStream_t st) {
+  HENN_HIP(hipMemsetAsync(word, 0, sizeof(uint32_t), st));
+  const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((size + 255) / 256, 256));
+  hipLaunchKernelGGL(k_max_reduce, dim3(g), dim3(256), 0, st, norms, size, word);
+  uint32_t h = 0;
+  HENN_HIP(hipMemcpyAsync(&h, word, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
   HENN_HIP(hipStreamSynchronize(st));
   float f;
   memcpy(&f, &h, sizeof(f));

@@ -149,6 +149,21 @@ struct DevBuf {
   T* get() const { return p; }
 };
 
+// Offsets of the parts of one device allocation, 256-byte aligned.
+class DevParts {
+ public:
+  template <typename T>
+  size_t add(int64_t count) {
+    const size_t at = size_;
+    size_ += (sizeof(T) * (size_t)(count > 0 ? count : 1) + 255) / 256 * 256;
+    return at;
+  }
+  int64_t bytes() const { return (int64_t)size_; }
+
+ private:
+  size_t size_ = 0;
+};
+
 inline int next_pow2(int v) {
   int p = 1;
   while (p < v) p *= 2;
@@ -327,13 +342,21 @@ int64_t launch_halve(uint64_t seed, int layer, int attempt, int64_t s, int m, in
 void launch_draw_mark(uint64_t seed, int layer, int attempt, int64_t s, int64_t draws,
                       uint32_t* bitmap, hipStream_t st);
 int64_t compact_bitmap(const uint32_t* bitmap, int64_t s, int32_t* out_local, hipStream_t st);
-int64_t exclusive_scan_u32(const uint32_t* in, int64_t n, uint32_t* out, hipStream_t st);
+// out[0 .. n] (and out2[0 .. n - 1], unless null) = the exclusive sums of in;
+// bsum: scan_scratch(n) words.
+int64_t scan_scratch(int64_t n);
+void exclusive_scan_u32(const uint32_t* in, int64_t n, uint32_t* out, uint32_t* out2,
+                        uint32_t* bsum, hipStream_t st);
 void launch_map_ids(const int32_t* prev_ids, const int32_t* local, int64_t count, int32_t* ids,
                     int32_t* down, hipStream_t st);
-void layer_mean(const float* vec, int64_t size, int dpad, float* mean_dev, hipStream_t st);
+// partial: mean_scratch(size, dpad) floats.
+int64_t mean_scratch(int64_t size, int dpad);
+void layer_mean(const float* vec, int64_t size, int dpad, float* mean_dev, float* partial,
+                hipStream_t st);
 void launch_row_norms(const float* vec, const float* mean, int64_t size, int dpad, float* norms,
                       hipStream_t st);
-float max_norm(const float* norms, int64_t size, hipStream_t st);
+// word: scratch on the device.
+float max_norm(const float* norms, int64_t size, uint32_t* word, hipStream_t st);
 void launch_quantize(int storage, const float* vec, int64_t size, int dpad, void* out,
                      float* scale, hipStream_t st);
 // FP32 rows of the stored values: decoded BF16, or scale * decoded FP8.
@@ -379,7 +402,7 @@ void launch_remap_down(int32_t* down, int64_t size, const int32_t* below_newpos,
 // entries, inl nb * R.
 void nsw_merge_batch(const float* vec, int dpad, int nchunks, int metric, const int32_t* res,
                      int64_t lo, int64_t nb, int R, int32_t* adj, int M, uint32_t* cnt,
-                     uint32_t* off, int32_t* inl, int lpn, int cpl, hipStream_t st);
+                     uint32_t* off, uint32_t* bsum, int32_t* inl, int lpn, int cpl, hipStream_t st);
 void prune_graph(const float* vec, int64_t size, int dpad, int nchunks, int metric,
                  const int32_t* adj_in, int C, int R, int32_t* adj_out, int lpn, int cpl,
                  hipStream_t st);

@@ -1755,45 +1755,57 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
                         int lpn, int cpl, int32_t* adj, int gram, hipStream_t st) {
   if (size <= 0) return 0;
   if (dpad > 1024) throw HipError{hipErrorInvalidValue, "kNN build supports d <= 1024"};
-  DevBuf<float> norms_buf(size), mean_buf(metric == 0 ? dpad : 1);
-  // rows left to the next pass (two lists used in turn) and their number
-  DevBuf<int32_t> fb_a(size), fb_b(size);
-  DevBuf<uint32_t> fb_count_buf(1);
-  float* norms = norms_buf.get();
-  float* mean = metric == 0 ? mean_buf.get() : nullptr;
-  uint32_t* fb_count = fb_count_buf.get();
-  if (metric == 0) layer_mean(vec, size, dpad, mean, st);
-  launch_row_norms(vec, mean, size, dpad, norms, st);
-  const float nmax = max_norm(norms, size, st);
-
-  const int kh = dpad <= 32 ? 16 : dpad <= 64 ? 32 : 64;
   const bool wide = dpad > 128;
   const int kp = wide ? (dpad + 63) / 64 * 64 : (dpad + 15) / 16 * 16;
+  // FP16 rows (d <= 128: as they are staged, with the pad of eight)
+  const int ld = wide ? kp : kp + 8;
   // rows and norm terms of the FP16 and split forms, padded to whole tiles
   const int64_t size_pad = (size + 127) / 128 * 128;
+  const int64_t half_rows = gram == 0 ? size_pad : 0;
+  // one allocation for what lives through the call: a dozen small ones cost
+  // a layer of a few thousand rows as much as its tiles.  Rows left to the
+  // next pass: two lists used in turn, and their number.
+  DevParts parts;
+  const size_t at_norms = parts.add<float>(size), at_mean = parts.add<float>(dpad);
+  const size_t at_partial = parts.add<float>(metric == 0 ? mean_scratch(size, dpad) : 0);
+  const size_t at_fa = parts.add<int32_t>(size), at_fb = parts.add<int32_t>(size);
+  const size_t at_count = parts.add<uint32_t>(1), at_stats = parts.add<HalfStats>(1);
+  const size_t at_half = parts.add<uint16_t>(half_rows * ld);
+  const size_t at_term = parts.add<float>(half_rows), at_rres = parts.add<float>(half_rows);
+  DevBuf<uint8_t> work(parts.bytes());
+  float* norms = reinterpret_cast<float*>(work.get() + at_norms);
+  float* mean = metric == 0 ? reinterpret_cast<float*>(work.get() + at_mean) : nullptr;
+  int32_t* fb_a = reinterpret_cast<int32_t*>(work.get() + at_fa);
+  int32_t* fb_b = reinterpret_cast<int32_t*>(work.get() + at_fb);
+  uint32_t* fb_count = reinterpret_cast<uint32_t*>(work.get() + at_count);
+  HalfStats* stats = reinterpret_cast<HalfStats*>(work.get() + at_stats);
+  uint16_t* half_buf = reinterpret_cast<uint16_t*>(work.get() + at_half);
+  float* half_term = reinterpret_cast<float*>(work.get() + at_term);
+  float* rres = reinterpret_cast<float*>(work.get() + at_rres);
+  if (metric == 0)
+    layer_mean(vec, size, dpad, mean, reinterpret_cast<float*>(work.get() + at_partial), st);
+  launch_row_norms(vec, mean, size, dpad, norms, st);
+  const float nmax = max_norm(norms, size, fb_count, st);
+
+  const int kh = dpad <= 32 ? 16 : dpad <= 64 ? 32 : 64;
 
   // FP16 rows: the scale takes the largest norm to 2^13 .. 2^14
   const bool half = gram == 0 && isfinite(nmax);
   float s = 1.0f;
   HalfStats hs{0, 0};
-  // (d <= 128: as they are staged, with the pad of eight)
-  const int ld = wide ? kp : kp + 8;
-  DevBuf<uint16_t> half_buf(half ? size_pad * ld : 1);
-  DevBuf<float> half_term(half ? size_pad : 1), rres(half ? size : 1);
   if (half) {
     if (nmax > 0.0f) {
       int e = 0;
       (void)frexpf(sqrtf(nmax), &e);
       s = ldexpf(1.0f, std::max(-60, std::min(60, 14 - e)));
     }
-    DevBuf<HalfStats> stats(1);
-    HENN_HIP(hipMemsetAsync(stats.get(), 0, sizeof(HalfStats), st));
+    HENN_HIP(hipMemsetAsync(stats, 0, sizeof(HalfStats), st));
     const unsigned nb = (unsigned)std::min<int64_t>((size_pad + 3) / 4, 512);
     hipLaunchKernelGGL(k_half_rows, dim3(nb), dim3(256), 0, st, vec, mean, norms, metric, size,
-                       size_pad, dpad, ld, s, half_buf.get(), half_term.get(), rres.get(),
-                       stats.get());
+                       size_pad, dpad, ld, s, half_buf, half_term, rres,
+                       stats);
     HENN_HIP(hipGetLastError());
-    HENN_HIP(hipMemcpyAsync(&hs, stats.get(), sizeof(hs), hipMemcpyDeviceToHost, st));
+    HENN_HIP(hipMemcpyAsync(&hs, stats, sizeof(hs), hipMemcpyDeviceToHost, st));
     HENN_HIP(hipStreamSynchronize(st));
   }
   // split BF16 rows, made when a pass first needs them
@@ -1817,14 +1829,14 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
                          int32_t* sl_i) {
     const dim3 grid(nbs, (unsigned)splits);
     if (form == Gram::kHalf && wide) {
-      hipLaunchKernelGGL(k_knn_gram_wide_h, grid, dim3(256), 0, st, half_buf.get(), size, kp,
-                         norms, half_term.get(), metric, s * s, sl_d, sl_i, b0, split_rows);
+      hipLaunchKernelGGL(k_knn_gram_wide_h, grid, dim3(256), 0, st, half_buf, size, kp,
+                         norms, half_term, metric, s * s, sl_d, sl_i, b0, split_rows);
     } else if (form == Gram::kHalf) {
       switch (kp / 16) {
 #define HENN_H(S_)                                                                              \
   case S_:                                                                                      \
-    hipLaunchKernelGGL((k_gram_topk_h<S_, kHalfKs, kHalfJ>), grid, dim3(256), 0, st, half_buf.get(),     \
-                       size, norms, half_term.get(), metric, s * s, sl_d, sl_i, b0, split_rows); \
+    hipLaunchKernelGGL((k_gram_topk_h<S_, kHalfKs, kHalfJ>), grid, dim3(256), 0, st, half_buf,     \
+                       size, norms, half_term, metric, s * s, sl_d, sl_i, b0, split_rows); \
     break;
         HENN_H(1) HENN_H(2) HENN_H(3) HENN_H(4) HENN_H(5) HENN_H(6) HENN_H(7) HENN_H(8)
 #undef HENN_H
@@ -1867,7 +1879,7 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
       float rmax, ratio;
       memcpy(&rmax, &hs.rmax, sizeof(float));
       memcpy(&ratio, &hs.ratio, sizeof(float));
-      e.rres = rres.get();
+      e.rres = rres;
       e.rmax = rmax;
       e.coef = c;
       // r <= ratio |.|, and 2 |x'| |y'| <= |x'|^2 + |y'|^2
@@ -1918,8 +1930,10 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
   {
     int64_t split_rows = 0;
     const int splits = gram_splits(size, size, &split_rows);
-    DevBuf<float> sl_d(size * splits * 2 * kShort);
-    DevBuf<int32_t> sl_i(size * splits * 2 * kShort);
+    const int64_t entries = size * splits * 2 * kShort;
+    DevBuf<float> lists(2 * entries);  // values, then positions
+    float* sl_d = lists.get();
+    int32_t* sl_i = reinterpret_cast<int32_t*>(sl_d + entries);
     const int64_t nb = (size + 127) / 128;
     const bool progress = getenv("HENN_PROGRESS") != nullptr;
     const int64_t slice =
@@ -1928,10 +1942,10 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
     for (int64_t b0 = 0; b0 < nb;) {
       const bool pilot = form == Gram::kHalf && b0 == 0 && nb > 512;
       const int64_t nbs = std::min<int64_t>(pilot ? 256 : slice, nb - b0);
-      launch_gram(form, b0, (unsigned)nbs, nullptr, size, splits, split_rows, sl_d.get(),
-                  sl_i.get());
-      rerank(form, nullptr, 128 * b0, std::min(128 * nbs, size - 128 * b0), splits, sl_d.get(),
-             sl_i.get(), fb_a.get());
+      launch_gram(form, b0, (unsigned)nbs, nullptr, size, splits, split_rows, sl_d,
+                  sl_i);
+      rerank(form, nullptr, 128 * b0, std::min(128 * nbs, size - 128 * b0), splits, sl_d,
+             sl_i, fb_a);
       b0 += nbs;
       if (pilot && (int64_t)left() * 4 > 128 * nbs) form = second;
       if (progress && b0 < nb) {
@@ -1949,17 +1963,19 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
   // the rows a pass could not prove run through the next form on just those
   // rows (128 of them share each pass over the layer, where the brute force
   // below reads the whole layer once per row)
-  int32_t *from = fb_a.get(), *to = fb_b.get();
+  int32_t *from = fb_a, *to = fb_b;
   auto retry = [&](Gram f) {
     if (nfb == 0) return;
     HENN_HIP(hipMemsetAsync(fb_count, 0, sizeof(uint32_t), st));
     int64_t split_rows = 0;
     const int splits = gram_splits(nfb, size, &split_rows);
-    DevBuf<float> sl_d((int64_t)nfb * splits * 2 * kShort);
-    DevBuf<int32_t> sl_i((int64_t)nfb * splits * 2 * kShort);
-    launch_gram(f, 0, (unsigned)((nfb + 127) / 128), from, nfb, splits, split_rows, sl_d.get(),
-                sl_i.get());
-    rerank(f, from, 0, nfb, splits, sl_d.get(), sl_i.get(), to);
+    const int64_t entries = (int64_t)nfb * splits * 2 * kShort;
+    DevBuf<float> lists(2 * entries);
+    float* sl_d = lists.get();
+    int32_t* sl_i = reinterpret_cast<int32_t*>(sl_d + entries);
+    launch_gram(f, 0, (unsigned)((nfb + 127) / 128), from, nfb, splits, split_rows, sl_d,
+                sl_i);
+    rerank(f, from, 0, nfb, splits, sl_d, sl_i, to);
     nfb = left();
     std::swap(from, to);
   };
@@ -2153,15 +2169,14 @@ void symmetrize_graph(const float* vec, int64_t size, int dpad, int nchunks, int
                       const int32_t* adj_knn, int R, int32_t* adj_out, int max_deg, int lpn,
                       int cpl, hipStream_t st) {
   const int64_t edges = size * R;
-  DevBuf<uint32_t> cnt_buf(size + 1), off_buf(size + 1);
+  DevBuf<uint32_t> cnt_buf(size + 1), off_buf(size + 1), bsum_buf(scan_scratch(size));
   DevBuf<int32_t> inl_buf(edges);
   uint32_t *cnt = cnt_buf.get(), *off = off_buf.get();
   int32_t* inl = inl_buf.get();
   HENN_HIP(hipMemsetAsync(cnt, 0, sizeof(uint32_t) * (size + 1), st));
   const unsigned eb = (unsigned)((edges + 255) / 256);
   hipLaunchKernelGGL(k_indeg, dim3(eb), dim3(256), 0, st, adj_knn, edges, cnt);
-  exclusive_scan_u32(cnt, size, off, st);
-  HENN_HIP(hipMemcpyAsync(cnt, off, sizeof(uint32_t) * size, hipMemcpyDeviceToDevice, st));
+  exclusive_scan_u32(cnt, size, off, cnt, bsum_buf.get(), st);
   hipLaunchKernelGGL(k_scatter_in, dim3(eb), dim3(256), 0, st, adj_knn, edges, R, (int64_t)0,
                      cnt, inl);
   const unsigned nb = (unsigned)((size + 3) / 4);
@@ -2241,7 +2256,8 @@ __global__ __launch_bounds__(256) void k_nsw_merge(const float* vec, int64_t lo,
 
 void nsw_merge_batch(const float* vec, int dpad, int nchunks, int metric, const int32_t* res,
                      int64_t lo, int64_t nb, int R, int32_t* adj, int M, uint32_t* cnt,
-                     uint32_t* off, int32_t* inl, int lpn, int cpl, hipStream_t st) {
+                     uint32_t* off, uint32_t* bsum, int32_t* inl, int lpn, int cpl,
+                     hipStream_t st) {
   const int64_t rows = nb * M;
   hipLaunchKernelGGL(k_nsw_rows, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, res,
                      nb, R, M, lo, adj);
@@ -2250,8 +2266,7 @@ void nsw_merge_batch(const float* vec, int dpad, int nchunks, int metric, const 
   const unsigned eb = (unsigned)((edges + 255) / 256);
   HENN_HIP(hipMemsetAsync(cnt, 0, sizeof(uint32_t) * (lo + 1), st));
   hipLaunchKernelGGL(k_indeg, dim3(eb), dim3(256), 0, st, res, edges, cnt);
-  exclusive_scan_u32(cnt, lo, off, st);
-  HENN_HIP(hipMemcpyAsync(cnt, off, sizeof(uint32_t) * lo, hipMemcpyDeviceToDevice, st));
+  exclusive_scan_u32(cnt, lo, off, cnt, bsum, st);
   hipLaunchKernelGGL(k_scatter_in, dim3(eb), dim3(256), 0, st, res, edges, R, lo, cnt, inl);
   const unsigned mb = (unsigned)((lo + 3) / 4);
   bool launched = false;
