@@ -604,6 +604,7 @@ __global__ __launch_bounds__(256) void k_half_rows(const float* vec, const float
 // the larger of the two (J + 1)-th has 2 (J + 1) values of the row at or
 // below it, and nothing beyond it is taken.  A list without
 // that bound would keep twice the values (the KS-th of its own half alone).
+// J = KS - 1: no common bound.
 template <int KS, int J>
 struct LaneList {
   float d[KS];
@@ -641,7 +642,7 @@ struct LaneList {
       d[0] = below ? nd : d[0];
     }
     n = 0;
-    tau = fminf(d[KS - 1], J + 1 < KS ? fmaxf(d[J], __shfl_xor(d[J], 32)) : INFINITY);
+    tau = J + 1 < KS ? fminf(d[KS - 1], fmaxf(d[J], __shfl_xor(d[J], 32))) : d[KS - 1];
   }
   // one 32-candidate block's values (acc[v]: candidate c0 + 8 (v >> 2) +
   // 4 h + (v & 3)); most blocks hold nothing for any lane, and of the others
@@ -697,17 +698,18 @@ struct LaneList {
 // norm is added when the list is written, so a step's arithmetic besides the
 // products is one minimum over the values and one compare.  Two independent
 // 32-candidate accumulators keep the products from waiting on each other.
-// 500,000 x 128: layer 0 in 75 ms (850 TFLOP/s of distance work) against 193
-// ms for the split form.  Matrix cores are busy 39% of the time and vector
+// 500,000 x 128: layer 0 in 78 ms (820 TFLOP/s of distance work) against 193
+// ms for the split form (R = 32).  Matrix cores are busy 39% of the time and vector
 // units 40% (staging and merging the values that enter a list);
 // two buffers and lists of 24 leave room for three blocks a CU, where three
 // buffers with two blocks took 85 ms and lists of 32 that take all their half
 // wants (no tau) 116 ms.
 constexpr int kHalfStep = 64;
-// 2 x 16 values bound a row's wants; at 500,000 x 128 the rows this leaves
-// unproven cost the next form 2 ms
-constexpr int kHalfKs = 24, kHalfJ = 15;
-
+// The R nearest of a row have to lie well below its bound to be proven: 2 x 16
+// values for R <= 16, and 2 x 20 above (with R = 32 and 2 x 16, 14% of the rows
+// of 1M x 128 stayed unproven and cost the next form 117 ms, against 30 ms and
+// 3% more in the tiles).
+constexpr int kHalfKs = 24, kHalfJ = 15, kHalfJ2 = 19;
 template <int S, int KS, int J>
 __global__ __launch_bounds__(256, 3) void k_gram_topk_h(const uint16_t* rows, int64_t size,
                                                         const float* norms, const float* yterm,
@@ -825,7 +827,7 @@ __global__ __launch_bounds__(256, 3) void k_gram_topk_h(const uint16_t* rows, in
 constexpr int kWideHRow = 8;
 // no common bound: with lists of 24 bounded by 2 x 16 values most rows of
 // 60,000 x 768 unit vectors (inner product) stayed unproven
-constexpr int kWideKs = 32, kWideJ = 31;
+constexpr int kWideKs = 32;
 constexpr int kWideHSlots = 128 * kWideHRow;  // one operand slice, a multiple of 64
 
 __global__ __launch_bounds__(256, 2) void k_knn_gram_wide_h(const uint16_t* rows, int64_t size,
@@ -845,7 +847,7 @@ __global__ __launch_bounds__(256, 2) void k_knn_gram_wide_h(const uint16_t* rows
   const bool l2 = metric == 0;
   const float f = l2 ? -2.0f : -1.0f;
   const float qn = (l2 && qvalid) ? norms[qrow] * s2 : 0.0f;
-  LaneList<kWideKs, kWideJ> list;
+  LaneList<kWideKs, kWideKs - 1> list;
   list.clear();
   uint2* cand = cand_all + wave * (kX3Cand * 64);
 
@@ -1791,6 +1793,7 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
 
   // FP16 rows: the scale takes the largest norm to 2^13 .. 2^14
   const bool half = gram == 0 && isfinite(nmax);
+  const int half_j = R <= 16 ? kHalfJ : kHalfJ2;  // of a list (LaneList)
   float s = 1.0f;
   HalfStats hs{0, 0};
   if (half) {
@@ -1833,12 +1836,16 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
                          norms, half_term, metric, s * s, sl_d, sl_i, b0, split_rows);
     } else if (form == Gram::kHalf) {
       switch (kp / 16) {
-#define HENN_H(S_)                                                                              \
-  case S_:                                                                                      \
-    hipLaunchKernelGGL((k_gram_topk_h<S_, kHalfKs, kHalfJ>), grid, dim3(256), 0, st, half_buf,     \
-                       size, norms, half_term, metric, s * s, sl_d, sl_i, b0, split_rows); \
+#define HENN_HJ(S_, J_)                                                                        \
+  hipLaunchKernelGGL((k_gram_topk_h<S_, kHalfKs, J_>), grid, dim3(256), 0, st, half_buf, size, \
+                     norms, half_term, metric, s * s, sl_d, sl_i, b0, split_rows)
+#define HENN_H(S_)                               \
+  case S_:                                       \
+    if (half_j == kHalfJ) HENN_HJ(S_, kHalfJ);   \
+    else HENN_HJ(S_, kHalfJ2);                   \
     break;
         HENN_H(1) HENN_H(2) HENN_H(3) HENN_H(4) HENN_H(5) HENN_H(6) HENN_H(7) HENN_H(8)
+#undef HENN_HJ
 #undef HENN_H
         default: throw HipError{hipErrorInvalidValue, "FP16 Gram: d <= 128"};
       }
@@ -1886,7 +1893,7 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
       e.coef_rel = 1.002f * 0.5f * e.mult * (2.0f * ratio + ratio * ratio) + c;
       e.gscale = 1.0f / (s * s);
       e.ks = wide ? kWideKs : kHalfKs;
-      e.j = wide ? kWideJ : kHalfJ;
+      e.j = wide ? kWideKs - 1 : half_j;
     } else {
       // FP32 tiles: 4 (dpad + 8) 2^-24 (|x'|^2 + |y'|^2)
       e.coef = form == Gram::kSplit ? x3_split_coef(dpad) : 4.0f * (float)(dpad + 8) * 0x1p-24f;

@@ -511,6 +511,22 @@ def test_fp16_gram_equals_fp32_gram_at_tile_edges(hn, n, d, metric, kind):
     assert np.array_equal(out[0], out[1])
 
 
+@pytest.mark.parametrize("n,d,metric", [(65, 128, 0), (2500, 100, 1), (4097, 24, 0),
+                                         (1500, 200, 0)])
+@pytest.mark.parametrize("degree", [15, 17, 32])
+def test_fp16_gram_lists_by_degree(hn, n, d, metric, degree):
+    """Degrees on both sides of the line where the lists' common bound deepens
+    (16 neighbours), and the largest: equal to FP32 tiles' graph, no tolerance."""
+    X = wl.gauss_mix(n, d, 5, 0.3, 45)
+    Xd = to_dev(X)
+    out = []
+    for gram in (0, 1):
+        idx = hn.henn_build(Xd, degree=degree, metric=metric, max_layers=0, gram=gram)
+        out.append(idx.export_layer(0)[1])
+        idx.free()
+    assert np.array_equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("d,metric", [(200, 0), (768, 1)])
 def test_wide_rows_end_to_end(hn, ho, d, metric):
     """Rows wider than 128 coordinates (K-sliced Gram build, 16-lane gathers):
