@@ -562,25 +562,36 @@ __global__ __launch_bounds__(256) void k_half_rows(const float* vec, const float
   float rm = 0.0f, ra = 0.0f;
   for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < size_pad;
        r += (int64_t)gridDim.x * 4) {
-    float r2 = 0.0f;
+    // the residual's square in the row's own units and in units of s: one of
+    // them stays in range where the other's terms fall below the smallest
+    // FP32 number (rows near 1e-19 and their residuals near 1e-23 in the
+    // first, rows far below the layer's largest in the second)
+    float r2 = 0.0f, r2s = 0.0f;
     for (int c = lane; c < ld; c += 64) {
       const float v =
           (r < size && c < dpad) ? vec[r * dpad + c] - (mean ? mean[c] : 0.0f) : 0.0f;
       const float sv = v * s;
       const _Float16 hv = fabsf(sv) < 0x1p-14f ? (_Float16)0.0f : (_Float16)sv;
       out[r * ld + c] = __builtin_bit_cast(uint16_t, hv);
-      const float d = v - (float)hv * inv;
+      const float d = v - (float)hv * inv, ds = sv - (float)hv;
       r2 = __builtin_fmaf(d, d, r2);
+      r2s = __builtin_fmaf(ds, ds, r2s);
     }
-    for (int m = 32; m > 0; m >>= 1) r2 += __shfl_xor(r2, m);
+    for (int m = 32; m > 0; m >>= 1) {
+      r2 += __shfl_xor(r2, m);
+      r2s += __shfl_xor(r2s, m);
+    }
     const float n = r < size ? norms[r] : 0.0f;
-    const float res = sqrtf(r2);
+    const float res = fmaxf(sqrtf(r2), sqrtf(r2s) * inv);
     if (lane == 0) {
       yterm[r] = r < size ? (metric == 0 ? n * s * s : 0.0f) : INFINITY;
       if (r < size) rres[r] = res;
     }
     if (res <= 3.0e38f) rm = fmaxf(rm, res);
+    // (a norm that vanished where the residual did not: no ratio bounds it
+    // but the trivial one)
     if (n > 0.0f && n <= 3.0e38f) ra = fmaxf(ra, res / sqrtf(n));
+    else if (n == 0.0f && res > 0.0f) ra = fmaxf(ra, 1.0f);
   }
   // one pair of atomics a block: one a wave took most of the time (10,000
   // rows: 110 us)

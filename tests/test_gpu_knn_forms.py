@@ -1,0 +1,54 @@
+"""The kNN build's Gram forms: what the proof of each shortlist rests on, and
+the order in which the forms take over from each other."""
+import numpy as np
+import pytest
+
+from gpu_util import to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hn():
+    import paper_2505_17368_amd as m
+    m.load_library()
+    return m
+
+
+def _layer0(hn, Xd, **kw):
+    idx = hn.henn_build(Xd, max_layers=0, **kw)
+    adj = idx.export_layer(0)[1]
+    idx.free()
+    return adj
+
+
+@pytest.mark.parametrize("d,scale", [(4, 1e-19), (8, 1e-19), (8, 3e-19), (8, 1.0), (8, 1e15)])
+def test_fp16_residuals_of_small_and_large_rows(hn, d, scale):
+    """Two tight groups far from the layer's mean, so that rows are near each
+    other against their norms.  At 1e-19 the squared FP16 residuals of the rows
+    are below the smallest FP32 number although the squared distances are not:
+    the proof has to hold all the same.  Checked against FP64: no neighbour
+    that was left out is nearer than the farthest listed one by more than the
+    canonical FP32 distance's own rounding (d <= 8 coordinates: each
+    difference within 2^-24, each square and sum within 2^-24 relative or half
+    a subnormal step, 2^-150), for both distances of the comparison."""
+    n, R = 3000, 16
+    g = np.random.default_rng(1)
+    u = g.standard_normal(d)
+    u /= np.linalg.norm(u)
+    sign = g.integers(0, 2, n) * 2 - 1
+    X = ((sign[:, None] * u + 0.05 / np.sqrt(d) * g.standard_normal((n, d))) * scale).astype(
+        np.float32)
+    adj = _layer0(hn, to_dev(X), degree=R)
+    assert (adj >= 0).all()
+    X64 = X.astype(np.float64)
+    bad = []
+    for r in range(n):
+        D = ((X64 - X64[r]) ** 2).sum(1)
+        D[r] = np.inf
+        true = np.partition(D, R - 1)[R - 1]
+        worst = D[adj[r]].max()
+        tol = 2 * (worst * (2 + d) * 2.0 ** -23 + d * 2.0 ** -150)
+        if worst > true + tol:
+            bad.append((r, worst, true))
+    assert not bad, f"{len(bad)} rows of {n} miss a nearer neighbour, first {bad[0]}"
