@@ -1210,7 +1210,7 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const float* vec, int64_t si
                                                     int nchunks, int metric, const float* sl_d,
                                                     const int32_t* sl_i, int splits,
                                                     const float* norms, GramErr err, int R,
-                                                    int32_t* adj, int32_t* fb_rows,
+                                                    int32_t* adj, uint32_t* fb_bits,
                                                     uint32_t* fb_count, const int32_t* row_list,
                                                     int64_t row0, int64_t n_rows) {
   __shared__ uint64_t keys[4][64];
@@ -1279,7 +1279,10 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const float* vec, int64_t si
     // multi-scale data pass here where (a) charges them the layer's largest.
     const float c = err.coef_rel;
     const bool proof_b = metric == 0 && exact_r * (1.0f + 3.0f * c) + 4.0f * c * nrow < cut;
-    if (!(proof_a || proof_b)) fb_rows[atomicAdd(fb_count, 1u)] = (int32_t)row;
+    if (!(proof_a || proof_b)) {
+      atomicOr(fb_bits + (row >> 5), 1u << (row & 31));
+      atomicAdd(fb_count, 1u);
+    }
   }
 }
 
@@ -1743,13 +1746,22 @@ void launch_root_gram(const float* Q, int64_t nq, int d, const RootAux& r, int d
 // Gram passes a layer's rows can take, cheapest first.
 enum class Gram { kHalf, kSplit, kFp32 };
 
-// Splits of the candidates for n_rows rows: about two 256-thread blocks fit a
-// CU, so 512 run at once.  The count with the shortest makespan, (rounds of
-// 512 blocks) x (candidates of a split + the 1,024 that filling its lists
-// costs about as much as), the fewest among equals; whole 128-candidate
-// tiles.  10,000 x 32: 79 blocks on 256 CUs took 1,142 us with the split
-// form's one pass over the layer.
-static int gram_splits(int64_t n_rows, int64_t size, int64_t* split_rows) {
+// How one Gram pass over n_rows rows of a layer is launched: splits of the
+// candidates (split_rows of them each), row blocks a launch, and the row
+// blocks of the pilot (0: none).
+struct GramPlan {
+  int splits;
+  int64_t split_rows, slice, pilot;
+};
+
+// Splits: about two 256-thread blocks fit a CU, so 512 run at once.  The count
+// with the shortest makespan, (rounds of 512 blocks) x (candidates of a split
+// + the 1,024 that filling its lists costs about as much as), the fewest among
+// equals; whole 128-candidate tiles.  10,000 x 32: 79 blocks on 256 CUs took
+// 1,142 us with the split form's one pass over the layer.
+//
+// Slices: very large layers report progress between launches.
+static GramPlan gram_plan(Gram form, int64_t n_rows, int64_t size, int dpad) {
   const int64_t blocks = (n_rows + 127) / 128, tiles = (size + 127) / 128;
   const int64_t most = std::min<int64_t>({32, tiles, std::max<int64_t>(1, (1 << 21) / n_rows)});
   int64_t splits = 1, best = -1;
@@ -1760,8 +1772,12 @@ static int gram_splits(int64_t n_rows, int64_t size, int64_t* split_rows) {
       splits = sp;
     }
   }
-  *split_rows = (tiles + splits - 1) / splits * 128;
-  return (int)((size + *split_rows - 1) / *split_rows);
+  GramPlan p;
+  p.split_rows = (tiles + splits - 1) / splits * 128;
+  p.splits = (int)((size + p.split_rows - 1) / p.split_rows);
+  p.slice = std::max<int64_t>(4096, (int64_t)(2e13 / ((double)size * dpad * 256.0)));
+  p.pilot = form == Gram::kHalf && blocks > 512 ? 256 : 0;
+  return p;
 }
 
 int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, int metric, int R,
@@ -1777,19 +1793,20 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
   const int64_t half_rows = gram == 0 ? size_pad : 0;
   // one allocation for what lives through the call: a dozen small ones cost
   // a layer of a few thousand rows as much as its tiles.  Rows left to the
-  // next pass: two lists used in turn, and their number.
+  // next pass: a bit each, their number, and their list.
   DevParts parts;
   const size_t at_norms = parts.add<float>(size), at_mean = parts.add<float>(dpad);
   const size_t at_partial = parts.add<float>(metric == 0 ? mean_scratch(size, dpad) : 0);
-  const size_t at_fa = parts.add<int32_t>(size), at_fb = parts.add<int32_t>(size);
+  const int64_t left_words = (size + 31) / 32;
+  const size_t at_list = parts.add<int32_t>(size), at_bits = parts.add<uint32_t>(left_words);
   const size_t at_count = parts.add<uint32_t>(1), at_stats = parts.add<HalfStats>(1);
   const size_t at_half = parts.add<uint16_t>(half_rows * ld);
   const size_t at_term = parts.add<float>(half_rows), at_rres = parts.add<float>(half_rows);
   DevBuf<uint8_t> work(parts.bytes());
   float* norms = reinterpret_cast<float*>(work.get() + at_norms);
   float* mean = metric == 0 ? reinterpret_cast<float*>(work.get() + at_mean) : nullptr;
-  int32_t* fb_a = reinterpret_cast<int32_t*>(work.get() + at_fa);
-  int32_t* fb_b = reinterpret_cast<int32_t*>(work.get() + at_fb);
+  int32_t* fb_list = reinterpret_cast<int32_t*>(work.get() + at_list);
+  uint32_t* fb_bits = reinterpret_cast<uint32_t*>(work.get() + at_bits);
   uint32_t* fb_count = reinterpret_cast<uint32_t*>(work.get() + at_count);
   HalfStats* stats = reinterpret_cast<HalfStats*>(work.get() + at_stats);
   uint16_t* half_buf = reinterpret_cast<uint16_t*>(work.get() + at_half);
@@ -1839,9 +1856,9 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
   // Gram tiles of one form over row blocks [b0, b0 + nbs) of the rows
   // (row_list, or all); the FP16 form takes no list
   auto launch_gram = [&](Gram form, int64_t b0, unsigned nbs, const int32_t* row_list,
-                         int64_t n_rows, int splits, int64_t split_rows, float* sl_d,
-                         int32_t* sl_i) {
-    const dim3 grid(nbs, (unsigned)splits);
+                         int64_t n_rows, const GramPlan& plan, float* sl_d, int32_t* sl_i) {
+    const dim3 grid(nbs, (unsigned)plan.splits);
+    const int64_t split_rows = plan.split_rows;
     if (form == Gram::kHalf && wide) {
       hipLaunchKernelGGL(k_knn_gram_wide_h, grid, dim3(256), 0, st, half_buf, size, kp,
                          norms, half_term, metric, s * s, sl_d, sl_i, b0, split_rows);
@@ -1913,16 +1930,16 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
     return e;
   };
   // re-rank and proof of the shortlists of rows [row0, row0 + n) (of
-  // row_list, or all); unproven rows are appended to out_rows
+  // row_list, or all); unproven rows are marked and counted
   auto rerank = [&](Gram form, const int32_t* row_list, int64_t row0, int64_t n, int splits,
-                    const float* sl_d, const int32_t* sl_i, int32_t* out_rows) {
+                    const float* sl_d, const int32_t* sl_i) {
     const unsigned nr = (unsigned)((n + 3) / 4);
     const GramErr err = err_of(form);
     bool launched = false;
 #define HENN_TRY(L, C)                                                                         \
   if (!launched && lpn == L && cpl == C) {                                                     \
     hipLaunchKernelGGL((k_knn_rerank<L, C>), dim3(nr), dim3(256), 0, st, vec, size, dpad,      \
-                       nchunks, metric, sl_d, sl_i, splits, norms, err, R, adj, out_rows,      \
+                       nchunks, metric, sl_d, sl_i, splits, norms, err, R, adj, fb_bits,       \
                        fb_count, row_list, row0, n);                                           \
     launched = true;                                                                           \
   }
@@ -1936,6 +1953,10 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
     HENN_HIP(hipStreamSynchronize(st));
     return n;
   };
+  auto clear_left = [&]() {
+    HENN_HIP(hipMemsetAsync(fb_count, 0, sizeof(uint32_t), st));
+    HENN_HIP(hipMemsetAsync(fb_bits, 0, sizeof(uint32_t) * left_words, st));
+  };
 
   // First pass, all rows.  Launched in slices of row blocks, so that very
   // large layers report progress (HENN_PROGRESS=1); the first slice of the
@@ -1944,28 +1965,27 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
   // once.
   Gram form = half ? Gram::kHalf : (!wide && gram == 0) ? Gram::kSplit : Gram::kFp32;
   const Gram second = (!wide && gram == 0) ? Gram::kSplit : Gram::kFp32;
-  HENN_HIP(hipMemsetAsync(fb_count, 0, sizeof(uint32_t), st));
+  clear_left();
   {
-    int64_t split_rows = 0;
-    const int splits = gram_splits(size, size, &split_rows);
-    const int64_t entries = size * splits * 2 * kShort;
+    GramPlan plan = gram_plan(form, size, size, dpad);
+    const int64_t entries = size * plan.splits * 2 * kShort;
     DevBuf<float> lists(2 * entries);  // values, then positions
     float* sl_d = lists.get();
     int32_t* sl_i = reinterpret_cast<int32_t*>(sl_d + entries);
     const int64_t nb = (size + 127) / 128;
     const bool progress = getenv("HENN_PROGRESS") != nullptr;
-    const int64_t slice =
-        std::max<int64_t>(4096, (int64_t)(2e13 / ((double)size * dpad * 256.0)));
     auto t_last = std::chrono::steady_clock::now();
     for (int64_t b0 = 0; b0 < nb;) {
-      const bool pilot = form == Gram::kHalf && b0 == 0 && nb > 512;
-      const int64_t nbs = std::min<int64_t>(pilot ? 256 : slice, nb - b0);
-      launch_gram(form, b0, (unsigned)nbs, nullptr, size, splits, split_rows, sl_d,
-                  sl_i);
-      rerank(form, nullptr, 128 * b0, std::min(128 * nbs, size - 128 * b0), splits, sl_d,
-             sl_i, fb_a);
+      const bool pilot = b0 == 0 && plan.pilot > 0;
+      const int64_t nbs = std::min(pilot ? plan.pilot : plan.slice, nb - b0);
+      launch_gram(form, b0, (unsigned)nbs, nullptr, size, plan, sl_d, sl_i);
+      rerank(form, nullptr, 128 * b0, std::min(128 * nbs, size - 128 * b0), plan.splits, sl_d,
+             sl_i);
       b0 += nbs;
-      if (pilot && (int64_t)left() * 4 > 128 * nbs) form = second;
+      if (pilot && (int64_t)left() * 4 > 128 * nbs) {
+        form = second;
+        plan = gram_plan(form, size, size, dpad);  // no more splits than before
+      }
       if (progress && b0 < nb) {
         HENN_HIP(hipStreamSynchronize(st));
         const auto now = std::chrono::steady_clock::now();
@@ -1978,28 +1998,31 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
     }
   }
   uint32_t nfb = left();
-  // the rows a pass could not prove run through the next form on just those
+  // The rows a pass could not prove run through the next form on just those
   // rows (128 of them share each pass over the layer, where the brute force
-  // below reads the whole layer once per row)
-  int32_t *from = fb_a, *to = fb_b;
+  // below reads the whole layer once per row).  They are listed in the layer's
+  // order: rows that are neighbours in it are often near each other, take the
+  // same candidates into their lists at the same tiles, and then cost a wave
+  // one pass over a list and not one each.  100,000 x 128 curve points, where
+  // nearly every row is listed: build 136.5 ms with the rows in the order in
+  // which they failed, 95.2 ms like this.
   auto retry = [&](Gram f) {
     if (nfb == 0) return;
-    HENN_HIP(hipMemsetAsync(fb_count, 0, sizeof(uint32_t), st));
-    int64_t split_rows = 0;
-    const int splits = gram_splits(nfb, size, &split_rows);
-    const int64_t entries = (int64_t)nfb * splits * 2 * kShort;
+    (void)compact_bitmap(fb_bits, size, fb_list, st);
+    clear_left();
+    const GramPlan plan = gram_plan(f, nfb, size, dpad);
+    const int64_t entries = (int64_t)nfb * plan.splits * 2 * kShort;
     DevBuf<float> lists(2 * entries);
     float* sl_d = lists.get();
     int32_t* sl_i = reinterpret_cast<int32_t*>(sl_d + entries);
-    launch_gram(f, 0, (unsigned)((nfb + 127) / 128), from, nfb, splits, split_rows, sl_d,
-                sl_i);
-    rerank(f, from, 0, nfb, splits, sl_d, sl_i, to);
+    launch_gram(f, 0, (unsigned)((nfb + 127) / 128), fb_list, nfb, plan, sl_d, sl_i);
+    rerank(f, fb_list, 0, nfb, plan.splits, sl_d, sl_i);
     nfb = left();
-    std::swap(from, to);
   };
   if (half) retry(second);
   if (gram == 0 && !wide) retry(Gram::kFp32);
   if (nfb > 0) {
+    (void)compact_bitmap(fb_bits, size, fb_list, st);
     const int G = 64 / lpn;
     const int rpad = R;
     int n2 = 1;
@@ -2009,7 +2032,7 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
 #define HENN_TRY(L, C)                                                                          \
   if (!launched && lpn == L && cpl == C) {                                                      \
     hipLaunchKernelGGL((k_knn_exact<L, C>), dim3(nfb), dim3(256), lds2, st, vec, size, dpad,    \
-                       nchunks, metric, from, R, rpad, adj);                                    \
+                       nchunks, metric, fb_list, R, rpad, adj);                                 \
     launched = true;                                                                            \
   }
     HENN_KNN_COMBOS(HENN_TRY)
