@@ -1754,23 +1754,37 @@ struct GramPlan {
   int64_t split_rows, slice, pilot;
 };
 
-// Splits: about two 256-thread blocks fit a CU, so 512 run at once.  The count
-// with the shortest makespan, (rounds of 512 blocks) x (candidates of a split
-// + the 1,024 that filling its lists costs about as much as), the fewest among
-// equals; whole 128-candidate tiles.  10,000 x 32: 79 blocks on 256 CUs took
-// 1,142 us with the split form's one pass over the layer.
+// Splits: about two 256-thread blocks fit a CU, so 512 run at once.  Every
+// split fills its own lists, at a cost that follows the data: each value that
+// enters a list costs a pass over it.
+//
+// The FP16 form, which a pilot keeps away from data that it does not suit,
+// takes the count with the shortest makespan, (rounds of 512 blocks) x
+// (candidates of a split + the 1,024 that filling its lists costs about as
+// much as), the fewest among equals; whole 128-candidate tiles.  10,000 x 32:
+// 79 blocks on 256 CUs took 1,142 us with one pass over the layer.
+//
+// The later forms get the rows that are left, and whole layers of multi-scale
+// data, where many values enter a list: they split only as far as it takes to
+// fill the chip once.  The makespan rule for them too / this one, builds with
+// R = 32: curve points 50,000 x 128 35.6 / 32.3 ms, 100,000 x 128 95.2 / 85.7
+// ms; mixture of 60,000 x 128 13.5 / 12.0 ms.
 //
 // Slices: very large layers report progress between launches.
 static GramPlan gram_plan(Gram form, int64_t n_rows, int64_t size, int dpad) {
   const int64_t blocks = (n_rows + 127) / 128, tiles = (size + 127) / 128;
   const int64_t most = std::min<int64_t>({32, tiles, std::max<int64_t>(1, (1 << 21) / n_rows)});
   int64_t splits = 1, best = -1;
-  for (int64_t sp = 1; sp <= most; ++sp) {
-    const int64_t span = (blocks * sp + 511) / 512 * ((tiles + sp - 1) / sp + 8);
-    if (best < 0 || span < best) {
-      best = span;
-      splits = sp;
+  if (form == Gram::kHalf) {
+    for (int64_t sp = 1; sp <= most; ++sp) {
+      const int64_t span = (blocks * sp + 511) / 512 * ((tiles + sp - 1) / sp + 8);
+      if (best < 0 || span < best) {
+        best = span;
+        splits = sp;
+      }
     }
+  } else {
+    splits = std::max<int64_t>(1, std::min(most, 512 / blocks));
   }
   GramPlan p;
   p.split_rows = (tiles + splits - 1) / splits * 128;
@@ -2408,3 +2422,18 @@ void repair_graph(const float* vec, int64_t size, int dpad, int nchunks, int met
 }
 
 }  // namespace henn
+
+extern "C" henn_status henn_testing_knn_plan(int32_t form, int64_t n_rows, int64_t n, int32_t d,
+                                             henn_testing_gram_plan* out) {
+  using namespace henn;
+  if (!out || form < 0 || form > 2 || n_rows < 1 || n < n_rows || d < 1 || d > 1024) {
+    set_error("kNN plan arguments");
+    return HENN_E_INVAL;
+  }
+  const GramPlan p = gram_plan((Gram)form, n_rows, n, (d + 7) / 8 * 8);
+  out->splits = p.splits;
+  out->split_rows = p.split_rows;
+  out->slice_blocks = p.slice;
+  out->pilot_blocks = p.pilot;
+  return HENN_OK;
+}

@@ -57,6 +57,13 @@ class SearchParams(ctypes.Structure):
                 ("workspace_bytes", ctypes.c_int64), ("query_ns", ctypes.c_void_p)]
 
 
+class GramPlan(ctypes.Structure):
+    """henn_testing_gram_plan (test-only)."""
+    _fields_ = [("splits", ctypes.c_int32), ("reserved", ctypes.c_int32),
+                ("split_rows", ctypes.c_int64), ("slice_blocks", ctypes.c_int64),
+                ("pilot_blocks", ctypes.c_int64)]
+
+
 class LayerInfo(ctypes.Structure):
     _fields_ = [("size", ctypes.c_int64), ("draws", ctypes.c_int64), ("eps", ctypes.c_double),
                 ("window", ctypes.c_int64), ("attempts", ctypes.c_int32),
@@ -150,9 +157,11 @@ def load_library(path: str = LIB_PATH):
                  "henn_server_submit", "henn_server_submit_batch", "henn_server_tick",
                  "henn_server_poll",
                  "henn_server_stats", "henn_nsw_insert", "henn_insert", "henn_delete",
-                 "henn_testing_fail_alloc_after"):
+                 "henn_testing_fail_alloc_after", "henn_testing_knn_plan"):
         getattr(lib, name).restype = ctypes.c_int
     lib.henn_testing_fail_alloc_after.argtypes = [ctypes.c_int64]
+    lib.henn_testing_knn_plan.argtypes = [ctypes.c_int32, ctypes.c_int64, ctypes.c_int64,
+                                          ctypes.c_int32, P(GramPlan)]
     _lib = lib
     return lib
 
@@ -170,6 +179,13 @@ def fail_alloc_after(n: int) -> None:
     """Test-only: the next n device allocations of the library succeed, later
     ones fail as out of memory; n < 0 turns the injector off."""
     _check(load_library().henn_testing_fail_alloc_after(int(n)))
+
+
+def knn_plan(form: int, n_rows: int, n: int, d: int) -> GramPlan:
+    """Test-only: how the kNN build launches one Gram pass (host-only)."""
+    out = GramPlan()
+    _check(load_library().henn_testing_knn_plan(form, n_rows, n, d, ctypes.byref(out)))
+    return out
 
 
 def last_error() -> str:
