@@ -34,9 +34,10 @@ extern "C" {
 henn_status henn_testing_fail_alloc_after(int64_t n);
 
 /* How the kNN build launches one Gram pass (form 0: FP16, 1: split BF16, 2:
- * FP32) over n_rows rows of a layer of n points in d dimensions: splits of the
- * candidates, candidates a split, 128-row blocks a launch, and the blocks of
- * the pilot that decides whether the FP16 form goes on (0: none).
+ * FP32) over n_rows rows of a layer of n points in d dimensions, for a graph of
+ * this degree: splits of the candidates, candidates a split, 128-row blocks a
+ * launch, and the blocks of the pilot that decides whether the FP16 form goes
+ * on (0: none).
  * Host-only. */
 typedef struct {
   int32_t splits;
@@ -44,7 +45,7 @@ typedef struct {
   int64_t split_rows, slice_blocks, pilot_blocks;
 } henn_testing_gram_plan;
 henn_status henn_testing_knn_plan(int32_t form, int64_t n_rows, int64_t n, int32_t d,
-                                  henn_testing_gram_plan *out);
+                                  int32_t degree, henn_testing_gram_plan *out);
 
 #ifdef __cplusplus
 }

@@ -66,8 +66,8 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // (the rows another form could not prove) and the shortlists go to
 // position i; otherwise rows 0 .. size - 1 in order (n_rows = size).
 // blockIdx.y: the split of the candidates this block takes (split_rows of
-// them, a multiple of the tile); row i's shortlist of split y is number
-// i * gridDim.y + y.
+// them, a multiple of the tile); the shortlist of split y of the launch's
+// i-th row (i = 0 for the first row of block0) is number i * gridDim.y + y.
 template <int KH, int KS>
 __global__ __launch_bounds__(256, 2) void k_gram_topk(const float* vec, int64_t size, int dpad,
                                                       const float* norms, const float* mean,
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(256, 2) void k_gram_topk(const float* vec, int64_t 
     cur ^= 1;
   }
   if (qvalid) {
-    const int64_t o = (qi * gridDim.y + blockIdx.y) * (2 * KS) + h * KS;
+    const int64_t o = ((qi - block0 * 128) * gridDim.y + blockIdx.y) * (2 * KS) + h * KS;
 #pragma unroll
     for (int j = 0; j < KS; ++j) {
       sl_d[o + j] = td[j];
@@ -516,7 +516,7 @@ __global__ __launch_bounds__(256, 2) void k_gram_topk_x3(const uint16_t* rows, i
   }
   merge();
   if (qvalid) {
-    const int64_t o = (qi * gridDim.y + blockIdx.y) * (2 * KS) + h * KS;
+    const int64_t o = ((qi - block0 * 128) * gridDim.y + blockIdx.y) * (2 * KS) + h * KS;
 #pragma unroll
     for (int j = 0; j < KS; ++j) {
       sl_d[o + j] = td[j];
@@ -717,9 +717,10 @@ struct LaneList {
 // wants (no tau) 116 ms.
 constexpr int kHalfStep = 64;
 // The R nearest of a row have to lie well below its bound to be proven: 2 x 16
-// values for R <= 16, and 2 x 20 above (with R = 32 and 2 x 16, 14% of the rows
-// of 1M x 128 stayed unproven and cost the next form 117 ms, against 30 ms and
-// 3% more in the tiles).
+// values a split for R <= 16, and 2 x 20 above, with two splits at least
+// (half_least_splits).  With R = 32, two splits and 2 x 16, 14% of the rows of
+// 1M x 128 stayed unproven and cost the next form 117 ms, against 30 ms and 3%
+// more in the tiles.
 constexpr int kHalfKs = 24, kHalfJ = 15, kHalfJ2 = 19;
 template <int S, int KS, int J>
 __global__ __launch_bounds__(256, 3) void k_gram_topk_h(const uint16_t* rows, int64_t size,
@@ -821,7 +822,7 @@ __global__ __launch_bounds__(256, 3) void k_gram_topk_h(const uint16_t* rows, in
   // the block's LDS is not given back with copies under way
   __builtin_amdgcn_s_waitcnt(0xF70);
   list.merge(cand, lane, qrow);
-  if (qvalid) list.store(sl_d, sl_i, qrow * gridDim.y + blockIdx.y, h, qn);
+  if (qvalid) list.store(sl_d, sl_i, (qrow - block0 * 128) * gridDim.y + blockIdx.y, h, qn);
 }
 
 // d > 128: GEMM-shaped.  A block owns 128 rows (32 a wave) and walks its
@@ -947,7 +948,7 @@ __global__ __launch_bounds__(256, 2) void k_knn_gram_wide_h(const uint16_t* rows
     slice_barrier();
   }
   list.merge(cand, lane, qrow);
-  if (qvalid) list.store(sl_d, sl_i, qrow * gridDim.y + blockIdx.y, h, qn);
+  if (qvalid) list.store(sl_d, sl_i, (qrow - block0 * 128) * gridDim.y + blockIdx.y, h, qn);
 }
 
 // Shortlist pass for rows wider than 128 coordinates (up to 1024), where
@@ -1136,7 +1137,7 @@ __global__ __launch_bounds__(256) void k_knn_gram_wide(const float* vec, int64_t
     }
   }
   if (qvalid) {
-    const int64_t o = (qi * gridDim.y + blockIdx.y) * (2 * kShort) + h * kShort;
+    const int64_t o = ((qi - block0 * 128) * gridDim.y + blockIdx.y) * (2 * kShort) + h * kShort;
     float* od = sl_d + o;
     int32_t* oi = sl_i + o;
 #pragma unroll
@@ -1216,7 +1217,7 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const float* vec, int64_t si
   __shared__ uint64_t keys[4][64];
   __shared__ int32_t cids[4][64];
   const int wave = threadIdx.x >> 6;
-  // shortlist i belongs to row row_list[i] (or row i)
+  // shortlist i belongs to row row_list[row0 + i] (or row row0 + i)
   const int64_t li = row0 + (int64_t)blockIdx.x * 4 + wave;
   if (li >= row0 + n_rows) return;
   const int64_t row = row_list ? (int64_t)row_list[li] : li;
@@ -1235,7 +1236,7 @@ __global__ __launch_bounds__(256) void k_knn_rerank(const float* vec, int64_t si
   float cut = INFINITY;
   uint64_t best = ~0ull;
   for (int sp = 0; sp < splits; ++sp) {
-    const int64_t o = (li * splits + sp) * (2 * kShort);
+    const int64_t o = ((li - row0) * splits + sp) * (2 * kShort);
     const float gv = sl_d[o + lane] * err.gscale;
     cut = fminf(cut, fminf(__shfl(gv, err.ks - 1), __shfl(gv, kShort + err.ks - 1)));
     cut = fminf(cut, fmaxf(__shfl(gv, err.j), __shfl(gv, kShort + err.j)));
@@ -1746,6 +1747,19 @@ void launch_root_gram(const float* Q, int64_t nq, int d, const RootAux& r, int d
 // Gram passes a layer's rows can take, cheapest first.
 enum class Gram { kHalf, kSplit, kFp32 };
 
+constexpr int64_t kListRows = 1 << 21;
+
+// Least splits of the FP16 form (d <= 128).  A split bounds a row by about
+// the 2 (J + 1) nearest that it holds, and the bound of all is the lowest, so
+// one split puts it near rank 44 of the layer and two near rank 88.  More than
+// 16 neighbours need the second: the R-th has to lie below the bound by twice
+// the error.  Mixtures of 128 coordinates, R = 32, one split / two: 130,000
+// points 30.3 / 15.5 ms a build, 262,144 77.0 / 36.9 ms, 1.2M 1144 / 485 ms
+// (2 to 24% of the rows proven / nearly all); 262,144 x 32 43.2 / 25.8 ms.
+// For 16 and fewer one is enough (R = 16, one / two: 65,000 x 128 uniform 5.3
+// / 6.2 ms, mixture 6.4 / 6.1 ms).  The wide form has no common bound.
+static int half_least_splits(int R, int dpad) { return dpad > 128 || R <= 16 ? 1 : 2; }
+
 // How one Gram pass over n_rows rows of a layer is launched: splits of the
 // candidates (split_rows of them each), row blocks a launch, and the row
 // blocks of the pilot (0: none).
@@ -1761,7 +1775,7 @@ struct GramPlan {
 // The FP16 form, which a pilot keeps away from data that it does not suit,
 // takes the count with the shortest makespan, (rounds of 512 blocks) x
 // (candidates of a split + the 1,024 that filling its lists costs about as
-// much as), the fewest among equals; whole 128-candidate tiles.  10,000 x 32:
+// much as), the fewest within 1 / 64 of it; whole 128-candidate tiles.  10,000 x 32:
 // 79 blocks on 256 CUs took 1,142 us with one pass over the layer.
 //
 // The later forms get the rows that are left, and whole layers of multi-scale
@@ -1770,15 +1784,24 @@ struct GramPlan {
 // R = 32: curve points 50,000 x 128 35.6 / 32.3 ms, 100,000 x 128 95.2 / 85.7
 // ms; mixture of 60,000 x 128 13.5 / 12.0 ms.
 //
-// Slices: very large layers report progress between launches.
-static GramPlan gram_plan(Gram form, int64_t n_rows, int64_t size, int dpad) {
+// Slices: a launch's lists are kept for its rows and splits only, at most
+// kListRows of them (1 GiB), and very large layers report progress between
+// launches.
+static GramPlan gram_plan(Gram form, int R, int64_t n_rows, int64_t size, int dpad) {
   const int64_t blocks = (n_rows + 127) / 128, tiles = (size + 127) / 128;
-  const int64_t most = std::min<int64_t>({32, tiles, std::max<int64_t>(1, (1 << 21) / n_rows)});
-  int64_t splits = 1, best = -1;
+  const int64_t most = std::min<int64_t>(32, tiles);
+  const int64_t report =
+      std::max<int64_t>(4096, (int64_t)(2e13 / ((double)size * dpad * 256.0)));
+  auto slice_of = [&](int64_t sp) { return std::min(report, kListRows / 128 / sp); };
+  int64_t splits = 1;
   if (form == Gram::kHalf) {
-    for (int64_t sp = 1; sp <= most; ++sp) {
-      const int64_t span = (blocks * sp + 511) / 512 * ((tiles + sp - 1) / sp + 8);
-      if (best < 0 || span < best) {
+    const int64_t least = std::min<int64_t>(most, half_least_splits(R, dpad));
+    int64_t best = -1;
+    for (int64_t sp = least; sp <= most; ++sp) {
+      const int64_t slice = slice_of(sp), whole = blocks / slice, rest = blocks - whole * slice;
+      const int64_t rounds = whole * ((slice * sp + 511) / 512) + (rest * sp + 511) / 512;
+      const int64_t span = rounds * ((tiles + sp - 1) / sp + 8);
+      if (best < 0 || span < best - best / 64) {
         best = span;
         splits = sp;
       }
@@ -1789,7 +1812,7 @@ static GramPlan gram_plan(Gram form, int64_t n_rows, int64_t size, int dpad) {
   GramPlan p;
   p.split_rows = (tiles + splits - 1) / splits * 128;
   p.splits = (int)((size + p.split_rows - 1) / p.split_rows);
-  p.slice = std::max<int64_t>(4096, (int64_t)(2e13 / ((double)size * dpad * 256.0)));
+  p.slice = slice_of(p.splits);
   p.pilot = form == Gram::kHalf && blocks > 512 ? 256 : 0;
   return p;
 }
@@ -1967,6 +1990,10 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
     HENN_HIP(hipStreamSynchronize(st));
     return n;
   };
+  // list entries of a pass over n_rows rows: those of its largest launch
+  auto list_entries = [&](const GramPlan& plan, int64_t n_rows) {
+    return std::min(n_rows, 128 * plan.slice) * plan.splits * 2 * kShort;
+  };
   auto clear_left = [&]() {
     HENN_HIP(hipMemsetAsync(fb_count, 0, sizeof(uint32_t), st));
     HENN_HIP(hipMemsetAsync(fb_bits, 0, sizeof(uint32_t) * left_words, st));
@@ -1981,12 +2008,12 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
   const Gram second = (!wide && gram == 0) ? Gram::kSplit : Gram::kFp32;
   clear_left();
   {
-    GramPlan plan = gram_plan(form, size, size, dpad);
-    const int64_t entries = size * plan.splits * 2 * kShort;
+    GramPlan plan = gram_plan(form, R, size, size, dpad);
+    const int64_t nb = (size + 127) / 128;
+    const int64_t entries = list_entries(plan, size);
     DevBuf<float> lists(2 * entries);  // values, then positions
     float* sl_d = lists.get();
     int32_t* sl_i = reinterpret_cast<int32_t*>(sl_d + entries);
-    const int64_t nb = (size + 127) / 128;
     const bool progress = getenv("HENN_PROGRESS") != nullptr;
     auto t_last = std::chrono::steady_clock::now();
     for (int64_t b0 = 0; b0 < nb;) {
@@ -1998,7 +2025,10 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
       b0 += nbs;
       if (pilot && (int64_t)left() * 4 > 128 * nbs) {
         form = second;
-        plan = gram_plan(form, size, size, dpad);  // no more splits than before
+        const GramPlan next = gram_plan(form, R, size, size, dpad);
+        plan = next;
+        // the lists hold a launch of the plan they were made for
+        plan.slice = std::min(next.slice, entries / (128 * next.splits * 2 * kShort));
       }
       if (progress && b0 < nb) {
         HENN_HIP(hipStreamSynchronize(st));
@@ -2024,13 +2054,17 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
     if (nfb == 0) return;
     (void)compact_bitmap(fb_bits, size, fb_list, st);
     clear_left();
-    const GramPlan plan = gram_plan(f, nfb, size, dpad);
-    const int64_t entries = (int64_t)nfb * plan.splits * 2 * kShort;
+    const GramPlan plan = gram_plan(f, R, nfb, size, dpad);
+    const int64_t entries = list_entries(plan, nfb), nb = ((int64_t)nfb + 127) / 128;
     DevBuf<float> lists(2 * entries);
     float* sl_d = lists.get();
     int32_t* sl_i = reinterpret_cast<int32_t*>(sl_d + entries);
-    launch_gram(f, 0, (unsigned)((nfb + 127) / 128), fb_list, nfb, plan, sl_d, sl_i);
-    rerank(f, fb_list, 0, nfb, plan.splits, sl_d, sl_i);
+    for (int64_t b0 = 0; b0 < nb; b0 += plan.slice) {
+      const int64_t nbs = std::min(plan.slice, nb - b0);
+      launch_gram(f, b0, (unsigned)nbs, fb_list, nfb, plan, sl_d, sl_i);
+      rerank(f, fb_list, 128 * b0, std::min(128 * nbs, (int64_t)nfb - 128 * b0), plan.splits, sl_d,
+             sl_i);
+    }
     nfb = left();
   };
   if (half) retry(second);
@@ -2424,13 +2458,14 @@ void repair_graph(const float* vec, int64_t size, int dpad, int nchunks, int met
 }  // namespace henn
 
 extern "C" henn_status henn_testing_knn_plan(int32_t form, int64_t n_rows, int64_t n, int32_t d,
-                                             henn_testing_gram_plan* out) {
+                                             int32_t degree, henn_testing_gram_plan* out) {
   using namespace henn;
-  if (!out || form < 0 || form > 2 || n_rows < 1 || n < n_rows || d < 1 || d > 1024) {
+  if (!out || form < 0 || form > 2 || n_rows < 1 || n < n_rows || d < 1 || d > 1024 ||
+      degree < 1 || degree > 32) {
     set_error("kNN plan arguments");
     return HENN_E_INVAL;
   }
-  const GramPlan p = gram_plan((Gram)form, n_rows, n, (d + 7) / 8 * 8);
+  const GramPlan p = gram_plan((Gram)form, degree, n_rows, n, (d + 7) / 8 * 8);
   out->splits = p.splits;
   out->split_rows = p.split_rows;
   out->slice_blocks = p.slice;

@@ -161,7 +161,7 @@ def load_library(path: str = LIB_PATH):
         getattr(lib, name).restype = ctypes.c_int
     lib.henn_testing_fail_alloc_after.argtypes = [ctypes.c_int64]
     lib.henn_testing_knn_plan.argtypes = [ctypes.c_int32, ctypes.c_int64, ctypes.c_int64,
-                                          ctypes.c_int32, P(GramPlan)]
+                                          ctypes.c_int32, ctypes.c_int32, P(GramPlan)]
     _lib = lib
     return lib
 
@@ -181,10 +181,10 @@ def fail_alloc_after(n: int) -> None:
     _check(load_library().henn_testing_fail_alloc_after(int(n)))
 
 
-def knn_plan(form: int, n_rows: int, n: int, d: int) -> GramPlan:
+def knn_plan(form: int, n_rows: int, n: int, d: int, degree: int) -> GramPlan:
     """Test-only: how the kNN build launches one Gram pass (host-only)."""
     out = GramPlan()
-    _check(load_library().henn_testing_knn_plan(form, n_rows, n, d, ctypes.byref(out)))
+    _check(load_library().henn_testing_knn_plan(form, n_rows, n, d, degree, ctypes.byref(out)))
     return out
 
 

@@ -52,3 +52,12 @@ def test_fp16_residuals_of_small_and_large_rows(hn, d, scale):
         if worst > true + tol:
             bad.append((r, worst, true))
     assert not bad, f"{len(bad)} rows of {n} miss a nearer neighbour, first {bad[0]}"
+
+
+def test_layers_of_several_launches(hn):
+    """More rows than one launch takes (4,096 blocks): the lists are kept for a
+    launch's rows only.  FP16 first and FP32 alone give the same graph."""
+    g = np.random.default_rng(3)
+    X = g.standard_normal((4096 * 128 + 5000, 8)).astype(np.float32)
+    Xd = to_dev(X)
+    assert np.array_equal(_layer0(hn, Xd, degree=17), _layer0(hn, Xd, degree=17, gram=1))
