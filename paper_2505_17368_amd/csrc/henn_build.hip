@@ -223,17 +223,25 @@ __global__ void k_compact(const uint32_t* bm, int64_t nwords, int64_t nbits, con
   }
 }
 
-int64_t compact_bitmap(const uint32_t* bitmap, int64_t s, int32_t* out_local, hipStream_t st) {
-  const int64_t nwords = (s + 31) / 32;
-  const int64_t nb = (nwords + kScanBlock - 1) / kScanBlock;
-  DevBuf<uint32_t> bsum_buf(nb + 1);
-  uint32_t* bsum = bsum_buf.get();
-  uint32_t* total = bsum + nb;
+int64_t compact_scratch(int64_t s) {
+  return ((s + 31) / 32 + kScanBlock - 1) / kScanBlock + 1;
+}
+
+uint32_t* launch_compact(const uint32_t* bitmap, int64_t s, int32_t* out, uint32_t* bsum,
+                         hipStream_t st) {
+  const int64_t nwords = (s + 31) / 32, nb = compact_scratch(s) - 1;
   hipLaunchKernelGGL(k_block_popc, dim3((unsigned)nb), dim3(kScanBlock), 0, st, bitmap, nwords,
                      bsum);
-  hipLaunchKernelGGL(k_scan_bsum, dim3(1), dim3(1024), 0, st, bsum, nb, total);
+  hipLaunchKernelGGL(k_scan_bsum, dim3(1), dim3(1024), 0, st, bsum, nb, bsum + nb);
   hipLaunchKernelGGL(k_compact, dim3((unsigned)nb), dim3(kScanBlock), 0, st, bitmap, nwords, s,
-                     bsum, out_local);
+                     bsum, out);
+  HENN_HIP(hipGetLastError());
+  return bsum + nb;
+}
+
+int64_t compact_bitmap(const uint32_t* bitmap, int64_t s, int32_t* out_local, hipStream_t st) {
+  DevBuf<uint32_t> bsum(compact_scratch(s));
+  const uint32_t* total = launch_compact(bitmap, s, out_local, bsum.get(), st);
   uint32_t h_total = 0;
   HENN_HIP(hipMemcpyAsync(&h_total, total, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
   HENN_HIP(hipStreamSynchronize(st));

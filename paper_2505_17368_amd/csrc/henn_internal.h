@@ -342,6 +342,11 @@ int64_t launch_halve(uint64_t seed, int layer, int attempt, int64_t s, int m, in
 void launch_draw_mark(uint64_t seed, int layer, int attempt, int64_t s, int64_t draws,
                       uint32_t* bitmap, hipStream_t st);
 int64_t compact_bitmap(const uint32_t* bitmap, int64_t s, int32_t* out_local, hipStream_t st);
+// The same without waiting; bsum: compact_scratch(s) words.  Returns the
+// count's place on the device.
+int64_t compact_scratch(int64_t s);
+uint32_t* launch_compact(const uint32_t* bitmap, int64_t s, int32_t* out, uint32_t* bsum,
+                         hipStream_t st);
 // out[0 .. n] (and out2[0 .. n - 1], unless null) = the exclusive sums of in;
 // bsum: scan_scratch(n) words.
 int64_t scan_scratch(int64_t n);

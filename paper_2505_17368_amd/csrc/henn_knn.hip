@@ -1766,6 +1766,11 @@ static int half_least_splits(int R, int dpad) { return dpad > 128 || R <= 16 ? 1
 struct GramPlan {
   int splits;
   int64_t split_rows, slice, pilot;
+  void split(int64_t sp, int64_t size) {
+    const int64_t tiles = (size + 127) / 128;
+    split_rows = (tiles + sp - 1) / sp * 128;
+    splits = (int)((size + split_rows - 1) / split_rows);
+  }
 };
 
 // Splits: about two 256-thread blocks fit a CU, so 512 run at once.  Every
@@ -1809,9 +1814,8 @@ static GramPlan gram_plan(Gram form, int R, int64_t n_rows, int64_t size, int dp
   } else {
     splits = std::max<int64_t>(1, std::min(most, 512 / blocks));
   }
-  GramPlan p;
-  p.split_rows = (tiles + splits - 1) / splits * 128;
-  p.splits = (int)((size + p.split_rows - 1) / p.split_rows);
+  GramPlan p{};
+  p.split(splits, size);
   p.slice = slice_of(p.splits);
   p.pilot = form == Gram::kHalf && blocks > 512 ? 256 : 0;
   return p;
@@ -1835,16 +1839,18 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
   const size_t at_norms = parts.add<float>(size), at_mean = parts.add<float>(dpad);
   const size_t at_partial = parts.add<float>(metric == 0 ? mean_scratch(size, dpad) : 0);
   const int64_t left_words = (size + 31) / 32;
-  const size_t at_list = parts.add<int32_t>(size), at_bits = parts.add<uint32_t>(left_words);
-  const size_t at_count = parts.add<uint32_t>(1), at_stats = parts.add<HalfStats>(1);
+  const size_t at_list = parts.add<int32_t>(size), at_left = parts.add<uint32_t>(1 + left_words);
+  const size_t at_scan = parts.add<uint32_t>(compact_scratch(size));
+  const size_t at_stats = parts.add<HalfStats>(1);
   const size_t at_half = parts.add<uint16_t>(half_rows * ld);
   const size_t at_term = parts.add<float>(half_rows), at_rres = parts.add<float>(half_rows);
   DevBuf<uint8_t> work(parts.bytes());
   float* norms = reinterpret_cast<float*>(work.get() + at_norms);
   float* mean = metric == 0 ? reinterpret_cast<float*>(work.get() + at_mean) : nullptr;
   int32_t* fb_list = reinterpret_cast<int32_t*>(work.get() + at_list);
-  uint32_t* fb_bits = reinterpret_cast<uint32_t*>(work.get() + at_bits);
-  uint32_t* fb_count = reinterpret_cast<uint32_t*>(work.get() + at_count);
+  uint32_t* fb_count = reinterpret_cast<uint32_t*>(work.get() + at_left);
+  uint32_t* fb_bits = fb_count + 1;
+  uint32_t* fb_scan = reinterpret_cast<uint32_t*>(work.get() + at_scan);
   HalfStats* stats = reinterpret_cast<HalfStats*>(work.get() + at_stats);
   uint16_t* half_buf = reinterpret_cast<uint16_t*>(work.get() + at_half);
   float* half_term = reinterpret_cast<float*>(work.get() + at_term);
@@ -1995,15 +2001,15 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
     return std::min(n_rows, 128 * plan.slice) * plan.splits * 2 * kShort;
   };
   auto clear_left = [&]() {
-    HENN_HIP(hipMemsetAsync(fb_count, 0, sizeof(uint32_t), st));
-    HENN_HIP(hipMemsetAsync(fb_bits, 0, sizeof(uint32_t) * left_words, st));
+    HENN_HIP(hipMemsetAsync(fb_count, 0, sizeof(uint32_t) * (1 + left_words), st));
   };
 
-  // First pass, all rows.  Launched in slices of row blocks, so that very
-  // large layers report progress (HENN_PROGRESS=1); the first slice of the
-  // FP16 form is a small one, and when it leaves more than a quarter of its
-  // rows unproven (multi-scale data), the other rows take the next form at
-  // once.
+  // First pass, all rows, launched in slices of row blocks.  The first slice of
+  // the FP16 form is its pilot, and when that leaves more than a quarter of its
+  // rows unproven (multi-scale data), the whole layer takes the next form from
+  // the start, and what that leaves the one after.  (Going on with the next
+  // form behind the pilot, and then once more over what either had left, took
+  // 100,000 x 128 curve points 86.7 ms, this takes 71.7.)
   Gram form = half ? Gram::kHalf : (!wide && gram == 0) ? Gram::kSplit : Gram::kFp32;
   const Gram second = (!wide && gram == 0) ? Gram::kSplit : Gram::kFp32;
   clear_left();
@@ -2016,8 +2022,8 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
     int32_t* sl_i = reinterpret_cast<int32_t*>(sl_d + entries);
     const bool progress = getenv("HENN_PROGRESS") != nullptr;
     auto t_last = std::chrono::steady_clock::now();
+    bool pilot = plan.pilot > 0;
     for (int64_t b0 = 0; b0 < nb;) {
-      const bool pilot = b0 == 0 && plan.pilot > 0;
       const int64_t nbs = std::min(pilot ? plan.pilot : plan.slice, nb - b0);
       launch_gram(form, b0, (unsigned)nbs, nullptr, size, plan, sl_d, sl_i);
       rerank(form, nullptr, 128 * b0, std::min(128 * nbs, size - 128 * b0), plan.splits, sl_d,
@@ -2025,11 +2031,13 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
       b0 += nbs;
       if (pilot && (int64_t)left() * 4 > 128 * nbs) {
         form = second;
-        const GramPlan next = gram_plan(form, R, size, size, dpad);
-        plan = next;
+        plan = gram_plan(form, R, size, size, dpad);
         // the lists hold a launch of the plan they were made for
-        plan.slice = std::min(next.slice, entries / (128 * next.splits * 2 * kShort));
+        plan.slice = std::min(plan.slice, entries / (128 * plan.splits * 2 * kShort));
+        clear_left();
+        b0 = 0;
       }
+      pilot = false;
       if (progress && b0 < nb) {
         HENN_HIP(hipStreamSynchronize(st));
         const auto now = std::chrono::steady_clock::now();
@@ -2052,7 +2060,7 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
   // which they failed, 95.2 ms like this.
   auto retry = [&](Gram f) {
     if (nfb == 0) return;
-    (void)compact_bitmap(fb_bits, size, fb_list, st);
+    launch_compact(fb_bits, size, fb_list, fb_scan, st);
     clear_left();
     const GramPlan plan = gram_plan(f, R, nfb, size, dpad);
     const int64_t entries = list_entries(plan, nfb), nb = ((int64_t)nfb + 127) / 128;
@@ -2067,10 +2075,10 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
     }
     nfb = left();
   };
-  if (half) retry(second);
+  if (form == Gram::kHalf) retry(second);
   if (gram == 0 && !wide) retry(Gram::kFp32);
   if (nfb > 0) {
-    (void)compact_bitmap(fb_bits, size, fb_list, st);
+    launch_compact(fb_bits, size, fb_list, fb_scan, st);
     const int G = 64 / lpn;
     const int rpad = R;
     int n2 = 1;

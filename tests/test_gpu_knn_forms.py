@@ -61,3 +61,24 @@ def test_layers_of_several_launches(hn):
     X = g.standard_normal((4096 * 128 + 5000, 8)).astype(np.float32)
     Xd = to_dev(X)
     assert np.array_equal(_layer0(hn, Xd, degree=17), _layer0(hn, Xd, degree=17, gram=1))
+
+
+@pytest.mark.parametrize("n,d,metric,degree", [(26_000, 16, 0, 16), (33_003, 40, 1, 32),
+                                               (33_001, 130, 0, 8), (66_001, 8, 0, 32),
+                                               (65_700, 140, 1, 5)])
+@pytest.mark.parametrize("kind", ["scales", "gauss", "mixed"])
+def test_pilot_keeps_or_rejects_the_fp16_form(hn, n, d, metric, degree, kind):
+    """Layers without a pilot, with a small one and with one of 256 blocks:
+    rows of one scale, where the FP16 form goes on; rows of very different
+    scales, where the next form takes the whole layer; and a pilot of one kind
+    before a layer of the other.  The graph is that of FP32 tiles alone, with no tolerance."""
+    g = np.random.default_rng(n + d)
+    X = g.standard_normal((n, d)).astype(np.float32)
+    scale = np.exp2(g.integers(-12, 13, size=(n, 1))).astype(np.float32)
+    if kind == "scales":
+        X *= scale
+    elif kind == "mixed":
+        X[n * 5 // 9:] *= scale[n * 5 // 9:]
+    Xd = to_dev(X)
+    kw = dict(degree=degree, metric=metric)
+    assert np.array_equal(_layer0(hn, Xd, **kw), _layer0(hn, Xd, gram=1, **kw))
