@@ -1789,6 +1789,15 @@ struct GramPlan {
 // R = 32: curve points 50,000 x 128 35.6 / 32.3 ms, 100,000 x 128 95.2 / 85.7
 // ms; mixture of 60,000 x 128 13.5 / 12.0 ms.
 //
+// Pilot: its rows say whether the FP16 form goes on.  It is one round of
+// blocks (three of this form fit a CU, two of the wide one), so that a layer
+// that goes on loses nothing by it, where at least half as many are left to
+// save.  Against a pilot of 256 blocks for layers of more than 512: curve
+// points 50,000 x 64 18.7 / 15.7 ms a build (R = 16), uniform ones 33,000 x 128 4.9 ms both.  (A sixteenth of the
+// blocks, 31 of 65,000 x 128, left the chip waiting for 1.2 ms; four blocks
+// with their candidates over 32 splits took 0.3 ms; 256 blocks of one split,
+// a third of a round, made 65,000 x 128 uniform points 6.4 -> 7.0 ms.)
+//
 // Slices: a launch's lists are kept for its rows and splits only, at most
 // kListRows of them (1 GiB), and very large layers report progress between
 // launches.
@@ -1817,7 +1826,8 @@ static GramPlan gram_plan(Gram form, int R, int64_t n_rows, int64_t size, int dp
   GramPlan p{};
   p.split(splits, size);
   p.slice = slice_of(p.splits);
-  p.pilot = form == Gram::kHalf && blocks > 512 ? 256 : 0;
+  const int64_t pilot = (dpad > 128 ? 512 : 768) / p.splits;
+  if (form == Gram::kHalf && blocks > 200 && 2 * blocks >= 3 * pilot) p.pilot = pilot;
   return p;
 }
 

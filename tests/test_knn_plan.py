@@ -50,3 +50,15 @@ def test_lists_of_a_launch_are_bounded(form, n, d):
     rows = min(n, 128 * p.slice_blocks)
     assert p.slice_blocks >= 1 and rows * p.splits <= 1 << 21
     assert p.pilot_blocks <= p.slice_blocks
+
+
+@pytest.mark.parametrize("d", [16, 128, 768])
+@pytest.mark.parametrize("n", [33_000, 50_000, 65_537, 100_000, 1_000_000, 10_000_000])
+def test_fp16_pass_over_a_large_layer_has_a_pilot(n, d):
+    """One round of blocks, at most two thirds of the layer, decides before the
+    whole layer is paid for; the other forms have none."""
+    p = hn.knn_plan(HALF, n, n, d, 32)
+    assert 0 < p.pilot_blocks <= -(-n // 128) * 2 // 3
+    assert p.pilot_blocks * p.splits <= 768
+    assert hn.knn_plan(SPLIT, n, n, d, 32).pilot_blocks == 0
+    assert hn.knn_plan(FP32, n, n, d, 32).pilot_blocks == 0
