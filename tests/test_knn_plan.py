@@ -62,3 +62,11 @@ def test_fp16_pass_over_a_large_layer_has_a_pilot(n, d):
     assert p.pilot_blocks * p.splits <= 768
     assert hn.knn_plan(SPLIT, n, n, d, 32).pilot_blocks == 0
     assert hn.knn_plan(FP32, n, n, d, 32).pilot_blocks == 0
+
+
+@pytest.mark.parametrize("n", [2_100_000, 5_000_000, 10_000_000])
+def test_very_large_layers_take_no_extra_splits(n):
+    """They have rounds enough: only the proof of more than 16 neighbours asks
+    for a second split."""
+    assert hn.knn_plan(HALF, n, n, 32, 16).splits == 1
+    assert hn.knn_plan(HALF, n, n, 32, 32).splits == 2
