@@ -1851,7 +1851,10 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
   const size_t at_list = parts.add<int32_t>(size), at_left = parts.add<uint32_t>(1 + left_words);
   const size_t at_scan = parts.add<uint32_t>(compact_scratch(size));
   const size_t at_stats = parts.add<HalfStats>(1);
-  const size_t at_half = parts.add<uint16_t>(half_rows * ld);
+  // (the FP16 rows of large layers by themselves, given back before the split
+  // rows are made: 272 and 512 bytes a row at d = 128)
+  const bool half_apart = half_rows * ld * (int64_t)sizeof(uint16_t) > (512ll << 20);
+  const size_t at_half = parts.add<uint16_t>(half_apart ? 0 : half_rows * ld);
   const size_t at_term = parts.add<float>(half_rows), at_rres = parts.add<float>(half_rows);
   DevBuf<uint8_t> work(parts.bytes());
   float* norms = reinterpret_cast<float*>(work.get() + at_norms);
@@ -1861,7 +1864,10 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
   uint32_t* fb_bits = fb_count + 1;
   uint32_t* fb_scan = reinterpret_cast<uint32_t*>(work.get() + at_scan);
   HalfStats* stats = reinterpret_cast<HalfStats*>(work.get() + at_stats);
-  uint16_t* half_buf = reinterpret_cast<uint16_t*>(work.get() + at_half);
+  std::unique_ptr<DevBuf<uint16_t>> half_own;
+  if (half_apart) half_own.reset(new DevBuf<uint16_t>(half_rows * ld));
+  uint16_t* half_buf =
+      half_apart ? half_own->get() : reinterpret_cast<uint16_t*>(work.get() + at_half);
   float* half_term = reinterpret_cast<float*>(work.get() + at_term);
   float* rres = reinterpret_cast<float*>(work.get() + at_rres);
   if (metric == 0)
@@ -1896,6 +1902,7 @@ int64_t build_knn_graph(const float* vec, int64_t size, int dpad, int nchunks, i
   std::unique_ptr<DevBuf<float>> split_term;
   auto need_split = [&]() {
     if (split_buf) return;
+    half_own.reset();  // no FP16 pass follows
     split_term.reset(new DevBuf<float>(size_pad));
     split_buf.reset(new DevBuf<uint16_t>(size_pad * 2 * kp));
     const int64_t n = size_pad * kp;
