@@ -1118,6 +1118,61 @@ static int device_cus() {
   return c;
 }
 
+// The caller's table size, or the base size for the beam width.
+static int base_vis_bits(const henn_index* idx, const henn_search_params* sp, int ef_need) {
+  return sp->vis_bits ? sp->vis_bits
+                      : default_vis_bits(ef_need, idx->n,
+                                         !(sp->flags & (HENN_SEARCH_VIS16 | HENN_SEARCH_VIS32)));
+}
+
+// The launch shape of a search whose arguments are checked: the caller's
+// fields, else those of a tuned entry, else the defaults for this number of
+// queries.  Reads a.ef_cap; a.vis_bits holds the caller's or the base table
+// size and becomes the chosen one, with a.vis_bytes.
+static henn_status pick_shape(const henn_index* idx, int64_t nq, const henn_search_params* sp,
+                              int ef_need, SearchArgs& a, LaunchShape& sh) {
+  // autotuned shape for this (storage, beam bucket, k bucket), if cached
+  int want_lpn = sp->lanes_per_vec, want_wpb = sp->waves_per_block;
+  bool want_pers = (sp->flags & HENN_SEARCH_PERSISTENT) != 0;
+  bool own_vis = sp->vis_bits != 0;  // the caller's or the tuner's table size
+  {
+    std::lock_guard<std::mutex> lk(const_cast<henn_index*>(idx)->tune_mu);
+    for (const TuneEntry& te : idx->tune) {
+      if (te.storage == idx->storage && te.ef_bucket == a.ef_cap &&
+          te.k_bucket == next_pow2(sp->k_max)) {
+        if (!want_lpn) want_lpn = te.lanes_per_vec;
+        if (!want_wpb) want_wpb = te.waves_per_block;
+        if (!own_vis) a.vis_bits = te.vis_bits;
+        own_vis = true;
+        if (te.persistent && !(sp->flags & HENN_SEARCH_PERSISTENT)) want_pers = true;
+        break;
+      }
+    }
+  }
+  int lpn = 0, cpl = 0;
+  pick_search_lanes(idx->storage, idx->nchunks, nq, device_cus(), want_lpn, &lpn, &cpl);
+  if (lpn == 0) return fail(HENN_E_INVAL, "lanes_per_vec not available for this dimension");
+  sh.lanes_per_vec = lpn;
+  sh.chunks_per_lane = cpl;
+  if (!own_vis && !(sp->flags & (HENN_SEARCH_VIS16 | HENN_SEARCH_VIS32 | HENN_SEARCH_EXACT_VISITED)))
+    a.vis_bits =
+        pick_vis_bits(search_waves(idx->storage, a.ef_cap, idx->nchunks, lpn, cpl), ef_need,
+                      idx->L[0].deg, idx->n, nq, device_cus(), a.vis_bits);
+  sh.vis_bits = a.vis_bits;
+  a.vis_bytes = (sp->flags & HENN_SEARCH_VIS32) ? 4 : vis_tag_bytes(idx->n, a.vis_bits);
+  if (a.vis_bytes == 1 && (sp->flags & HENN_SEARCH_VIS16)) a.vis_bytes = 2;
+  int wpb = want_wpb > 0 ? want_wpb : 4;
+  if (wpb != 1 && wpb != 2 && wpb != 4 && wpb != 8) return fail(HENN_E_INVAL, "waves_per_block");
+  const bool exact_vis = (sp->flags & HENN_SEARCH_EXACT_VISITED) != 0;
+  while (wpb > 1 &&
+         search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes, exact_vis) * wpb > 65536)
+    wpb /= 2;
+  sh.waves_per_block = wpb;
+  sh.persistent = want_pers;
+  sh.blocks = 0;
+  return HENN_OK;
+}
+
 // The search behind henn_search_batch and henn_search_batch_noalloc.
 // Scratch (the persistent work counter, then the root-scan keys) comes from
 // `fixed` when given (fixed_bytes must hold search_workspace_bytes), else from
@@ -1179,9 +1234,7 @@ static henn_status search_impl(const henn_index* idx, const float* Q, int64_t nq
     a.metric = idx->metric;
     if (sp->vis_bits != 0 && (sp->vis_bits < 8 || sp->vis_bits > 13))
       return fail(HENN_E_INVAL, "vis_bits in [8, 13]");
-    a.vis_bits = sp->vis_bits ? sp->vis_bits
-                              : default_vis_bits(ef_need, idx->n,
-                                                 !(sp->flags & (HENN_SEARCH_VIS16 | HENN_SEARCH_VIS32)));
+    a.vis_bits = base_vis_bits(idx, sp, ef_need);
     a.root_complete = idx->root_complete ? 1 : 0;
     a.out_ids = out_ids;
     a.out_dist = out_dist;
@@ -1193,48 +1246,13 @@ static henn_status search_impl(const henn_index* idx, const float* Q, int64_t nq
     if (!rows_addressable(a))
       return fail(HENN_E_UNSUPPORTED, "search needs n * ceil(d / 8) < 2^32");
 
-    // autotuned shape for this (storage, beam bucket, k bucket), if cached
-    int want_lpn = sp->lanes_per_vec, want_wpb = sp->waves_per_block;
-    bool want_pers = (sp->flags & HENN_SEARCH_PERSISTENT) != 0;
-    bool own_vis = sp->vis_bits != 0;  // the caller's or the tuner's table size
-    {
-      std::lock_guard<std::mutex> lk(const_cast<henn_index*>(idx)->tune_mu);
-      for (const TuneEntry& te : idx->tune) {
-        if (te.storage == idx->storage && te.ef_bucket == a.ef_cap &&
-            te.k_bucket == next_pow2(sp->k_max)) {
-          if (!want_lpn) want_lpn = te.lanes_per_vec;
-          if (!want_wpb) want_wpb = te.waves_per_block;
-          if (!own_vis) a.vis_bits = te.vis_bits;
-          own_vis = true;
-          if (te.persistent && !(sp->flags & HENN_SEARCH_PERSISTENT)) want_pers = true;
-          break;
-        }
-      }
-    }
     LaunchShape sh;
-    int lpn = 0, cpl = 0;
-    pick_search_lanes(idx->storage, idx->nchunks, nq, device_cus(), want_lpn, &lpn, &cpl);
-    if (lpn == 0) return fail(HENN_E_INVAL, "lanes_per_vec not available for this dimension");
-    sh.lanes_per_vec = lpn;
-    sh.chunks_per_lane = cpl;
-    if (!own_vis && !(sp->flags & (HENN_SEARCH_VIS16 | HENN_SEARCH_VIS32 | HENN_SEARCH_EXACT_VISITED)))
-      a.vis_bits = pick_vis_bits(idx->storage, cpl, ef_need, idx->L[0].deg, idx->n, nq,
-                                 device_cus(), a.vis_bits);
-    sh.vis_bits = a.vis_bits;
-    a.vis_bytes = (sp->flags & HENN_SEARCH_VIS32) ? 4 : vis_tag_bytes(idx->n, a.vis_bits);
-    if (a.vis_bytes == 1 && (sp->flags & HENN_SEARCH_VIS16)) a.vis_bytes = 2;
-    int wpb = want_wpb > 0 ? want_wpb : 4;
-    if (wpb != 1 && wpb != 2 && wpb != 4 && wpb != 8) return fail(HENN_E_INVAL, "waves_per_block");
-    const bool exact_vis = (sp->flags & HENN_SEARCH_EXACT_VISITED) != 0;
-    while (wpb > 1 &&
-           search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes, exact_vis) * wpb > 65536)
-      wpb /= 2;
-    sh.waves_per_block = wpb;
-    sh.persistent = want_pers;
-    sh.blocks = 0;
+    const henn_status picked = pick_shape(idx, nq, sp, ef_need, a, sh);
+    if (picked != HENN_OK) return picked;
 
     // scratch: the persistent work counter (256 B), the root-scan data, the
     // exact visited sets
+    const bool exact_vis = (sp->flags & HENN_SEARCH_EXACT_VISITED) != 0;
     const int rmode = root_mode(idx, sp);
     if (sh.persistent || rmode != 0 || exact_vis) {
       const int64_t need = search_workspace_bytes(idx, nq, sp);
@@ -1291,6 +1309,33 @@ static henn_status search_impl(const henn_index* idx, const float* Q, int64_t nq
     return HENN_OK;
   } catch (const HipError& e) {
     if (ws_owned) (void)hipFreeAsync(ws, st);
+    return from_hip(e);
+  }
+}
+
+henn_status henn_testing_search_shape(const henn_index* idx, int64_t nq,
+                                      const henn_search_params* sp,
+                                      henn_testing_shape* out) {
+  if (!idx || !sp || !out || nq < 1) return fail(HENN_E_INVAL, "search shape arguments");
+  const int ef_need = std::max(std::max(sp->k_max, sp->ef ? sp->ef_max : sp->ef_all), sp->ef_upper);
+  try {
+    SearchArgs a;
+    memset(&a, 0, sizeof(a));
+    a.ef_cap = next_pow2(ef_need);
+    a.vis_bits = base_vis_bits(idx, sp, ef_need);
+    LaunchShape sh;
+    const henn_status st = pick_shape(idx, nq, sp, ef_need, a, sh);
+    if (st != HENN_OK) return st;
+    out->lanes_per_vec = sh.lanes_per_vec;
+    out->waves_per_block = sh.waves_per_block;
+    out->vis_bits = sh.vis_bits;
+    out->persistent = sh.persistent ? 1 : 0;
+    out->lds_per_wave = (int32_t)search_lds_per_wave(
+        a.ef_cap, a.vis_bits, a.vis_bytes, (sp->flags & HENN_SEARCH_EXACT_VISITED) != 0);
+    out->register_waves = search_waves(idx->storage, a.ef_cap, idx->nchunks, sh.lanes_per_vec,
+                                       sh.chunks_per_lane);
+    return HENN_OK;
+  } catch (const HipError& e) {
     return from_hip(e);
   }
 }

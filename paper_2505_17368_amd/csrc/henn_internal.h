@@ -290,6 +290,8 @@ bool launch_search(int storage, const SearchArgs& a, const LaunchShape& s, hipSt
 template <int KIND, int NB>
 bool search_dispatch(const SearchArgs& a, const LaunchShape& s, hipStream_t st);
 template <int KIND, int NB>
+int waves_dispatch(int nchunks, int lpn, int cpl);
+template <int KIND, int NB>
 bool serve_dispatch(const SearchArgs& a, const ServeArgs& sv, const LaunchShape& sh,
                     hipStream_t st);
 
@@ -435,13 +437,18 @@ void pick_row_lanes(int nchunks, int* lpn, int* cpl);
 void pick_search_lanes(int storage, int nchunks, int64_t nq, int cus, int requested_lpn, int* lpn,
                        int* cpl);
 
+// Waves of the search kernel that a CU's registers hold.
+int search_waves(int storage, int ef_cap, int nchunks, int lpn, int cpl);
+
 // log2 of the visited table's entries for a search of nq queries, at least
-// `base`: the largest table (to 2^14) that costs no resident wave its LDS,
-// and no more than eight entries per possible evaluation of the beam.  A
-// larger table forgets fewer rows: 300,000 x 128, beam 84, 3315 evaluations
-// a query at 2^12 one-byte entries against 2995 distinct rows; 60,000 x 768,
-// beam 256, 8197 against 6210.
-int pick_vis_bits(int storage, int cpl, int ef_need, int deg, int64_t n, int64_t nq, int cus,
+// `base`: the largest table (to 2^14) that costs no resident wave its LDS
+// (register_waves: search_waves), and no more than eight entries per possible
+// evaluation of the beam.  A larger table forgets fewer rows: 300,000 x 128,
+// beam 84, 3315 evaluations a query at 2^12 one-byte entries against 2995
+// distinct rows; 60,000 x 768, beam 256, 8197 against 6210.  One that keeps
+// waves out costs more than it saves: 3,000 queries, 20,000 x 128 BF16, beam
+// 193, sized for 8 waves a CU of the 16 that fit, 1395 us against 825.
+int pick_vis_bits(int register_waves, int ef_need, int deg, int64_t n, int64_t nq, int cus,
                   int base);
 
 }  // namespace henn

@@ -30,6 +30,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <atomic>
 
 #include "henn_device.h"
 #include "henn_internal.h"
@@ -1478,6 +1479,22 @@ static void launch_one(const SearchArgs& a, const LaunchShape& sh, hipStream_t s
   }
 }
 
+// Waves of the search kernel of this shape that a CU's registers hold (asked
+// of the runtime once per kernel).
+template <int KIND, int LPN, int CPL, bool FULL, int NB>
+static int resident_waves() {
+  static std::atomic<int> waves{0};
+  int w = waves.load(std::memory_order_relaxed);
+  if (w == 0) {
+    auto kern = search_kernel<KIND, LPN, CPL, FULL, NB>(false);
+    HENN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &w, reinterpret_cast<const void*>(kern), 64, 0));
+    w = std::max(w, 4);
+    waves.store(w, std::memory_order_relaxed);
+  }
+  return w;
+}
+
 #define HENN_SEARCH_COMBOS(X) \
   X(1, 1) X(2, 1) X(4, 1) X(2, 2) X(4, 2) X(8, 1) X(2, 4) X(4, 4) X(8, 2) X(16, 1) X(8, 4) \
   X(16, 2) X(4, 8) X(16, 4) X(16, 8)
@@ -1495,6 +1512,17 @@ bool search_dispatch(const SearchArgs& a, const LaunchShape& sh, hipStream_t st)
   HENN_SEARCH_COMBOS(HENN_TRY)
 #undef HENN_TRY
   return false;
+}
+
+template <int KIND, int NB>
+int waves_dispatch(int nchunks, int lpn, int cpl) {
+#define HENN_TRY(LPN, CPL)                                               \
+  if (lpn == LPN && cpl == CPL)                                          \
+    return nchunks == LPN * CPL ? resident_waves<KIND, LPN, CPL, true, NB>() \
+                                : resident_waves<KIND, LPN, CPL, false, NB>();
+  HENN_SEARCH_COMBOS(HENN_TRY)
+#undef HENN_TRY
+  return 4;
 }
 
 template <int KIND, int NB>
@@ -1518,6 +1546,7 @@ bool serve_dispatch(const SearchArgs& a, const ServeArgs& sv, const LaunchShape&
 #define HENN_INST(PART, KIND, NB, EXT)                                                       \
   EXT template bool search_dispatch<KIND, NB>(const SearchArgs&, const LaunchShape&,         \
                                               hipStream_t);                                  \
+  EXT template int waves_dispatch<KIND, NB>(int, int, int);                                  \
   EXT template bool serve_dispatch<KIND, NB>(const SearchArgs&, const ServeArgs&,            \
                                              const LaunchShape&, hipStream_t);
 #if HENN_PART < 0 || HENN_PART == 1
@@ -1688,13 +1717,29 @@ void pick_search_lanes(int storage, int nchunks, int64_t nq, int cus, int reques
   pick_lanes_at_most(nchunks, requested_lpn, storage == kF32 || many ? 2 : 4, lpn, cpl);
 }
 
-int pick_vis_bits(int storage, int cpl, int ef_need, int deg, int64_t n, int64_t nq, int cus,
+template <int KIND>
+static int search_waves_kind(int ef_cap, int nchunks, int lpn, int cpl) {
+  switch (list_blocks(ef_cap)) {
+    case 2: return waves_dispatch<KIND, 2>(nchunks, lpn, cpl);
+    case 4: return waves_dispatch<KIND, 4>(nchunks, lpn, cpl);
+    default: return waves_dispatch<KIND, 0>(nchunks, lpn, cpl);
+  }
+}
+
+int search_waves(int storage, int ef_cap, int nchunks, int lpn, int cpl) {
+  switch (storage) {
+    case kF32: return search_waves_kind<kF32>(ef_cap, nchunks, lpn, cpl);
+    case kBF16: return search_waves_kind<kBF16>(ef_cap, nchunks, lpn, cpl);
+    default: return search_waves_kind<kFP8>(ef_cap, nchunks, lpn, cpl);
+  }
+}
+
+int pick_vis_bits(int register_waves, int ef_need, int deg, int64_t n, int64_t nq, int cus,
                   int base) {
-  // resident waves of a CU: what the registers of the shape leave room for,
-  // or what the batch gives it
-  const int simd = cpl >= 8 ? 2 : storage == kFP8 ? (cpl <= 2 ? 6 : 4) : cpl == 1 ? 5 : cpl == 2 ? 3 : 2;
-  const int64_t waves = std::min<int64_t>(4 * simd, (nq + cus - 1) / cus);
+  // resident waves of a CU: what the kernel's registers leave room for, or
+  // what the batch gives it
   const int ef_cap = next_pow2(ef_need);
+  const int64_t waves = std::min<int64_t>(register_waves, (nq + cus - 1) / cus);
   int bits = base;
   for (int b = base + 1; b <= 14 && (1ll << b) <= 8ll * ef_need * deg; ++b) {
     if ((int64_t)search_lds_per_wave(ef_cap, b, vis_tag_bytes(n, b)) * waves > 160 * 1024) break;

@@ -64,6 +64,12 @@ class GramPlan(ctypes.Structure):
                 ("pilot_blocks", ctypes.c_int64)]
 
 
+class SearchShape(ctypes.Structure):
+    """henn_testing_shape (test-only)."""
+    _fields_ = [(f, ctypes.c_int32) for f in ("lanes_per_vec", "waves_per_block", "vis_bits",
+                                              "persistent", "lds_per_wave", "register_waves")]
+
+
 class LayerInfo(ctypes.Structure):
     _fields_ = [("size", ctypes.c_int64), ("draws", ctypes.c_int64), ("eps", ctypes.c_double),
                 ("window", ctypes.c_int64), ("attempts", ctypes.c_int32),
@@ -157,11 +163,14 @@ def load_library(path: str = LIB_PATH):
                  "henn_server_submit", "henn_server_submit_batch", "henn_server_tick",
                  "henn_server_poll",
                  "henn_server_stats", "henn_nsw_insert", "henn_insert", "henn_delete",
-                 "henn_testing_fail_alloc_after", "henn_testing_knn_plan"):
+                 "henn_testing_fail_alloc_after", "henn_testing_knn_plan",
+                 "henn_testing_search_shape"):
         getattr(lib, name).restype = ctypes.c_int
     lib.henn_testing_fail_alloc_after.argtypes = [ctypes.c_int64]
     lib.henn_testing_knn_plan.argtypes = [ctypes.c_int32, ctypes.c_int64, ctypes.c_int64,
                                           ctypes.c_int32, ctypes.c_int32, P(GramPlan)]
+    lib.henn_testing_search_shape.argtypes = [vp, ctypes.c_int64, P(SearchParams),
+                                              P(SearchShape)]
     _lib = lib
     return lib
 
@@ -398,6 +407,15 @@ def workspace_size(index: HennIndex, nq: int, **kw) -> int:
     _check(load_library().henn_search_workspace_size(index.handle, nq, ctypes.byref(sp),
                                                      ctypes.byref(b)))
     return b.value
+
+
+def search_shape(index: HennIndex, nq: int, **kw) -> SearchShape:
+    """Test-only: the launch shape of a search of nq queries (see search_params)."""
+    sp = search_params(**kw)
+    out = SearchShape()
+    _check(load_library().henn_testing_search_shape(index.handle, nq, ctypes.byref(sp),
+                                                    ctypes.byref(out)))
+    return out
 
 
 def henn_search_batch(index: HennIndex, Q, k=10, ef=32, k_arr=None, ef_arr=None, k_max=None,
