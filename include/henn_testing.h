@@ -48,11 +48,13 @@ henn_status henn_testing_knn_plan(int32_t form, int64_t n_rows, int64_t n, int32
                                   int32_t degree, henn_testing_gram_plan *out);
 
 /* The launch shape henn_search_batch takes for nq queries with these params
- * on the current device: the bytes of LDS a wave uses and how many waves the
+ * on the current device: the 64-position blocks of the beam's list in
+ * registers (0: in LDS), the bytes of LDS a wave uses and how many waves the
  * kernel's registers let a CU hold. */
 typedef struct {
   int32_t lanes_per_vec, waves_per_block, vis_bits, persistent;
-  int32_t lds_per_wave, register_waves;
+  int32_t list_blocks, lds_per_wave, register_waves;
+  int32_t reserved;
 } henn_testing_shape;
 henn_status henn_testing_search_shape(const henn_index *idx, int64_t nq,
                                       const henn_search_params *sp, henn_testing_shape *out);

@@ -1154,18 +1154,20 @@ static henn_status pick_shape(const henn_index* idx, int64_t nq, const henn_sear
   if (lpn == 0) return fail(HENN_E_INVAL, "lanes_per_vec not available for this dimension");
   sh.lanes_per_vec = lpn;
   sh.chunks_per_lane = cpl;
-  if (!own_vis && !(sp->flags & (HENN_SEARCH_VIS16 | HENN_SEARCH_VIS32 | HENN_SEARCH_EXACT_VISITED)))
-    a.vis_bits =
-        pick_vis_bits(search_waves(idx->storage, a.ef_cap, idx->nchunks, lpn, cpl), ef_need,
-                      idx->L[0].deg, idx->n, nq, device_cus(), a.vis_bits);
+  const bool exact_vis = (sp->flags & HENN_SEARCH_EXACT_VISITED) != 0;
+  sh.list_blocks =
+      exact_vis ? 0 : pick_list_blocks(idx->storage, idx->nchunks, a.ef_cap, nq, device_cus());
+  if (!own_vis && !exact_vis && !(sp->flags & (HENN_SEARCH_VIS16 | HENN_SEARCH_VIS32)))
+    a.vis_bits = pick_vis_bits(
+        search_waves(idx->storage, sh.list_blocks, idx->nchunks, lpn, cpl), sh.list_blocks, ef_need,
+        idx->L[0].deg, idx->n, nq, device_cus(), a.vis_bits);
   sh.vis_bits = a.vis_bits;
   a.vis_bytes = (sp->flags & HENN_SEARCH_VIS32) ? 4 : vis_tag_bytes(idx->n, a.vis_bits);
   if (a.vis_bytes == 1 && (sp->flags & HENN_SEARCH_VIS16)) a.vis_bytes = 2;
   int wpb = want_wpb > 0 ? want_wpb : 4;
   if (wpb != 1 && wpb != 2 && wpb != 4 && wpb != 8) return fail(HENN_E_INVAL, "waves_per_block");
-  const bool exact_vis = (sp->flags & HENN_SEARCH_EXACT_VISITED) != 0;
   while (wpb > 1 &&
-         search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes, exact_vis) * wpb > 65536)
+         search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes, sh.list_blocks) * wpb > 65536)
     wpb /= 2;
   sh.waves_per_block = wpb;
   sh.persistent = want_pers;
@@ -1330,10 +1332,11 @@ henn_status henn_testing_search_shape(const henn_index* idx, int64_t nq,
     out->waves_per_block = sh.waves_per_block;
     out->vis_bits = sh.vis_bits;
     out->persistent = sh.persistent ? 1 : 0;
-    out->lds_per_wave = (int32_t)search_lds_per_wave(
-        a.ef_cap, a.vis_bits, a.vis_bytes, (sp->flags & HENN_SEARCH_EXACT_VISITED) != 0);
-    out->register_waves = search_waves(idx->storage, a.ef_cap, idx->nchunks, sh.lanes_per_vec,
-                                       sh.chunks_per_lane);
+    out->list_blocks = sh.list_blocks;
+    out->lds_per_wave =
+        (int32_t)search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes, sh.list_blocks);
+    out->register_waves = search_waves(idx->storage, sh.list_blocks, idx->nchunks,
+                                       sh.lanes_per_vec, sh.chunks_per_lane);
     return HENN_OK;
   } catch (const HipError& e) {
     return from_hip(e);

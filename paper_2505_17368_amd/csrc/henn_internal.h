@@ -247,6 +247,7 @@ struct LaunchShape {
   int chunks_per_lane;  // CPL
   int waves_per_block;
   int vis_bits;
+  int list_blocks;      // the beam's list (pick_list_blocks)
   bool persistent;
   int blocks;           // persistent grid size (0 = computed)
 };
@@ -269,15 +270,29 @@ inline int default_vis_bits(int ef_need, int64_t n, bool narrow_ok) {
   return b;
 }
 
-// Where a beam of capacity ef_cap keeps its list: 64-position blocks in
+// Where a beam of capacity ef_cap can keep its list: 64-position blocks in
 // registers, or 0 for LDS.  Two blocks a lane are four registers and four are
 // eight; past that the list's compares and lane moves would cost more than
 // the LDS form's searches.
 constexpr int list_blocks(int ef_cap) { return ef_cap <= 128 ? 2 : ef_cap <= 256 ? 4 : 0; }
 
-// Shared-memory bytes one wave needs for a given list capacity (exact: the
-// exact visited set, whose list is in LDS at every capacity).
-size_t search_lds_per_wave(int ef_cap, int vis_bits, int vis_bytes, bool exact = false);
+// Where a search of nq queries keeps it.  Four blocks shorten an expansion,
+// which is what a batch waits for that does not fill the chip; past eight
+// waves a CU their registers and instructions cost more than that gives, but
+// for FP32 rows of more than 64 coordinates (and rows of more than 128, where
+// every form waits for the rows).  Beam 140, us in registers / in LDS: 20,000
+// x 16 FP8, 100 queries 237 / 268, 1,000 285 / 293, 3,000 334 / 317, 21,000
+// 1514 / 1437; 20,000 x 128 BF16 420 / 439, 504 / 480, 617 / 563, 3244 / 2853;
+// 60,000 x 100 FP32 at 8,000 1371 / 1587.
+inline int pick_list_blocks(int storage, int nchunks, int ef_cap, int64_t nq, int cus) {
+  const int blocks = list_blocks(ef_cap);
+  const bool many = nq > 8ll * cus && nchunks <= (storage == 0 /* FP32 */ ? 8 : 16);
+  return blocks == 4 && many ? 0 : blocks;
+}
+
+// Shared-memory bytes one wave needs for a given list capacity and place
+// (blocks: list_blocks, 0 in LDS; the exact visited set's is always there).
+size_t search_lds_per_wave(int ef_cap, int vis_bits, int vis_bytes, int blocks);
 
 // Whether every layer's rows have 32-bit first-chunk indices
 // (size * chunks per row < 2^32), which the search kernel needs.
@@ -438,17 +453,17 @@ void pick_search_lanes(int storage, int nchunks, int64_t nq, int cus, int reques
                        int* cpl);
 
 // Waves of the search kernel that a CU's registers hold.
-int search_waves(int storage, int ef_cap, int nchunks, int lpn, int cpl);
+int search_waves(int storage, int blocks, int nchunks, int lpn, int cpl);
 
 // log2 of the visited table's entries for a search of nq queries, at least
 // `base`: the largest table (to 2^14) that costs no resident wave its LDS
-// (register_waves: search_waves), and no more than eight entries per possible
+// (register_waves: search_waves; blocks: the beam's list), and no more than eight entries per possible
 // evaluation of the beam.  A larger table forgets fewer rows: 300,000 x 128,
 // beam 84, 3315 evaluations a query at 2^12 one-byte entries against 2995
 // distinct rows; 60,000 x 768, beam 256, 8197 against 6210.  One that keeps
 // waves out costs more than it saves: 3,000 queries, 20,000 x 128 BF16, beam
 // 193, sized for 8 waves a CU of the 16 that fit, 1395 us against 825.
-int pick_vis_bits(int register_waves, int ef_need, int deg, int64_t n, int64_t nq, int cus,
-                  int base);
+int pick_vis_bits(int register_waves, int blocks, int ef_need, int deg, int64_t n, int64_t nq,
+                  int cus, int base);
 
 }  // namespace henn

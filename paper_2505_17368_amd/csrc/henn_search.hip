@@ -6,7 +6,7 @@
 // inter-layer edge (Def. HENN: the same point one layer below).
 //
 // The beam keeps one ascending list W of (distance, id, expanded) keys, in
-// registers up to a width of 256 and in LDS beyond, and repeatedly expands
+// registers or in LDS (pick_list_blocks), and repeatedly expands
 // the smallest unexpanded entry; this is the
 // two-heap SEARCH-LAYER of HNSW (the candidate set the paper relies on for
 // k > 1) in an equivalent form: the expansion sequence and the final list
@@ -43,9 +43,9 @@
 namespace henn {
 
 #if HENN_COMMON_PART
-size_t search_lds_per_wave(int ef_cap, int vis_bits, int vis_bytes, bool exact) {
+size_t search_lds_per_wave(int ef_cap, int vis_bits, int vis_bytes, int blocks) {
   const size_t vis = ((size_t)1 << vis_bits) * vis_bytes, list = (size_t)ef_cap * 8;
-  if (exact || list_blocks(ef_cap) == 0) return list + 64 * 8 * 2 + 64 * 4 * 2 + vis;
+  if (blocks == 0) return list + 64 * 8 * 2 + 64 * 4 * 2 + vis;
   // the list is in registers; its final copy takes the table's place
   return 64 * 8 + 64 * 4 * 3 + (vis > list ? vis : list);
 }
@@ -1394,7 +1394,7 @@ static __global__ void k_serve_admit(const float* staged_q, const int32_t* meta,
 
 template <int KIND, int LPN, int CPL, bool FULL, int NB>
 static void launch_serve_one(const SearchArgs& a, const ServeArgs& sv, int wpb, hipStream_t st) {
-  const size_t per_wave = search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes);
+  const size_t per_wave = search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes, NB);
   const unsigned blocks = (unsigned)((sv.n_active + wpb - 1) / wpb);
   auto kern = serve_kernel<KIND, LPN, CPL, FULL, NB>();
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * wpb), per_wave * wpb, st, a, sv,
@@ -1456,7 +1456,7 @@ static __global__ void k_reset_counter(uint32_t* c) { *c = 0u; }
 template <int KIND, int LPN, int CPL, bool FULL, int NB>
 static void launch_one(const SearchArgs& a, const LaunchShape& sh, hipStream_t st) {
   const bool exact = a.vis_exact != nullptr;
-  const size_t per_wave = search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes, exact);
+  const size_t per_wave = search_lds_per_wave(a.ef_cap, a.vis_bits, a.vis_bytes, NB);
   const int wpb = sh.waves_per_block;
   const size_t lds = per_wave * wpb;
   auto kern = search_kernel<KIND, LPN, CPL, FULL, NB>(exact);
@@ -1599,7 +1599,7 @@ bool rows_addressable(const SearchArgs& a) {
 
 template <int KIND>
 static bool launch_search_kind(const SearchArgs& a, const LaunchShape& s, hipStream_t st) {
-  switch (a.vis_exact ? 0 : list_blocks(a.ef_cap)) {
+  switch (s.list_blocks) {
     case 2: return search_dispatch<KIND, 2>(a, s, st);
     case 4: return search_dispatch<KIND, 4>(a, s, st);
     default: return search_dispatch<KIND, 0>(a, s, st);
@@ -1619,7 +1619,7 @@ bool launch_search(int storage, const SearchArgs& a, const LaunchShape& s, hipSt
 template <int KIND>
 static bool launch_serve_kind(const SearchArgs& a, const ServeArgs& sv, const LaunchShape& sh,
                               hipStream_t st) {
-  switch (list_blocks(a.ef_cap)) {
+  switch (sh.list_blocks) {
     case 2: return serve_dispatch<KIND, 2>(a, sv, sh, st);
     case 4: return serve_dispatch<KIND, 4>(a, sv, sh, st);
     default: return serve_dispatch<KIND, 0>(a, sv, sh, st);
@@ -1718,31 +1718,31 @@ void pick_search_lanes(int storage, int nchunks, int64_t nq, int cus, int reques
 }
 
 template <int KIND>
-static int search_waves_kind(int ef_cap, int nchunks, int lpn, int cpl) {
-  switch (list_blocks(ef_cap)) {
+static int search_waves_kind(int blocks, int nchunks, int lpn, int cpl) {
+  switch (blocks) {
     case 2: return waves_dispatch<KIND, 2>(nchunks, lpn, cpl);
     case 4: return waves_dispatch<KIND, 4>(nchunks, lpn, cpl);
     default: return waves_dispatch<KIND, 0>(nchunks, lpn, cpl);
   }
 }
 
-int search_waves(int storage, int ef_cap, int nchunks, int lpn, int cpl) {
+int search_waves(int storage, int blocks, int nchunks, int lpn, int cpl) {
   switch (storage) {
-    case kF32: return search_waves_kind<kF32>(ef_cap, nchunks, lpn, cpl);
-    case kBF16: return search_waves_kind<kBF16>(ef_cap, nchunks, lpn, cpl);
-    default: return search_waves_kind<kFP8>(ef_cap, nchunks, lpn, cpl);
+    case kF32: return search_waves_kind<kF32>(blocks, nchunks, lpn, cpl);
+    case kBF16: return search_waves_kind<kBF16>(blocks, nchunks, lpn, cpl);
+    default: return search_waves_kind<kFP8>(blocks, nchunks, lpn, cpl);
   }
 }
 
-int pick_vis_bits(int register_waves, int ef_need, int deg, int64_t n, int64_t nq, int cus,
-                  int base) {
+int pick_vis_bits(int register_waves, int blocks, int ef_need, int deg, int64_t n, int64_t nq,
+                  int cus, int base) {
   // resident waves of a CU: what the kernel's registers leave room for, or
   // what the batch gives it
   const int ef_cap = next_pow2(ef_need);
   const int64_t waves = std::min<int64_t>(register_waves, (nq + cus - 1) / cus);
   int bits = base;
   for (int b = base + 1; b <= 14 && (1ll << b) <= 8ll * ef_need * deg; ++b) {
-    if ((int64_t)search_lds_per_wave(ef_cap, b, vis_tag_bytes(n, b)) * waves > 160 * 1024) break;
+    if ((int64_t)search_lds_per_wave(ef_cap, b, vis_tag_bytes(n, b), blocks) * waves > 160 * 1024) break;
     bits = b;
   }
   return bits;

@@ -300,8 +300,11 @@ henn_status henn_server_create(const henn_index* idx, const henn_server_params* 
     s->shape.lanes_per_vec = lpn;
     s->shape.chunks_per_lane = cpl;
     s->shape.vis_bits = s->vis_bits;
+    s->shape.list_blocks = list_blocks(s->ef_cap);
     int wpb = want_wpb ? want_wpb : 4;
-    while (wpb > 1 && search_lds_per_wave(s->ef_cap, s->vis_bits, vis_tag_bytes(idx->n, s->vis_bits)) * wpb > 65536) wpb /= 2;
+    while (wpb > 1 && search_lds_per_wave(s->ef_cap, s->vis_bits, vis_tag_bytes(idx->n, s->vis_bits),
+                                          s->shape.list_blocks) * wpb > 65536)
+      wpb /= 2;
     s->shape.waves_per_block = wpb;
     const int64_t M = p->max_slots;
     if (p->pool_bytes < state_bytes(s, p->k_max, p->ef_max))

@@ -67,7 +67,8 @@ class GramPlan(ctypes.Structure):
 class SearchShape(ctypes.Structure):
     """henn_testing_shape (test-only)."""
     _fields_ = [(f, ctypes.c_int32) for f in ("lanes_per_vec", "waves_per_block", "vis_bits",
-                                              "persistent", "lds_per_wave", "register_waves")]
+                                              "persistent", "list_blocks", "lds_per_wave",
+                                              "register_waves", "reserved")]
 
 
 class LayerInfo(ctypes.Structure):

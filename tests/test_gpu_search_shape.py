@@ -64,6 +64,8 @@ def test_every_default_shape_gives_the_same_bits(hn, storage):
         sizes = (1, 257, 2048, 2049, 3072, 3073, 8192, 8193)
         shapes = [_shape(idx, nq, k=10, ef=ef) for nq in sizes]
         assert len({s.vis_bits for s in shapes}) > 1
+        assert {s.list_blocks for s in shapes} == ({2} if ef == 100 else
+                                                   {4} if storage == "f32" else {0, 4})
         if storage != "f32":
             assert len({s.lanes_per_vec for s in shapes}) > 1
         ref_i, ref_d = hn.henn_search_batch(idx, Qd[:8193], k=10, ef=ef)
