@@ -204,7 +204,10 @@ __device__ inline void list_load(RegList<NB>& L, int lane, int efl, int n, const
   for (int b = 0; b < NB; ++b) {
     const int i = 64 * b + lane - off;
     uint64_t v = i < 0 ? 1ull : ~0ull;
-    if (i >= 0 && i < n) v = in[i];
+    if (i >= 0 && i < n) {
+      v = in[i];
+      if ((v >> 32) == 0) v |= 1ull << 32;  // above the fillers (see gather_pass)
+    }
     L.ex[b] = ballot((v & 1ull) != 0);
     L.w[b] = (i >= 0 && i < n) ? wkey_strip(v) : v;
   }

@@ -111,7 +111,8 @@ struct henn_server {
   henn_server_params p{};
   hipStream_t st = nullptr;
   int d = 0, k_max = 0, ef_cap = 0, vis_bits = 0;
-  LaunchShape shape{};
+  LaunchShape shape{};  // of a step, but for the list's place
+  int cus = 0;
   // device
   float* slot_q = nullptr;
   int32_t *slot_k = nullptr, *slot_ef = nullptr, *slot_ids = nullptr, *cap = nullptr;
@@ -300,11 +301,12 @@ henn_status henn_server_create(const henn_index* idx, const henn_server_params* 
     s->shape.lanes_per_vec = lpn;
     s->shape.chunks_per_lane = cpl;
     s->shape.vis_bits = s->vis_bits;
-    s->shape.list_blocks = list_blocks(s->ef_cap);
+    s->cus = cus;
+    // room for the list's LDS form, which a tick of many requests may take
     int wpb = want_wpb ? want_wpb : 4;
-    while (wpb > 1 && search_lds_per_wave(s->ef_cap, s->vis_bits, vis_tag_bytes(idx->n, s->vis_bits),
-                                          s->shape.list_blocks) * wpb > 65536)
-      wpb /= 2;
+    const size_t lds = search_lds_per_wave(s->ef_cap, s->vis_bits,
+                                           vis_tag_bytes(idx->n, s->vis_bits), 0);
+    while (wpb > 1 && lds * wpb > 65536) wpb /= 2;
     s->shape.waves_per_block = wpb;
     const int64_t M = p->max_slots;
     if (p->pool_bytes < state_bytes(s, p->k_max, p->ef_max))
@@ -616,7 +618,10 @@ henn_status henn_server_tick(henn_server* s, int32_t* n_active_out) {
     sv.done_count = s->done_d + c;
     sv.done_clear = s->done_d + (c ^ 1);
     sv.done_rows = s->rows_d + (int64_t)c * s->p.max_slots * (1 + 2 * s->k_max);
-    if (!launch_serve_step(idx->storage, a, sv, s->shape, s->st))
+    // a request's saved state is the same whichever form a tick takes
+    LaunchShape sh = s->shape;
+    sh.list_blocks = pick_list_blocks(idx->storage, idx->nchunks, s->ef_cap, n_active, s->cus);
+    if (!launch_serve_step(idx->storage, a, sv, sh, s->st))
       return srv_fail(HENN_E_UNSUPPORTED, "no serving kernel for this shape");
     HENN_HIP(hipGetLastError());
     // the count follows the step on the stream; the next tick (or a drain)

@@ -237,3 +237,34 @@ def test_upper_layer_beam_wider_than_the_request_list():
         assert np.array_equal(got[j][0], ref_i[j]), j
         assert np.array_equal(got[j][1].view(np.uint32), ref_d[j].view(np.uint32)), j
     idx.free()
+
+
+def test_list_changes_its_place_while_requests_are_in_flight(setup):
+    """Beams of 129 to 256: a tick of many requests (over eight a CU) keeps the
+    lists in LDS, one of few in registers.  Requests that are saved under one
+    form and go on under the other return what a plain search returns."""
+    hn, X, Q, idx = setup
+    import torch
+    line = 8 * torch.cuda.get_device_properties(0).multi_processor_count
+    n = line + 700
+    Qm = wl.uniform(n, 32, 61)
+    rng = np.random.default_rng(9)
+    ks = rng.choice([1, 10], size=n).astype(np.int32)
+    efs = rng.choice([16, 60, 130, 200], size=n).astype(np.int32)
+    srv = hn.Server(idx, max_slots=n, pool_bytes=64 << 20, k_max=10, ef_max=200,
+                    steps_per_tick=7)
+    srv.submit_batch(Qm, ks, efs, np.arange(n, dtype=np.int64))
+    got, active = {}, []
+    while len(got) < n:
+        active.append(srv.tick())
+        for t, i, d in zip(*srv.poll()):
+            got[int(t)] = (i.copy(), d.copy())
+        assert len(active) < 100000
+    assert max(active) > line and any(0 < a <= line for a in active)
+    gi, gd = hn.henn_search_batch(idx, to_dev(Qm), k_arr=to_dev(ks), ef_arr=to_dev(efs), k_max=10,
+                                  ef_max=200)
+    gi, gd = gi.cpu().numpy(), gd.cpu().numpy()
+    for j in range(n):
+        assert np.array_equal(got[j][0], gi[j]), j
+        assert np.array_equal(got[j][1].view(np.uint32), gd[j].view(np.uint32)), j
+    srv.close()
