@@ -261,7 +261,9 @@ henn_status henn_search_batch_noalloc(const henn_index *idx, const float *Q, int
  * given search parameters, writes *sp with the tuned fields set into
  * *tuned (may be NULL), and caches the choice in the index for later calls
  * whose tuned fields are 0 and whose storage, beam-width bucket and k_max
- * bucket match.  Results never depend on the shape (every shape computes the
+ * bucket match.  Where the shape of an untuned call, or its visited table,
+ * is faster than every one tried, the index keeps that (it follows the number
+ * of queries of each call), and *tuned still holds the best one tried.  Results never depend on the shape (every shape computes the
  * same canonical distances), only the speed does.
  *   Q: device FP32 [nq][d] calibration queries (nq >= 1); outputs are
  *   scratch allocated inside.  Synchronous on hip_stream.
@@ -322,7 +324,8 @@ typedef struct {
   int32_t lanes_per_vec;  /* 0 = the shape henn_autotune chose for this index and
                              storage (its beam bucket first), else the default */
   int32_t waves_per_block;
-  int32_t vis_bits;       /* 0 = by beam width, as henn_search_batch chooses */
+  int32_t vis_bits;       /* 0 = by beam width: 2^10 / 2^11 / 2^12 entries for beams to 64 /
+                             256 / 2048, one more bit where its tags take one byte */
 } henn_server_params;
 
 typedef struct {

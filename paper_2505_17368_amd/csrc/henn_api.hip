@@ -1135,15 +1135,17 @@ static henn_status pick_shape(const henn_index* idx, int64_t nq, const henn_sear
   int want_lpn = sp->lanes_per_vec, want_wpb = sp->waves_per_block;
   bool want_pers = (sp->flags & HENN_SEARCH_PERSISTENT) != 0;
   bool own_vis = sp->vis_bits != 0;  // the caller's or the tuner's table size
-  {
+  if (!(sp->flags & kSearchUntuned)) {
     std::lock_guard<std::mutex> lk(const_cast<henn_index*>(idx)->tune_mu);
     for (const TuneEntry& te : idx->tune) {
       if (te.storage == idx->storage && te.ef_bucket == a.ef_cap &&
           te.k_bucket == next_pow2(sp->k_max)) {
         if (!want_lpn) want_lpn = te.lanes_per_vec;
         if (!want_wpb) want_wpb = te.waves_per_block;
-        if (!own_vis) a.vis_bits = te.vis_bits;
-        own_vis = true;
+        if (!own_vis && te.vis_bits) {
+          a.vis_bits = te.vis_bits;
+          own_vis = true;
+        }
         if (te.persistent && !(sp->flags & HENN_SEARCH_PERSISTENT)) want_pers = true;
         break;
       }
@@ -1467,10 +1469,25 @@ henn_status henn_autotune(henn_index* idx, const float* Q, int64_t nq,
         if (t < bt) { bt = t; bestp = q; }
       }
     }
+    // 3) the untuned shape, and the winner with the default table: that one
+    //    follows the number of queries and goes past the swept sizes, so an
+    //    index keeps it where no swept shape is faster
+    henn_search_params keep = bestp;
+    for (int all = 0; all < 2; ++all) {
+      henn_search_params q = bestp;
+      q.flags |= kSearchUntuned;
+      q.vis_bits = 0;
+      if (all) {
+        q.lanes_per_vec = q.waves_per_block = 0;
+        q.flags &= ~HENN_SEARCH_PERSISTENT;
+      }
+      const float t = time_of(q);
+      if (t < bt) { bt = t; keep = q; }
+    }
     const int ef_need = std::max(std::max(sp->k_max, sp->ef ? sp->ef_max : sp->ef_all), sp->ef_upper);
-    TuneEntry te{idx->storage, next_pow2(ef_need), next_pow2(sp->k_max), bestp.lanes_per_vec,
-                 bestp.waves_per_block, bestp.vis_bits,
-                 (bestp.flags & HENN_SEARCH_PERSISTENT) ? 1 : 0};
+    TuneEntry te{idx->storage, next_pow2(ef_need), next_pow2(sp->k_max), keep.lanes_per_vec,
+                 keep.waves_per_block, keep.vis_bits,
+                 (keep.flags & HENN_SEARCH_PERSISTENT) ? 1 : 0};
     {
       std::lock_guard<std::mutex> lk(idx->tune_mu);
       bool found = false;

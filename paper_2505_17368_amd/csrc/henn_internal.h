@@ -87,7 +87,11 @@ struct RootShortlist {
 int64_t root_shortlist_bytes(int64_t nq, int kp);
 RootShortlist root_shortlist_at(void* base, int64_t nq, int kp);
 
+// A search flag of the library's own: take no tuned entry.
+constexpr uint32_t kSearchUntuned = 1u << 31;
+
 // One autotuned launch shape, valid for a (storage, beam bucket, k bucket).
+// Fields that are 0 are left to the defaults for the number of queries.
 struct TuneEntry {
   int storage, ef_bucket, k_bucket;
   int lanes_per_vec, waves_per_block, vis_bits, persistent;

@@ -75,3 +75,33 @@ def test_every_default_shape_gives_the_same_bits(hn, storage):
             assert np.array_equal(d.cpu().numpy().view(np.uint32),
                                   ref_d[:nq].cpu().numpy().view(np.uint32)), (ef, nq)
     idx.free()
+
+
+@pytest.mark.parametrize("n,d,storage,nq,ef", [(20_000, 128, "f32", 2000, 250),
+                                               (20_000, 40, "fp8", 64, 500),
+                                               (5000, 32, "bf16", 500, 64)])
+def test_tuned_index_keeps_the_best_tried_or_the_default(hn, n, d, storage, nq, ef):
+    """What a tuned index runs is either the shape the tuner returns or, in its
+    table or as a whole, the untuned shape; other beam widths stay untuned."""
+    X = wl.uniform(n, d, 71)
+    Qd = to_dev(wl.uniform(nq, d, 72))
+    idx = hn.henn_build(to_dev(X), degree=24, max_degree=48, graph="knn_sym", storage=storage)
+
+    def fields(s):
+        return s.lanes_per_vec, s.waves_per_block, s.vis_bits, bool(s.persistent)
+
+    plain = fields(_shape(idx, nq, k=10, ef=ef))
+    other = fields(_shape(idx, nq, k=10, ef=8 * ef if ef <= 256 else 16))
+    ref_i, ref_d = hn.henn_search_batch(idx, Qd, k=10, ef=ef)
+    t = hn.henn_autotune(idx, Qd, k=10, ef=ef)
+    tuned = t["lanes_per_vec"], t["waves_per_block"], t["vis_bits"], t["persistent"]
+    assert 8 <= t["vis_bits"] <= 12
+    own_table = fields(_shape(idx, nq, k=10, ef=ef, lanes_per_vec=t["lanes_per_vec"],
+                              waves_per_block=t["waves_per_block"], persistent=t["persistent"]))
+    now = fields(_shape(idx, nq, k=10, ef=ef))
+    assert now in (plain, tuned, own_table)
+    assert fields(_shape(idx, nq, k=10, ef=8 * ef if ef <= 256 else 16)) == other
+    i, dd = hn.henn_search_batch(idx, Qd, k=10, ef=ef)
+    assert np.array_equal(i.cpu().numpy(), ref_i.cpu().numpy())
+    assert np.array_equal(dd.cpu().numpy().view(np.uint32), ref_d.cpu().numpy().view(np.uint32))
+    idx.free()
