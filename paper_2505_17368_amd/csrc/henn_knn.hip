@@ -1786,10 +1786,11 @@ struct GramPlan {
 // 2% more of them took 2.1M x 32 uniform points 601 ms against 547.
 //
 // The later forms get the rows that are left, and whole layers of multi-scale
-// data, where many values enter a list: they split only as far as it takes to
-// fill the chip once.  The makespan rule for them too / this one, builds with
-// R = 32: curve points 50,000 x 128 35.6 / 32.3 ms, 100,000 x 128 95.2 / 85.7
-// ms; mixture of 60,000 x 128 13.5 / 12.0 ms.
+// data, where many values enter a list: one split as soon as there is a block
+// for every CU, else four rounds of blocks.  Curve points of 128 coordinates,
+// R = 32, ms a build by splits of the split-BF16 pass: 118 blocks 11.1 / 9.6 /
+// 8.7 / 8.0 with 1 / 3 / 5 / 12, 196 blocks 17.2 / 15.2 / 14.4 / 13.5; 391
+// blocks 30.1 / 30.9 / 36.8 / 35.1, 782 blocks 70.1 / 74.1 / 79.4 / 90.5.
 //
 // Pilot: its rows say whether the FP16 form goes on.  It is one round of
 // blocks (three of this form fit a CU, two of the wide one), so that a layer
@@ -1819,7 +1820,7 @@ static GramPlan gram_plan(Gram form, int R, int64_t n_rows, int64_t size, int dp
       }
     }
   } else {
-    splits = std::max<int64_t>(1, std::min(most, 512 / blocks));
+    splits = blocks < 256 ? std::min(most, 2048 / blocks) : 1;
   }
   GramPlan p{};
   p.split(splits, size);

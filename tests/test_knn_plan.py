@@ -23,12 +23,12 @@ def test_splits_cover_the_layer(form, n, part):
 @pytest.mark.parametrize("n", SIZES)
 @pytest.mark.parametrize("part", [1, 3, 10])
 def test_later_forms_split_only_to_fill_the_chip(form, n, part):
-    """Each split fills lists of its own: a pass whose blocks fill the chip
-    (512 at once) is not split, and the others not past one round."""
+    """Each split fills lists of its own: a pass with a block for every CU is
+    not split, and the others to four rounds of 512 blocks at most."""
     rows = max(1, n // part)
     blocks = -(-rows // 128)
     p = hn.knn_plan(form, rows, n, 128, 32)
-    assert p.splits * blocks <= max(512, blocks)
+    assert p.splits == 1 if blocks >= 256 else p.splits * blocks <= 2048
 
 
 @pytest.mark.parametrize("degree", [17, 24, 32])
