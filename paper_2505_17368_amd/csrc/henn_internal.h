@@ -437,11 +437,13 @@ void prune_graph(const float* vec, int64_t size, int dpad, int nchunks, int metr
 void pick_lanes(int nchunks, int requested_lpn, int* lpn, int* cpl);
 
 // The same for the kernels that take a wave a row (ring keys, re-rank, merges,
-// repair): at most two chunks a lane.  There are always enough waves, so they
-// gain from reading longer runs of a row at once and from fewer registers:
-// 500,000 x 128 with 8 x 2 instead of 4 x 4, ring keys 3.7 -> 2.2 ms, re-rank
-// 4.4 -> 3.3 ms, merge 2.8 -> 2.0 ms; 16 x 1 measures the same.  (Ring hits,
-// with few rows a centre, lose: 0.67 -> 0.83 ms.)
+// repair, pruning, the root check): at most two chunks a lane.  There are
+// always enough waves, so they gain from reading longer runs of a row at once
+// and from fewer registers: 500,000 x 128 with 8 x 2 instead of 4 x 4, ring
+// keys 3.7 -> 2.2 ms, re-rank 4.4 -> 3.3 ms, merge 2.8 -> 2.0 ms; 16 x 1
+// measures the same.  The brute force for rows that nothing proves takes them
+// too: 2,495 rows of 100,000 x 128, 15.0 -> 10.1 ms.  (Ring hits, with few
+// rows a centre, lose: 0.67 -> 0.83 ms.)
 void pick_row_lanes(int nchunks, int* lpn, int* cpl);
 
 // The same for a search of nq queries.  Few lanes a row put more rows into

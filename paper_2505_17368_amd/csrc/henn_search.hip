@@ -15,10 +15,12 @@
 // entries; a forgotten node that comes back is either already in W (caught
 // by the duplicate check) or no better than W's worst (rejected again).
 //
-// Per expansion: 16 neighbour ids (one 64-byte load), the visited filter,
-// coalesced gathers of the fresh neighbours' rows (LPN lanes per row, each
-// lane a run of CPL 8-coordinate chunks), the canonical FP32 reduction
-// (henn_device.h), and a merge of the new keys into W by rank computation.
+// Per expansion: one adjacency row (a lane a neighbour), the visited filter,
+// gathers of the fresh neighbours' rows (LPN lanes per row, each lane a run of
+// CPL 8-coordinate chunks; up to kGatherRows rows a lane group in flight), the
+// canonical FP32 reduction (henn_device.h), and the new keys' way into W: one
+// insertion each where W is in registers, with the next entry's adjacency row
+// read ahead, or a merge by rank computation in LDS.
 // Precision forms traverse BF16 / FP8 rows and re-rank the first
 // min(|W|, rerank_factor*k) entries from the FP32 copy at the end.
 //
