@@ -61,7 +61,8 @@ def parse():
     ap.add_argument("--degree", type=int, default=32)
     ap.add_argument("--max-degree", type=int, default=60)
     ap.add_argument("--gram", default="split", choices=["split", "fp32"],
-                    help="kNN graph Gram tiles: split BF16 (default) or FP32 matrix cores")
+                    help="kNN graph Gram tiles: the default forms (FP16, then split BF16 and "
+                         "FP32 for the rows it leaves) or FP32 matrix cores alone")
     ap.add_argument("--root-max", type=int, default=4096)
     ap.add_argument("--no-cpu", action="store_true")
     ap.add_argument("--shape", default=None,
