@@ -1215,13 +1215,13 @@ __device__ void finish_query(const SearchArgs& a, const float (&q)[CPL][8], int 
   wave_sync();
 }
 
-// The per-query time output, read from the kernel's argument segment at the
-// point of use (SearchArgs is the first argument of every kernel that calls
-// search_one, so it starts the segment) through an opaque pointer: the
-// traversal keeps its scalar registers full, and a pointer held across it
-// would spill.
-__device__ __forceinline__ int64_t* query_ns_arg() {
-  auto* kp = __builtin_amdgcn_kernarg_segment_ptr();
+// The per-query time output, read from the kernel's argument segment (where a
+// is) at the point of use through an opaque pointer: the traversal keeps its
+// scalar registers full, and a pointer held across it would spill.  The
+// segment's address comes from the kernel: asked for here, it is null wherever
+// the compiler makes a called function of search_one.
+__device__ __forceinline__ int64_t* query_ns_arg(const SearchArgs& a) {
+  auto* kp = (const __attribute__((address_space(4))) char*)&a;
   asm volatile("" : "+s"(kp));
   return reinterpret_cast<const SearchArgs*>((const char*)kp)->query_ns;
 }
@@ -1232,7 +1232,7 @@ __device__ void search_one(const SearchArgs& a, int64_t qi, WaveLds s) {
   // the constant-rate clock when times are asked for; the start waits in the
   // query's output word (volatile: a memory round trip, so no register stays
   // live across the traversal)
-  if (int64_t* qt = query_ns_arg()) {
+  if (int64_t* qt = query_ns_arg(a)) {
     if (s.lane == 0) *reinterpret_cast<volatile int64_t*>(qt + qi) = (int64_t)wall_clock64();
   }
   const int t = s.lane % LPN;
@@ -1257,7 +1257,7 @@ __device__ void search_one(const SearchArgs& a, int64_t qi, WaveLds s) {
   finish_query<KIND, LPN, CPL>(a, q, s.lane, W, st, a.out_ids + qi * a.k_max,
                                a.out_dist + qi * a.k_max,
                                a.counters ? a.counters + qi * 4 : nullptr);
-  int64_t* qt = query_ns_arg();
+  int64_t* qt = query_ns_arg(a);
   if (qt && s.lane == 0) {
     volatile int64_t* slot = reinterpret_cast<volatile int64_t*>(qt + qi);
     const uint32_t ticks = (uint32_t)((uint64_t)wall_clock64() - (uint64_t)*slot);
